@@ -288,13 +288,14 @@ int rt3d_adjoint_emergent(rt3d_ctx *ctx, const double *g_em, double tol, int max
 /* ---- sweep workgroup shape and its tuning -------------------------------------------------- */
 
 /* The sweep workgroup shapes: shape i runs threads[i] threads, each carrying lines[i] lines of
- * both directions of an x-mirrored direction pair.  Fills min(count, max_n) entries of the arrays
- * (either may be NULL) and returns the count.  Host-only. */
+ * both directions of an x-mirrored direction pair.  (With rows of up to 512 columns a thread carries 1 or 4
+ * lines: threads[i] is then the largest workgroup, and with lines[i] > 2 no thread carries fewer than 4.)
+ * Fills min(count, max_n) entries of the arrays (either may be NULL) and returns the count.  Host-only. */
 int rt3d_sweep_shapes(int *threads, int *lines, int max_n);
 
 /* Rebuild the sweep plan (bands and work items) for a shape; medium, J and Lambda* are kept, and
- * the results change only by the summation order of the partial planes.  Errors: RT3D_ERR_ARG
- * (shape out of range, or its bands do not fit the grid; the context is unchanged), RT3D_ERR_OOM,
+ * the results change only by the summation order of the partial planes (not at all with rows of up to 512
+ * columns).  Errors: RT3D_ERR_ARG (shape out of range, or its bands do not fit the grid; the context is unchanged), RT3D_ERR_OOM,
  * RT3D_ERR_HIP (after these two the context cannot sweep -- RT3D_ERR_STATE -- until a later call
  * succeeds). */
 int rt3d_set_sweep_shape(rt3d_ctx *ctx, int shape);
@@ -407,7 +408,8 @@ int rt3d_batch_get_stats(rt3d_batch *b, char *json_buf, int buflen);
  * device buffers valid on hip_stream (a hipStream_t; NULL = the default stream).  The grid descriptor
  * is taken as for rt3d_create (bottom_bc 0 or 1; the LTE-diffusion condition needs a context), with
  * the default sweep shape (shape 0 of rt3d_sweep_shapes); J_fs is bitwise what rt3d_formal_solution
- * of a context with that shape gives for the same S and boundary light.  The library allocates no
+ * of a context with that shape gives for the same S and boundary light (to rounding where only the smaller
+ * partial planes of larger bands fit the array, about 3.3 million voxels with 16 x 16 angles).  The library allocates no
  * device memory for it: the packed medium, the plan's tables and the partial planes live in a
  * file-scope device array of 128 MiB per device (held from the library's load until the process
  * ends); direction pairs are swept in ranges whose partial planes fit.  Host memory is used for the

@@ -282,7 +282,7 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
     SweepArgs w{};
     w.nx = c->g.nx; w.ny = c->g.ny; w.nz = c->g.nz;
     w.n_down = c->A.n_dir / 2;
-    w.pseg = c->pseg; w.player = c->player; w.pairs = c->pairs; w.items = c->items;
+    w.pseg = c->pseg; w.player = c->player; w.cseg = c->cseg; w.pairs = c->pairs; w.items = c->items;
     w.cs = c->cs;
     w.Ibot = nullptr;
     w.I_top = 0.0;
@@ -290,17 +290,11 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
     w.Iem = nullptr;
     w.Iem_base = nullptr;
     w.xtab = c->xtab;
-    const size_t smem = sweep_smem_bytes(c->plan, false);
-    const dim3 grid(c->plan.items.size());
-    with_sweep_shape(c->sweep_shape, [&](auto tag) {
-        using Tag = decltype(tag);
-        hipLaunchKernelGGL((sweep_kernel<double, Tag::threads, Tag::lines>), grid, dim3(Tag::threads), smem,
-                           c->stream, w);
-    });
+    launch_sweep_kernel(w, c->plan, c->sweep_shape, int(c->plan.items.size()), false, c->stream);
     if ((rc = check_launch(c, "sweep_kernel (adjoint)"))) return rc;
     ReduceArgs ra{};
     ra.nx = c->g.nx; ra.ny = c->g.ny; ra.nz = c->g.nz; ra.n_pair = c->plan.n_pair;
-    ra.pairs = c->pairs; ra.row_min = c->row_min; ra.P = c->P; ra.chi = c->chi;
+    ra.pairs = c->pairs; ra.blocks = c->blocks; ra.P = c->P; ra.chi = c->chi;
     ra.J = c->adj_nu; ra.base = c->adj_f; ra.Jfs = c->adj_fs; ra.rb = c->adj_r;
     hipLaunchKernelGGL(reduce_kernel_pair<double>,
                        dim3(((c->g.nx + 1) / 2 * c->g.ny + kPlaneThreads - 1) / kPlaneThreads, c->g.nz),

@@ -134,6 +134,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kBatchSweepM
     sweep_body<real, NT, LPT>(a, bi.item, smem_raw);
 }
 
+// Members whose plans have the column form
+template <typename real>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void column_sweep_kernel_batch(
+    const SweepArgs *args, const BatchItem *items, const MemberState *st, int want)
+{
+    extern __shared__ unsigned char smem_raw[];
+    const BatchItem bi = uniform_copy(items[blockIdx.x]);
+    if (st && st[bi.member].mode != want) return;
+    const SweepArgs a = args[bi.member];
+    column_sweep_body<real>(a, bi.item, smem_raw);
+}
+
 template <typename real>
 __global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_batch(const ReduceArgs *args, const PlaneBlock *blocks,
                                                                      const MemberState *st, int want)
@@ -364,11 +376,13 @@ struct rt3d_batch {
     AaArgs *d_aa = nullptr;            // [n] (window slots come from the member state)
     JacobiArgs *d_jac = nullptr;       // [M][n]
     int jac_M = 0;
-    BatchItem *d_items = nullptr;
+    BatchItem *d_items = nullptr;      // bands of the members in the window form, then in the column form
     PlaneBlock *d_planes = nullptr, *d_columns = nullptr;
     PlaneBlock *d_pplanes = nullptr;   // the reduction's blocks: chunks of voxel pairs of a row
-    int n_items = 0, n_planes = 0, n_columns = 0, n_pplanes = 0;
-    size_t smem64 = 0, smem32 = 0;
+    int n_window = 0, n_column = 0, n_planes = 0, n_columns = 0, n_pplanes = 0;
+    size_t smem64 = 0, smem32 = 0;     // LDS of the window form's workgroups
+    int col_threads = 64, col_rows = 1;   // threads, rows per thread and LDS of the column form's
+    size_t col_smem64 = 0, col_smem32 = 0;
     long max_V = 0;
     bool tables_ok = false;            // argument arrays and block tables match the members
     bool plans_ok = true;              // false after a failed shape change
@@ -513,10 +527,12 @@ int build_tables(rt3d_batch *b)
     std::vector<NgArgs> ng(n);
     std::vector<AaArgs> aa(n);
     std::vector<MemberScalars> sc(n);
-    std::vector<std::pair<double, BatchItem>> work;
+    std::vector<std::pair<double, BatchItem>> work, column_work;
     std::vector<PlaneBlock> planes, columns, pplanes;
     const SweepShape sh = kSweepShapes[b->shape];
-    b->smem64 = b->smem32 = 0;
+    b->smem64 = b->smem32 = b->col_smem64 = b->col_smem32 = 0;
+    b->col_threads = 64;
+    b->col_rows = 1;
     b->max_V = 0;
     for (int i = 0; i < n; ++i) {
         rt3d_ctx *c = b->m[i];
@@ -533,7 +549,7 @@ int build_tables(rt3d_batch *b)
             SweepArgs &s = sw[v * n + i];
             s.nx = nx; s.ny = ny; s.nz = nz;
             s.n_down = c->A.n_dir / 2;
-            s.pseg = c->pseg; s.player = c->player; s.pairs = c->pairs; s.items = c->items;
+            s.pseg = c->pseg; s.player = c->player; s.cseg = c->cseg; s.pairs = c->pairs; s.items = c->items;
             s.cs = c->cs;
             s.Ibot = (c->g.bottom_bc != 1 && !diff) ? c->B : nullptr;
             s.Islope = (c->g.bottom_bc == 2 && !diff) ? c->bot_slope : nullptr;
@@ -546,7 +562,7 @@ int build_tables(rt3d_batch *b)
         for (int v = 0; v < 3; ++v) {
             ReduceArgs &a = red[v * n + i];
             a.nx = nx; a.ny = ny; a.nz = nz; a.n_pair = c->plan.n_pair;
-            a.pairs = c->pairs; a.row_min = c->row_min; a.P = c->P; a.chi = c->chi;
+            a.pairs = c->pairs; a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
             a.J = c->J; a.Jfs = c->Jfs;
             a.base = v == 1 ? c->Fa : nullptr;
             a.rb = v == 2 ? nullptr : c->r;
@@ -562,14 +578,24 @@ int build_tables(rt3d_batch *b)
         AaArgs &w = aa[i];
         w.V = c->V; w.k = 0; w.X = c->aa_x; w.G = c->aa_g; w.work = c->aa_work; w.J = c->J;
         sc[i] = MemberScalars{c->d_maxrel, c->d_maxdist, c->d_flag};
-        b->smem64 = std::max(b->smem64, sweep_smem_bytes(c->plan, false));
-        b->smem32 = std::max(b->smem32, sweep_smem_bytes(c->plan, true));
-        // sweep work: a band costs about (segments over all layers) x (line slots per thread)
-        for (const WorkItem &it : c->plan.items) {
-            double segs = 0.0;
-            for (int z = 0; z < nz; ++z) segs += c->plan.player[size_t(it.pair) * nz + z].ns;
-            const double slots = std::ceil(double(it.rows) * nx / sh.threads);
-            work.push_back({segs * slots, BatchItem{i, it}});
+        if (c->plan.columns) {
+            // the longest chains of segments first, as in a single problem
+            b->col_threads = std::max(b->col_threads, c->plan.block_threads);
+            b->col_rows = std::max(b->col_rows, c->plan.col_rows);
+            for (const WorkItem &it : c->plan.items) {
+                const rt3d::PairInfo &pi = c->plan.pairs[it.pair];
+                column_work.push_back({pi.n_seg * rt3d::column_segment_cycles(pi.split ? 1 : rt3d::kColumnRows), BatchItem{i, it}});
+            }
+        } else {
+            b->smem64 = std::max(b->smem64, sweep_smem_bytes(c->plan, false));
+            b->smem32 = std::max(b->smem32, sweep_smem_bytes(c->plan, true));
+            // sweep work: a band costs about (segments over all layers) x (line slots per thread)
+            for (const WorkItem &it : c->plan.items) {
+                double segs = 0.0;
+                for (int z = 0; z < nz; ++z) segs += c->plan.player[size_t(it.pair) * nz + z].ns;
+                const double slots = std::ceil(double(it.rows) * nx / sh.threads);
+                work.push_back({segs * slots, BatchItem{i, it}});
+            }
         }
         const int chunks = (nx * ny + kPlaneThreads - 1) / kPlaneThreads;
         for (int z = 0; z < nz; ++z)
@@ -592,11 +618,17 @@ int build_tables(rt3d_batch *b)
         }
     }
     // dispatch the most expensive bands of all members first
-    std::stable_sort(work.begin(), work.end(), [](const std::pair<double, BatchItem> &x,
-                                                  const std::pair<double, BatchItem> &y) { return x.first > y.first; });
     std::vector<BatchItem> items;
-    items.reserve(work.size());
-    for (auto &w : work) items.push_back(w.second);
+    items.reserve(work.size() + column_work.size());
+    for (auto *list : {&work, &column_work}) {
+        std::stable_sort(list->begin(), list->end(),
+                         [](const std::pair<double, BatchItem> &x, const std::pair<double, BatchItem> &y) {
+                             return x.first > y.first;
+                         });
+        for (auto &w : *list) items.push_back(w.second);
+    }
+    b->col_smem64 = size_t(b->col_threads) * column_edge<double>(b->col_rows) * sizeof(double);
+    b->col_smem32 = size_t(b->col_threads) * column_edge<float>(b->col_rows) * sizeof(float);
     int rc = RT3D_OK;
     auto chk = [&](int r) { if (!rc) rc = r; };
     chk(bupload(b, b->d_src, src)); chk(bupload(b, b->d_sw, sw)); chk(bupload(b, b->d_red, red));
@@ -607,7 +639,8 @@ int build_tables(rt3d_batch *b)
     if (rc) return rc;
     if (!b->d_state) BHIP_TRY(b, hipMalloc(reinterpret_cast<void **>(&b->d_state), n * sizeof(MemberState)), "hipMalloc");
     if (!b->d_params) BHIP_TRY(b, hipMalloc(reinterpret_cast<void **>(&b->d_params), sizeof(BatchParams)), "hipMalloc");
-    b->n_items = int(items.size());
+    b->n_window = int(work.size());
+    b->n_column = int(column_work.size());
     b->n_planes = int(planes.size());
     b->n_columns = int(columns.size());
     b->n_pplanes = int(pplanes.size());
@@ -674,7 +707,17 @@ int launch_check(rt3d_batch *b, const char *what)
 // sweep launch of one precision for the members in mode 'want' (st null: all members)
 int launch_sweep_batch(rt3d_batch *b, bool fp32, const SweepArgs *args, const MemberState *st, int want)
 {
-    const dim3 grid(b->n_items);
+    if (b->n_column > 0) {
+        const dim3 grid(b->n_column), blk(b->col_threads);
+        const BatchItem *items = b->d_items + b->n_window;
+        if (fp32)
+            hipLaunchKernelGGL(column_sweep_kernel_batch<float>, grid, blk, b->col_smem32, b->stream, args, items, st, want);
+        else
+            hipLaunchKernelGGL(column_sweep_kernel_batch<double>, grid, blk, b->col_smem64, b->stream, args, items, st, want);
+        const int rc = launch_check(b, "column_sweep_kernel_batch");
+        if (rc || b->n_window == 0) return rc;
+    }
+    const dim3 grid(b->n_window);
     const size_t smem = fp32 ? b->smem32 : b->smem64;
 #define RT3D_BATCH_SWEEP(NT_, LPT_)                                                                \
     do {                                                                                           \
@@ -836,8 +879,15 @@ int rt3d_batch_create(rt3d_batch **out, int n_members, const rt3d_grid_desc *des
     int rc = RT3D_OK;
     std::string msg;
     b->m.assign(n_members, nullptr);
+    // one launch sweeps all members
+    double load = 0.0;
+    for (int i = 0; i < n_members; ++i) {
+        rt3d::AngleSet A;
+        if (rt3d::make_angle_set(descs[i].n_theta, descs[i].n_phi, A))
+            load += rt3d::column_load(descs[i].nx, descs[i].ny, descs[i].nz, A);
+    }
     for (int i = 0; i < n_members && !rc; ++i) {
-        rc = create_ctx(&b->m[i], &descs[i], precision, b->stream, sweep_shape, msg);
+        rc = create_ctx(&b->m[i], &descs[i], precision, b->stream, sweep_shape, msg, load);
         if (rc) msg = "member " + std::to_string(i) + ": " + msg;
     }
     if (!rc) {
@@ -1201,7 +1251,7 @@ int rt3d_batch_get_stats(rt3d_batch *b, char *buf, int buflen)
                   "\"iters_min\":%ld,\"iters_max\":%ld,\"iters_sum\":%ld}",
                   b->n, b->precision == RT3D_FP64 ? "fp64" : "fp32_sweep", b->shape,
                   b->shape >= 0 ? kSweepShapes[b->shape].threads : 0, b->shape >= 0 ? kSweepShapes[b->shape].lines : 0,
-                  vox, vox_dir, bytes, b->n_items, b->n_planes, b->graph_M, b->replays, b->polls, b->solve_ms,
+                  vox, vox_dir, bytes, b->n_window + b->n_column, b->n_planes, b->graph_M, b->replays, b->polls, b->solve_ms,
                   it_min < 0 ? 0 : it_min, it_max, it_sum);
     const std::string s = tmp;
     if (int(s.size()) + 1 > buflen) return bfail(b, RT3D_ERR_ARG, "stats buffer too small");

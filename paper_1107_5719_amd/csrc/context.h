@@ -31,6 +31,7 @@ struct rt3d_ctx {
     size_t real_size = 8;
     int lstar_early_exit = 0;
     int sweep_shape = 0;       // index into kSweepShapes
+    double sweep_load = 0.0;   // work of the launch that holds this context's sweep (0: its own; see column_load)
     int os_method = RT3D_OS_JACOBI;   // inner solve of the OS step
     double anchor_ratio = kAnchorRatioDefault;   // FP32 form: re-anchor when c < ratio * max|J - Ja|/|J|
     int jacobi_xcd = 4;        // Jacobi grid: 0 plain, 1 chunks padded to 8 per plane, 2 contiguous chunk
@@ -60,7 +61,9 @@ struct rt3d_ctx {
     double c_last = INFINITY, da_last = 0.0;
     long fp64_sweeps = 0, fp32_sweeps = 0;
     int *seg_off = nullptr, *seg_n = nullptr, *seg_a = nullptr, *seg_bb = nullptr, *seg_bm = nullptr;
-    int *seg_ai = nullptr, *seg_bi = nullptr, *row_min = nullptr;
+    int *seg_ai = nullptr, *seg_bi = nullptr;
+    rt3d::LayerBlock *blocks = nullptr;
+    rt3d::ColumnSeg *cseg = nullptr;
     rt3d::DirInfo *dirs = nullptr;
     rt3d::PairInfo *pairs = nullptr;
     rt3d::PairSeg *pseg = nullptr;
@@ -128,11 +131,12 @@ int n_sweep_shapes();
 
 // New context with the given sweep shape (index into the shape table); stream may be null.
 int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream_t stream, int shape,
-               std::string &msg);
+               std::string &msg, double load = 0.0);
 // The sweep plan of a grid and angle set for a shape, on the host (no device work); false with the
 // reason in msg when the grid does not fit the sweep kernel's line and LDS budgets.
+// load: as rt3d_ctx::sweep_load.  columns: take the column form of the sweep where the grid allows it.
 bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3d::SweepPlan &plan,
-                std::string &msg);
+                std::string &msg, double load = 0.0, bool columns = true);
 // (Re)build the sweep plan for a shape (or take the given one) and upload its tables; Lambda* and
 // the state are kept.
 int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built = nullptr);

@@ -192,6 +192,16 @@ static int pos_mod(int a, int n)
     return r < 0 ? r + n : r;
 }
 
+// dispatch the most expensive work items first
+static void sort_work(std::vector<std::pair<double, WorkItem>> &work, SweepPlan &P)
+{
+    std::stable_sort(work.begin(), work.end(),
+                     [](const std::pair<double, WorkItem> &x, const std::pair<double, WorkItem> &y) {
+                         return x.first > y.first;
+                     });
+    for (auto &w : work) P.items.push_back(w.second);
+}
+
 bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
                       size_t lds_bytes_max, SweepPlan &P, std::string &err)
 {
@@ -340,7 +350,10 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
     for (int p = 0; p < P.n_pair; ++p) {
         PairInfo &pi = P.pairs[p];
         pi.p_off = off;
-        off += int64_t(pi.n_bands) * nz * pi.win_rows * nx;
+        pi.band_stride = int64_t(nz) * pi.win_rows * nx;
+        off += pi.n_bands * pi.band_stride;
+        for (int k = 0; k < nz; ++k)
+            P.blocks.push_back(LayerBlock{P.row_min[size_t(pi.dA) * nz + k], pi.win_rows, k * pi.win_rows * nx, 0});
         for (int b = 0; b < pi.n_bands; ++b) {
             WorkItem it;
             it.pair = p;
@@ -351,12 +364,145 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
         }
     }
     P.p_elems = off;
-    // dispatch the most expensive bands first
-    std::stable_sort(work.begin(), work.end(),
-                     [](const std::pair<double, WorkItem> &x, const std::pair<double, WorkItem> &y) {
-                         return x.first > y.first;
-                     });
-    for (auto &w : work) P.items.push_back(w.second);
+    sort_work(work, P);
+    return true;
+}
+
+namespace {
+
+// Whether a pair with n_seg segments is split into single line rows.  A sweep lasts at least as long as the
+// chain of the longest lines: with R rows a wavefront alone takes about 450 + 165 R cycles per segment
+// (measured on 17^3 and 65^3 grids, where nothing else runs beside the shallowest directions), of which the
+// rows share the first term, so single rows make the chain short and four make the sum of all work (and
+// the partial planes) small.  A pair is split where the chain of four rows would take longer than 1.2 times
+// the launch's whole work (about 150 cycles per wavefront and segment) spread over all SIMDs.
+bool column_split(double n_seg, double load)
+{
+    return n_seg * column_segment_cycles(kColumnRows) > 1.2 * load * 150.0 / 1024.0;
+}
+
+// Bands of one workgroup: a thread per column, so G bands of nx columns fill G nx of its lanes.  The
+// waves of a workgroup go to the four SIMDs of a CU in turn, the first always to the first one, so 5 waves
+// load a SIMD as much as 8 do (129 columns: 5, 7 and 9 waves 2.33, 1.98 and 2.41 ms at 129^3 x 256).  G
+// maximises the lanes in use over that, less a little per wave, since large workgroups wait longer at
+// their barriers.  A grid that leaves the chip short of waves (fill: waves per SIMD with one row per
+// thread) takes single waves instead (33^3 x 64: 63 us against 72 with 4 waves).
+int column_bands(int nx, int n_bands, double fill, int max_waves)
+{
+    const int most = std::max(1, std::min({1024 / nx, n_bands, 64 * max_waves / nx}));
+    if (fill < 3.0) return std::min(most, std::max(1, 64 / nx));
+    static const double load[8] = {1.3, 2.5, 3.3, 4.0, 8.0, 8.0, 7.5, 8.0};
+    const double per_wave = fill < 12.0 ? 0.04 : 0.02;
+    int best = 1;
+    double best_score = -1e9;
+    for (int G = 1; G <= most; ++G) {
+        const int w = (G * nx + 63) / 64;
+        const double l = load[(w - 1) % 8] + 8.0 * ((w - 1) / 8);
+        const double score = G * nx / (64.0 * l) - per_wave * w;
+        if (score > best_score) {
+            best = G;
+            best_score = score;
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
+double column_load(int nx, int ny, int nz, const AngleSet &A)
+{
+    // 1 + tan(theta) (|cos phi| + |sin phi|) segments per layer on average
+    double seg = 0.0;
+    for (int d = 0; d < A.n_dir; ++d) seg += 1.0 + (std::fabs(A.ox[d]) + std::fabs(A.oy[d])) / std::fabs(A.mu[d]);
+    return 0.5 * seg * nz * (double(nx) * ny / 64.0);
+}
+
+bool make_column_plan(const AngleSet &A, int threads, int lines, double load, SweepPlan &plan)
+{
+    if (plan.nx > kColumnMaxNx) return false;
+    SweepPlan P = plan;
+    const int nx = P.nx, ny = P.ny, nz = P.nz;
+    P.columns = true;
+    P.cseg.clear();
+    P.pseg.clear();
+    P.player.clear();
+    P.blocks.assign(size_t(P.n_pair) * nz, LayerBlock{});
+    P.items.clear();
+    P.max_win_rows = 0;
+    P.block_threads = 64;
+    P.col_rows = 1;
+    // waves per SIMD of the launch, if its other members are like this one
+    const double fill = double(nx) * ny / 64.0 * P.n_pair / 1024.0 * load / column_load(nx, ny, nz, A);
+    std::vector<std::pair<double, WorkItem>> work;
+    int64_t off = 0;
+    for (int p = 0; p < P.n_pair; ++p) {
+        PairInfo &pi = P.pairs[p];
+        int n_seg = 0;
+        for (int k = 0; k < nz; ++k) n_seg += P.seg_n[size_t(pi.dA) * nz + k];
+        pi.split = lines <= 2 && column_split(n_seg, load) ? 1 : 0;
+        const int rows = pi.split ? 1 : kColumnRows;
+        const int n_parts = (ny + rows - 1) / rows;       // bands, or line rows
+        const int G = column_bands(nx, n_parts, fill, std::max(1, threads / 64));
+        P.block_threads = std::max(P.block_threads, (G * nx + 63) / 64 * 64);
+        P.col_rows = std::max(P.col_rows, rows);
+        pi.band_rows = kColumnRows;
+        pi.n_bands = (ny + kColumnRows - 1) / kColumnRows;
+        pi.last_rows = ny - (pi.n_bands - 1) * kColumnRows;
+        pi.inv_rows = 1.0f / float(kColumnRows);
+        pi.xsgn = A.ox[pi.dA] > 0.0 ? 1 : -1;
+        pi.ysgn = A.oy[pi.dA] > 0.0 ? 1 : -1;
+        pi.c_off = int(P.cseg.size());
+        pi.n_seg = n_seg;
+        pi.win_rows = 0;
+        int64_t block = 0;
+        int prev_i = 0, prev_j = 0;
+        size_t prev_end = 0;                   // the last segment of the layer before
+        for (int st = 0; st < nz; ++st) {
+            const int k = pi.down ? nz - 1 - st : st;
+            const size_t ka = size_t(pi.dA) * nz + k;
+            const int o = P.seg_off[ka], n = P.seg_n[ka];
+            int jmin = P.seg_bi[o], jmax = jmin;
+            for (int s = 0; s < n; ++s) {
+                const int i = P.seg_ai[o + s], j = P.seg_bi[o + s];
+                jmin = std::min(jmin, j);
+                jmax = std::max(jmax, j);
+                if (st == 0 && s == 0) {
+                    pi.row0 = pos_mod(j, ny);
+                } else {
+                    if (i != prev_i) P.cseg.back().flags |= kNextColumn;
+                    if (j != prev_j) P.cseg.back().flags |= kNextRow;
+                }
+                P.cseg.push_back(ColumnSeg{P.seg_len[o + s], s + 1 == n ? kLayerEnd : 0, 0});
+                prev_i = i;
+                prev_j = j;
+                pi.sa_last = P.seg_a[o + s];
+            }
+            const int cover = rows + jmax - jmin;
+            if (st == 0) pi.cover0 = cover;
+            else P.cseg[prev_end].cover = cover;
+            prev_end = P.cseg.size() - 1;
+            pi.win_rows = std::max(pi.win_rows, cover);
+            P.blocks[size_t(p) * nz + k] = LayerBlock{P.row_min[ka], cover, int(block), 0};
+            block += int64_t(cover) * nx;
+        }
+        pi.band_stride = block;
+        pi.p_off = off;
+        off += n_parts * block;
+        // the kernel addresses a workgroup's bands with 32-bit byte offsets
+        if (G * block * int64_t(sizeof(double)) >= (int64_t(1) << 32) - 16) return false;
+        P.max_win_rows = std::max(P.max_win_rows, pi.win_rows);
+        for (int b = 0; b < n_parts; b += G) {
+            WorkItem it;
+            it.pair = p;
+            it.band = b;
+            it.j0 = b * rows;
+            it.rows = std::min(G, n_parts - b);
+            work.push_back({n_seg * column_segment_cycles(rows), it});
+        }
+    }
+    P.p_elems = off;
+    sort_work(work, P);
+    plan = std::move(P);
     return true;
 }
 

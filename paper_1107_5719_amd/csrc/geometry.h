@@ -58,6 +58,30 @@ struct PairInfo {
     float inv_rows;    // 1 / Bj (band lookup; corrected exactly in the kernel)
     int64_t p_off;     // element offset of this pair's partial planes in P
     double mu;         // direction cosine with the z axis (the same for both)
+    int64_t band_stride;   // elements of P per band
+    // column form: bands of kColumnRows line rows, either each held by one thread per column, or (split) each
+    // line row by a thread of its own with partial planes of its own (band_stride is then a line row's)
+    int split;
+    int c_off, n_seg;  // the pair's segments in the list: first entry, count
+    int xsgn, ysgn;    // signs of direction A's column moves and of both directions' row moves
+    int row0;          // row offset of the first segment modulo ny
+    int cover0;        // rows that a band (split: a line row) touches in the first layer
+    int sa_last;       // direction A's column offset at the last segment modulo nx
+};
+
+// A segment as the column form of the sweep reads it, in sweep order: its length, what follows it, and,
+// where its layer ends, the rows that a band (split: a line row) touches in the next layer.
+enum { kNextColumn = 1, kNextRow = 2, kLayerEnd = 4 };   // the lines change columns / rows, the layer ends
+struct ColumnSeg {
+    double len;
+    int flags, cover;
+};
+
+// Where the reduction finds a pair's partial planes of one layer: the layer's first row offset (modulo
+// ny), the rows that a band (split: a line row) touches in it, and its block's offset in that band's part
+// of P.
+struct LayerBlock {
+    int rmin, cover, off, pad;
 };
 
 // Segment s of a pair in one layer, packed for one scalar load: the column offset of direction A
@@ -77,7 +101,8 @@ struct PairLayer {
     int off, ns, rmin, pad;
 };
 
-// One workgroup of the sweep: direction pair p, band of line rows [j0, j0 + rows).
+// One workgroup of the sweep: direction pair p, band of line rows [j0, j0 + rows); in the column form the
+// rows bands from band on, the first starting at line row j0.
 struct WorkItem {
     int pair, band, j0, rows;
 };
@@ -97,6 +122,12 @@ struct SweepPlan {
     std::vector<PairInfo> pairs;
     std::vector<PairSeg> pseg;            // packed per-pair segments
     std::vector<PairLayer> player;        // per (pair, layer): index pair * nz + k
+    std::vector<LayerBlock> blocks;       // per (pair, layer): index pair * nz + k
+    // column form (the window form's pseg and player are empty then)
+    bool columns = false;
+    int col_rows = 0;                     // most rows per thread of any pair
+    int block_threads = 0;                // threads of a workgroup
+    std::vector<ColumnSeg> cseg;
     std::vector<WorkItem> items;          // in dispatch order (most expensive first)
     int64_t p_elems = 0;                  // size of the partial-plane buffer P in elements
     int max_win_rows = 0;
@@ -115,5 +146,20 @@ inline size_t sweep_lds_bytes(int win_rows, int band_rows, int nx, bool f32)
 // band; lds_bytes_max bounds a band's LDS in either precision (sweep_lds_bytes).
 bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
                       size_t lds_bytes_max, SweepPlan &plan, std::string &err);
+
+// Turns a plan into the column form: a thread per column of a band (or, where the pair is split, of a line
+// row), workgroups of at most about threads threads that hold several bands (line rows) of a pair; a work
+// item's band and rows count those.  load: what the launch that sweeps this plan has to do (this plan's own,
+// or the sum over the members of a batch), see column_load.  lines > 2: no pair is split.  The sums of a
+// voxel's deposits have the same order whether a pair is split or not.  Rows of more than kColumnMaxNx
+// columns keep the window form (false is returned and the plan left as it is): there one row fills a workgroup
+// by itself.
+constexpr int kColumnMaxNx = 512;
+constexpr int kColumnRows = 4;
+bool make_column_plan(const AngleSet &A, int threads, int lines, double load, SweepPlan &plan);
+// Wavefronts times segments of a grid's sweep, one line row per thread
+double column_load(int nx, int ny, int nz, const AngleSet &A);
+// Cycles per segment of a wavefront of the column form that has its SIMD to itself, with rows line rows
+inline double column_segment_cycles(int rows) { return 450.0 + 165.0 * rows; }
 
 }  // namespace rt3d

@@ -7,6 +7,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <cstring>
 #include <type_traits>
 
 #include "geometry.h"
@@ -16,9 +19,11 @@ using rt3d::WorkItem;
 
 namespace {
 
-// Sweep workgroup shapes (threads, lines per thread and direction); the context picks one.
+// Sweep workgroup shapes (threads, lines per thread and direction); the context picks one.  The column form
+// takes from a shape only the threads that a workgroup may have and, with more than 2 lines, never splits
+// a pair into single rows.
 struct SweepShape { int threads, lines; };
-// Measured on MI355X at 129^3 x 256: 512 x 2 is fastest (64 VGPRs, 8 waves/SIMD; the sweep is
+// Measured on MI355X at 129^3 x 256 in the window form: 512 x 2 is fastest (64 VGPRs, 8 waves/SIMD; the sweep is
 // latency-bound, so occupancy beats lines per thread and prefetching).
 constexpr SweepShape kSweepShapes[] = {{512, 2}, {512, 4}, {256, 8}, {1024, 2}, {256, 4}, {256, 2}};
 // Calls f(NT, LPT) (as integral constants) for the sweep shape with the given index.
@@ -42,10 +47,16 @@ constexpr size_t kWindowBytes = 48 * 1024;   // LDS budget of a band (deposit wi
 // the 160 KB of LDS a gfx950 workgroup may use (the rest holds the kernel's static LDS): one workgroup
 // per CU then, but no width limit below the line budget of a workgroup.
 constexpr size_t kWindowBytesWide = 156 * 1024;
-// Dynamic LDS of a sweep workgroup: the largest window and exchange buffers of any direction pair's
-// bands (each band lays out its own within this).
+// LDS elements that one thread of a column sweep passes its lines through at an x-face: two buffers of both
+// lines of every row, padded so that the lanes' 16-byte accesses meet no bank twice.
+template <typename real> __host__ __device__ constexpr int column_edge(int rows) { return 4 * rows + 16 / int(sizeof(real)); }
+// Dynamic LDS of a sweep workgroup.  Column form: column_edge of every thread.  Window form: the largest window
+// and exchange buffers of any direction pair's bands (each band lays out its own within this).
 inline size_t sweep_smem_bytes(const rt3d::SweepPlan &plan, bool f32)
 {
+    if (plan.columns)
+        return size_t(plan.block_threads) *
+               (f32 ? column_edge<float>(plan.col_rows) * sizeof(float) : column_edge<double>(plan.col_rows) * sizeof(double));
     size_t bytes = 0;
     for (const rt3d::PairInfo &pi : plan.pairs)
         bytes = std::max(bytes, rt3d::sweep_lds_bytes(pi.win_rows, pi.band_rows, plan.nx, f32));
@@ -82,6 +93,19 @@ constexpr double kExpStepHi = 6.93147180369123816490e-01 / 16;    // 21 trailing
 constexpr double kExpStepLo = 1.90821492927058770002e-10 / 16;
 constexpr double kExpRound = 6755399441055744.0;                   // 1.5 * 2^52
 
+// The table as exp_scale reads it: 2^(j/kExpTab) rounded to float64 from the 64-bit-mantissa long double
+// exp2, less j << (20 - kExpTabLog2) in the high word.
+inline void exp_table(double *tab)
+{
+    for (int j = 0; j < kExpTab; ++j) {
+        const double t = double(std::exp2(static_cast<long double>(j) / kExpTab));
+        uint64_t bits;
+        std::memcpy(&bits, &t, sizeof bits);
+        bits -= uint64_t(j) << (52 - kExpTabLog2);
+        std::memcpy(&tab[j], &bits, sizeof bits);
+    }
+}
+
 // a * b + c as one VOP3 v_fma_f64 with c in an SGPR pair.  For a constant addend the compiler would
 // otherwise keep c in VGPRs and copy it into the destination of a two-address v_fmac_f64 at every
 // use (a v_mov_b64 per polynomial step of every exponential in the sweep's segment loop).
@@ -103,6 +127,14 @@ __device__ inline double expm1_poly(double r)
     return p * r;
 }
 
+// 2^k T_j for n = 16 k + j (k >= -1022): the table holds T_j with j << 16 taken off its high word, so
+// that one shift-and-add of n puts k into the exponent field.
+__device__ inline double exp_scale(int n, const double *tab)
+{
+    const double t = tab[n & (kExpTab - 1)];
+    return __hiloint2double(__double2hiint(t) + int(unsigned(n) << (20 - kExpTabLog2)), __double2loint(t));
+}
+
 __device__ inline double expm1_nonpos_tab(double x, const double *tab)
 {
     x = fmax(x, -708.0);
@@ -110,7 +142,7 @@ __device__ inline double expm1_nonpos_tab(double x, const double *tab)
     const double kf = kr - kExpRound;
     const int n = __double2loint(kr);
     const double q = expm1_poly(fma(-kf, kExpStep, x));
-    const double s = ldexp(tab[n & (kExpTab - 1)], n >> kExpTabLog2);
+    const double s = exp_scale(n, tab);
     return fma(s, q, s - 1.0);
 }
 
@@ -124,7 +156,7 @@ __device__ inline void exp_pair_tab(double x, const double *tab, double &e, doub
     const double kf = kr - kExpRound;
     const int n = __double2loint(kr);
     const double q = expm1_poly(fma(-kf, kExpStepLo, fma(-kf, kExpStepHi, x)));
-    const double s = ldexp(tab[n & (kExpTab - 1)], n >> kExpTabLog2);
+    const double s = exp_scale(n, tab);
     e = fma(s, q, s);
     em1 = fma(s, q, s - 1.0);
 }
@@ -191,8 +223,9 @@ __global__ __launch_bounds__(kPlaneThreads) void source_kernel(SourceArgs a)
 
 struct SweepArgs {
     int nx, ny, nz, n_down;
-    const rt3d::PairSeg *pseg;
-    const rt3d::PairLayer *player;
+    const rt3d::PairSeg *pseg;        // window form
+    const rt3d::PairLayer *player;    // window form
+    const rt3d::ColumnSeg *cseg;      // column form
     const rt3d::PairInfo *pairs;
     const WorkItem *items;
     const void *cs;               // Vec2<real>
@@ -377,6 +410,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kSweepMinWav
     sweep_body<real, NT, LPT>(a, a.items[blockIdx.x], smem_raw);
 }
 
+}  // namespace
+
+#include "sweep_columns.h"
+
+namespace {
+
+// Launches n_items workgroups of one problem's sweep in the plan's form.
+inline void launch_sweep_kernel(const SweepArgs &a, const rt3d::SweepPlan &plan, int shape, int n_items, bool f32,
+                                hipStream_t stream)
+{
+    const size_t smem = sweep_smem_bytes(plan, f32);
+    const dim3 grid(n_items);
+    if (plan.columns) {
+        const dim3 blk(plan.block_threads);
+        if (f32) hipLaunchKernelGGL(column_sweep_kernel<float>, grid, blk, smem, stream, a);
+        else hipLaunchKernelGGL(column_sweep_kernel<double>, grid, blk, smem, stream, a);
+        return;
+    }
+    with_sweep_shape(shape, [&](auto tag) {
+        using Tag = decltype(tag);
+        if (f32)
+            hipLaunchKernelGGL((sweep_kernel<float, Tag::threads, Tag::lines>), grid, dim3(Tag::threads), smem, stream, a);
+        else
+            hipLaunchKernelGGL((sweep_kernel<double, Tag::threads, Tag::lines>), grid, dim3(Tag::threads), smem, stream, a);
+    });
+}
+
 // ------------------------------------------------------------------------------------------------
 // Angle reduction of the partial planes
 // ------------------------------------------------------------------------------------------------
@@ -384,7 +444,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kSweepMinWav
 struct ReduceArgs {
     int nx, ny, nz, n_pair;
     const rt3d::PairInfo *pairs;
-    const int *row_min;
+    const rt3d::LayerBlock *blocks;
     const void *P;            // real
     const double *chi;
     const double *J;          // for r = J_fs - J (may be null)
@@ -401,28 +461,30 @@ struct PairBands {
     const real *Pq;   // the pair's partial plane of layer k, at the voxel's column
     long o0, o1;      // elements of the band that starts the row's window offset and of the band before it
     int b1, off1;     // that earlier band (cyclically) and the row's offset in its window
+    int cover;        // rows of a full band's window in this layer (a shorter last band's has as many fewer)
+    int line_cover;   // rows of one line row's (split pairs)
 };
 
 template <typename real>
-__device__ inline PairBands<real> pair_bands(const ReduceArgs &a, const rt3d::PairInfo &pi, int i, int j, int k)
+__device__ inline PairBands<real> pair_bands(const ReduceArgs &a, const rt3d::PairInfo &pi, int q, int i, int j, int k)
 {
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int rows = pi.band_rows, nb = pi.n_bands, Hw = pi.win_rows;
-    const int rmin = a.row_min[pi.dA * nz + k];
-    int jj = j - rmin;
+    const int nx = a.nx, ny = a.ny;
+    const int rows = pi.band_rows, nb = pi.n_bands;
+    const rt3d::LayerBlock lb = a.blocks[q * a.nz + k];
+    int jj = j - lb.rmin;
     jj += (jj < 0) ? ny : 0;
     int b = min(int((float(jj) + 0.5f) * pi.inv_rows), nb - 1);
     b -= (b * rows > jj) ? 1 : 0;
     b += (b < nb - 1 && (b + 1) * rows <= jj) ? 1 : 0;
     const int off0 = jj - b * rows;
-    const long plane = long(Hw) * nx;
-    const long band_stride = long(nz) * plane;
     PairBands<real> r;
-    r.Pq = static_cast<const real *>(a.P) + pi.p_off + long(k) * plane + i;
+    r.Pq = static_cast<const real *>(a.P) + pi.p_off + lb.off + i;
     r.b1 = (b == 0) ? nb - 1 : b - 1;
     r.off1 = off0 + ((r.b1 == nb - 1) ? pi.last_rows : rows);
-    r.o0 = long(b) * band_stride + long(off0) * nx;
-    r.o1 = long(r.b1) * band_stride + long(r.off1) * nx;
+    r.o0 = long(b) * pi.band_stride + long(off0) * nx;
+    r.o1 = long(r.b1) * pi.band_stride + long(r.off1) * nx;
+    r.cover = lb.cover + (pi.split ? rows - 1 : 0);
+    r.line_cover = lb.cover;
     return r;
 }
 
@@ -431,6 +493,34 @@ __device__ inline int pair_bands_next_off(const rt3d::PairInfo &pi, int bb, int 
 {
     bb = (bb == 0) ? pi.n_bands - 1 : bb - 1;
     return off + ((bb == pi.n_bands - 1) ? pi.last_rows : pi.band_rows);
+}
+
+// Deposits of a split pair's band bb in the row at offset off of its window, for voxels (i, j, k) and the next
+// (d1 apart): its line rows' partials are added in the order that the lines come through the row and in the
+// precision of the sweep, which are the sums that a thread of an unsplit band makes.
+template <typename real>
+__device__ inline void split_band_sum(const PairBands<real> &pb, const rt3d::PairInfo &pi, int nx, int bb, int off,
+                                      int d1, double &s0, double &s1)
+{
+    constexpr int R = rt3d::kColumnRows;
+    const int n = bb == pi.n_bands - 1 ? pi.last_rows : R;
+    const int lo = max(0, off - pb.line_cover + 1), hi = min(n - 1, off);
+    real x[R], y[R];
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const int l = pi.ysgn > 0 ? max(hi - t, lo) : min(lo + t, hi);
+        const long o = long(bb * R + l) * pi.band_stride + long(off - l) * nx;
+        x[t] = pb.Pq[o];
+        y[t] = pb.Pq[o + d1];
+    }
+    real a = x[0], b = y[0];
+#pragma unroll
+    for (int t = 1; t < R; ++t) {
+        a = t <= hi - lo ? a + x[t] : a;
+        b = t <= hi - lo ? b + y[t] : b;
+    }
+    s0 = double(a);
+    s1 = double(b);
 }
 
 // The angle sum of the direction pairs [q0, q1) for voxels (i, j, k) and (i + d1, j, k) (d1 = 0: one
@@ -455,9 +545,17 @@ __device__ inline void reduce_pairs(const ReduceArgs &a, int i, int d1, int j, i
         for (int u = 0; u < U; ++u) {
             const int q = min(qb + u, q1 - 1);
             const rt3d::PairInfo pi = a.pairs[q];
-            const PairBands<real> pb = pair_bands<real>(a, pi, i, j, k);
-            m1[u] = pb.off1 < pi.win_rows;
-            more[u] = m1[u] && pair_bands_next_off(pi, pb.b1, pb.off1) < pi.win_rows;
+            const PairBands<real> pb = pair_bands<real>(a, pi, q, i, j, k);
+            m1[u] = pb.off1 < pb.cover - (pb.b1 == pi.n_bands - 1 ? pi.band_rows - pi.last_rows : 0);
+            more[u] = m1[u] && pair_bands_next_off(pi, pb.b1, pb.off1) < pb.cover;
+            if (pi.split) {
+                const int b0 = pb.b1 + 1 == pi.n_bands ? 0 : pb.b1 + 1;
+                const int off0 = pb.off1 - (pb.b1 == pi.n_bands - 1 ? pi.last_rows : pi.band_rows);
+                split_band_sum<real>(pb, pi, a.nx, b0, off0, d1, x0[u], x1[u]);
+                y0[u] = y1[u] = 0.0;
+                if (m1[u]) split_band_sum<real>(pb, pi, a.nx, pb.b1, pb.off1, d1, y0[u], y1[u]);
+                continue;
+            }
             const long o1 = m1[u] ? pb.o1 : pb.o0;
             x0[u] = double(pb.Pq[pb.o0]);
             x1[u] = double(pb.Pq[pb.o0 + d1]);
@@ -478,14 +576,20 @@ __device__ inline void reduce_pairs(const ReduceArgs &a, int i, int d1, int j, i
             }
             if (more[u]) {
                 // bands thinner than the window halo: still earlier bands cover the row
-                const PairBands<real> pb = pair_bands<real>(a, pi, i, j, k);
-                const long band_stride = long(a.nz) * pi.win_rows * a.nx;
+                const PairBands<real> pb = pair_bands<real>(a, pi, qb + u, i, j, k);
                 int bb = pb.b1, off = pb.off1;
                 while (true) {
                     off = pair_bands_next_off(pi, bb, off);
                     bb = (bb == 0) ? pi.n_bands - 1 : bb - 1;
-                    if (off >= pi.win_rows) break;
-                    const long o = long(bb) * band_stride + long(off) * a.nx;
+                    if (off >= pb.cover - (bb == pi.n_bands - 1 ? pi.band_rows - pi.last_rows : 0)) break;
+                    if (pi.split) {
+                        double z0, z1;
+                        split_band_sum<real>(pb, pi, a.nx, bb, off, d1, z0, z1);
+                        s0 += z0;
+                        s1 += z1;
+                        continue;
+                    }
+                    const long o = long(bb) * pi.band_stride + long(off) * a.nx;
                     s0 += double(pb.Pq[o]);
                     s1 += double(pb.Pq[o + d1]);
                 }

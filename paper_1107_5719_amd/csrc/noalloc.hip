@@ -102,43 +102,56 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     if (!build_plan(*g, A, 0, plan, msg)) return noalloc_fail(RT3D_ERR_ARG, msg);
     const int nx = g->nx, ny = g->ny, nz = g->nz;
     const long V = long(nx) * ny * nz;
-    const SweepShape shape = kSweepShapes[0];
 
-    // workspace layout: exponential table, {chi, S}, pair tables, layer table, pair segments, row minima,
-    // work items of every range, then the partial planes of one range of pairs
+    // workspace layout: exponential table, {chi, S}, pair tables, segments, layer blocks, work items of
+    // every range, then the partial planes of one range of pairs
     std::vector<double> tab(kExpTab);
-    for (int j = 0; j < kExpTab; ++j) tab[j] = double(std::exp2(static_cast<long double>(j) / kExpTab));
-    // ranges of pairs whose partial planes fit what the tables leave of the workspace
-    // (one copy of the pair table per range, at most one range per pair, with the partial-plane
-    // offsets relative to the range's first pair)
-    const size_t fixed = align256(tab.size() * sizeof(double)) + align256(size_t(V) * sizeof(double2)) +
-                         align256(plan.pairs.size() * plan.pairs.size() * sizeof(rt3d::PairInfo)) +
-                         align256(plan.player.size() * sizeof(rt3d::PairLayer)) +
-                         align256(plan.pseg.size() * sizeof(rt3d::PairSeg)) +
-                         align256(plan.row_min.size() * sizeof(int)) +
-                         align256(plan.items.size() * sizeof(rt3d::WorkItem));
+    exp_table(tab.data());
+    size_t fixed = 0;
+    std::vector<int> q_begin;             // pair ranges [q_begin[r], q_begin[r + 1])
+    // ranges of pairs whose partial planes fit what the tables leave of the workspace; 0 where one pair's do
+    // not
+    auto ranges = [&]() {
+        fixed = align256(tab.size() * sizeof(double)) + align256(size_t(V) * sizeof(double2)) +
+                align256(plan.pairs.size() * sizeof(rt3d::PairInfo)) +
+                align256(plan.player.size() * sizeof(rt3d::PairLayer)) +
+                align256(plan.pseg.size() * sizeof(rt3d::PairSeg)) +
+                align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg)) +
+                align256(plan.blocks.size() * sizeof(rt3d::LayerBlock)) +
+                align256(plan.items.size() * sizeof(rt3d::WorkItem));
+        q_begin.clear();
+        if (fixed >= kScratchBytes) return 0;
+        const size_t room = (kScratchBytes - fixed) / sizeof(double);
+        for (int q = 0; q < plan.n_pair;) {
+            const int64_t base = plan.pairs[q].p_off;
+            int q1 = q;
+            while (q1 < plan.n_pair) {
+                const int64_t end = q1 + 1 < plan.n_pair ? plan.pairs[q1 + 1].p_off : plan.p_elems;
+                if (size_t(end - base) > room) break;
+                ++q1;
+            }
+            if (q1 == q) return 0;
+            q_begin.push_back(q);
+            q = q1;
+        }
+        q_begin.push_back(plan.n_pair);
+        return int(q_begin.size()) - 1;
+    };
+    int n_range = ranges();
+    // a pair's planes are smaller when it is not split (as in a large launch), with the same result, and
+    // for the shallowest directions smaller still in the window form: grids that only fit so take it
+    for (int t = 0; t < 2 && n_range == 0 && plan.columns; ++t) {
+        plan = rt3d::SweepPlan();
+        if (!build_plan(*g, A, 0, plan, msg, t == 0 ? 1e30 : 0.0, t == 0)) return noalloc_fail(RT3D_ERR_ARG, msg);
+        n_range = ranges();
+    }
     if (fixed >= kScratchBytes)
         return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution: its tables need " +
                                               std::to_string(fixed) + " of " + std::to_string(kScratchBytes) +
                                               " workspace bytes");
-    const size_t room = (kScratchBytes - fixed) / sizeof(double);
-    std::vector<int> q_begin;             // pair ranges [q_begin[r], q_begin[r + 1])
-    for (int q = 0; q < plan.n_pair;) {
-        const int64_t base = plan.pairs[q].p_off;
-        int q1 = q;
-        while (q1 < plan.n_pair) {
-            const int64_t end = q1 + 1 < plan.n_pair ? plan.pairs[q1 + 1].p_off : plan.p_elems;
-            if (size_t(end - base) > room) break;
-            ++q1;
-        }
-        if (q1 == q)
-            return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution: the partial "
-                                              "planes of one direction pair exceed its workspace");
-        q_begin.push_back(q);
-        q = q1;
-    }
-    q_begin.push_back(plan.n_pair);
-    const int n_range = int(q_begin.size()) - 1;
+    if (n_range == 0)
+        return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution: the partial "
+                                          "planes of one direction pair exceed its workspace");
     // the work items of each range, in the plan's dispatch order
     std::vector<rt3d::WorkItem> items;
     std::vector<int> item_begin;
@@ -148,14 +161,10 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
             if (it.pair >= q_begin[r] && it.pair < q_begin[r + 1]) items.push_back(it);
     }
     item_begin.push_back(int(items.size()));
-    // per range, the pair table with the offsets of its partial planes taken from the range's first pair
-    std::vector<rt3d::PairInfo> range_pairs;
+    // the offsets of a pair's partial planes, taken from its range's first pair
     for (int r = 0; r < n_range; ++r) {
         const int64_t shift = plan.pairs[q_begin[r]].p_off;
-        for (rt3d::PairInfo pi : plan.pairs) {
-            pi.p_off -= shift;          // negative for the pairs before the range, which it does not touch
-            range_pairs.push_back(pi);
-        }
+        for (int q = q_begin[r]; q < q_begin[r + 1]; ++q) plan.pairs[q].p_off -= shift;
     }
 
     void *base = nullptr;
@@ -164,10 +173,11 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     unsigned char *p = static_cast<unsigned char *>(base);
     unsigned char *d_tab = p;        p += align256(tab.size() * sizeof(double));
     unsigned char *d_cs = p;         p += align256(size_t(V) * sizeof(double2));
-    unsigned char *d_pairs = p;      p += align256(plan.pairs.size() * plan.pairs.size() * sizeof(rt3d::PairInfo));
+    unsigned char *d_pairs = p;      p += align256(plan.pairs.size() * sizeof(rt3d::PairInfo));
     unsigned char *d_player = p;     p += align256(plan.player.size() * sizeof(rt3d::PairLayer));
     unsigned char *d_pseg = p;       p += align256(plan.pseg.size() * sizeof(rt3d::PairSeg));
-    unsigned char *d_rowmin = p;     p += align256(plan.row_min.size() * sizeof(int));
+    unsigned char *d_cseg = p;       p += align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg));
+    unsigned char *d_blocks = p;     p += align256(plan.blocks.size() * sizeof(rt3d::LayerBlock));
     unsigned char *d_items = p;      p += align256(plan.items.size() * sizeof(rt3d::WorkItem));
     double *d_P = reinterpret_cast<double *>(p);
     // from here on an early return first drains the stream: the copies read this call's host tables
@@ -175,9 +185,9 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
         hipStreamSynchronize(st);
         return noalloc_fail(code, m);
     };
-    if ((rc = upload(d_tab, tab, st)) || (rc = upload(d_pairs, range_pairs, st)) ||
+    if ((rc = upload(d_tab, tab, st)) || (rc = upload(d_pairs, plan.pairs, st)) ||
         (rc = upload(d_player, plan.player, st)) || (rc = upload(d_pseg, plan.pseg, st)) ||
-        (rc = upload(d_rowmin, plan.row_min, st)) || (rc = upload(d_items, items, st)))
+        (rc = upload(d_cseg, plan.cseg, st)) || (rc = upload(d_blocks, plan.blocks, st)) || (rc = upload(d_items, items, st)))
         return drain_fail(rc, thread_error());
     hipLaunchKernelGGL(pack_kernel, dim3(unsigned((V + kPlaneThreads - 1) / kPlaneThreads)), dim3(kPlaneThreads), 0,
                        st, V, chi, S, reinterpret_cast<double2 *>(d_cs));
@@ -189,7 +199,8 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     sa.n_down = A.n_dir / 2;
     sa.pseg = reinterpret_cast<const rt3d::PairSeg *>(d_pseg);
     sa.player = reinterpret_cast<const rt3d::PairLayer *>(d_player);
-    const rt3d::PairInfo *d_range_pairs = reinterpret_cast<const rt3d::PairInfo *>(d_pairs);
+    sa.cseg = reinterpret_cast<const rt3d::ColumnSeg *>(d_cseg);
+    sa.pairs = reinterpret_cast<const rt3d::PairInfo *>(d_pairs);
     sa.cs = d_cs;
     sa.Ibot = g->bottom_bc == 1 ? nullptr : I_bot;
     sa.Islope = nullptr;
@@ -201,19 +212,17 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     ReduceArgs ra{};
     ra.nx = nx; ra.ny = ny; ra.nz = nz; ra.n_pair = plan.n_pair;
 
-    ra.row_min = reinterpret_cast<const int *>(d_rowmin);
+    ra.pairs = sa.pairs;
+    ra.blocks = reinterpret_cast<const rt3d::LayerBlock *>(d_blocks);
     ra.P = d_P;
     ra.chi = chi;
     ra.Jfs = J_fs;
-    const size_t smem = sweep_smem_bytes(plan, false);
     const dim3 red_grid(unsigned(((nx + 1) / 2 * ny + kPlaneThreads - 1) / kPlaneThreads), unsigned(nz));
     for (int r = 0; r < n_range; ++r) {
         const int n_items = item_begin[r + 1] - item_begin[r];
         sa.items = reinterpret_cast<const rt3d::WorkItem *>(d_items) + item_begin[r];
-        sa.pairs = d_range_pairs + size_t(r) * plan.pairs.size();
-        ra.pairs = sa.pairs;
         if (n_items > 0)
-            hipLaunchKernelGGL((sweep_kernel<double, 512, 2>), dim3(unsigned(n_items)), dim3(shape.threads), smem, st, sa);
+            launch_sweep_kernel(sa, plan, 0, n_items, false, st);
         e = hipGetLastError();
         if (e != hipSuccess) return drain_fail(RT3D_ERR_HIP, std::string("sweep_kernel: ") + hipGetErrorString(e));
         hipLaunchKernelGGL(reduce_kernel_pair_range<double>, red_grid, dim3(kPlaneThreads), 0, st, ra, q_begin[r],

@@ -7,14 +7,17 @@
 // Kernels
 //   source_kernel   S = eps B + (1-eps) J packed with chi as {chi, S} per voxel (one 16-byte gather
 //                   per segment in the sweep).
-//   sweep_kernel    one workgroup per (x-mirrored direction pair, band of line rows): every thread
+//   column_sweep_kernel  (sweep_columns.h) one workgroup per (x-mirrored direction pair, bands of 4 line rows):
+//                   a thread stays in a column and the lines come through it; each row of voxels that a
+//                   band has touched in a layer is written once to the pair's partial planes P.
+//   sweep_kernel    the same for rows of more than 512 columns: one workgroup per (x-mirrored direction pair, band of line rows): every thread
 //                   owns a few slots, each carrying a line of both directions through the same voxel
 //                   (the B lines move between slots at x-face crossings), down (or up) through all
 //                   layers; the two lines share the voxel's chi,S gather, exponential and deposit.
 //                   All lines of a direction share one segment table, so segment s of every slot in
 //                   a layer lands in a distinct voxel: the deposits D_s go into an LDS window without
 //                   atomics, one segment index at a time, and each layer's window is written once to
-//                   a per-band partial plane P.  Deterministic; no float atomics.  The float64
+//                   a per-band partial plane P.  Both: deterministic; no float atomics; the float64
 //                   exponential uses a 16-entry table of 2^(j/16) (per context, copied to LDS).
 //   reduce_kernel_pair  per voxel (two neighbours of a row per thread), sums the partial planes of
 //                   all directions in a fixed order: J_fs = (1/chi) sum_d W_d |mu_d| sum_bands P, and
@@ -216,7 +219,7 @@ int launch_sweep(rt3d_ctx *c, bool fp32, bool diff)
     SweepArgs a{};
     a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz;
     a.n_down = c->A.n_dir / 2;
-    a.pseg = c->pseg; a.player = c->player;
+    a.pseg = c->pseg; a.player = c->player; a.cseg = c->cseg;
     a.pairs = c->pairs; a.items = c->items;
     a.cs = c->cs;
     a.Ibot = (c->g.bottom_bc != 1 && !diff) ? c->B : nullptr;
@@ -226,26 +229,9 @@ int launch_sweep(rt3d_ctx *c, bool fp32, bool diff)
     a.Iem = c->Iem;
     a.Iem_base = diff ? c->Iem_a : nullptr;
     a.xtab = c->xtab;
-    const size_t smem = sweep_smem_bytes(c->plan, fp32);
-    const dim3 grid(c->plan.items.size());
     TimedLaunch t(c, K_SWEEP);
     if (fp32) c->fp32_sweeps += 1; else c->fp64_sweeps += 1;
-#define RT3D_LAUNCH_SWEEP(NT_, LPT_)                                                           \
-    do {                                                                                          \
-        if (!fp32)                                                                                \
-            hipLaunchKernelGGL((sweep_kernel<double, NT_, LPT_>), grid, dim3(NT_), smem, c->stream, a); \
-        else                                                                                      \
-            hipLaunchKernelGGL((sweep_kernel<float, NT_, LPT_>), grid, dim3(NT_), smem, c->stream, a);  \
-    } while (0)
-    switch (c->sweep_shape) {
-    case 1: RT3D_LAUNCH_SWEEP(512, 4); break;
-    case 2: RT3D_LAUNCH_SWEEP(256, 8); break;
-    case 3: RT3D_LAUNCH_SWEEP(1024, 2); break;
-    case 4: RT3D_LAUNCH_SWEEP(256, 4); break;
-    case 5: RT3D_LAUNCH_SWEEP(256, 2); break;
-    default: RT3D_LAUNCH_SWEEP(512, 2); break;
-    }
-#undef RT3D_LAUNCH_SWEEP
+    launch_sweep_kernel(a, c->plan, c->sweep_shape, int(c->plan.items.size()), fp32, c->stream);
     return check_launch(c, "sweep_kernel");
 }
 
@@ -253,7 +239,7 @@ int launch_reduce(rt3d_ctx *c, bool with_residual, bool fp32, const double *base
 {
     ReduceArgs a{};
     a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
-    a.pairs = c->pairs; a.row_min = c->row_min; a.P = c->P; a.chi = c->chi;
+    a.pairs = c->pairs; a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
     a.J = c->J; a.base = base; a.Jfs = c->Jfs; a.rb = with_residual ? c->r : nullptr;
     TimedLaunch t(c, K_REDUCE);
     if (!fp32)
@@ -518,7 +504,7 @@ void free_plan(rt3d_ctx *c)
                      reinterpret_cast<void **>(&c->seg_n), reinterpret_cast<void **>(&c->seg_a),
                      reinterpret_cast<void **>(&c->seg_bb), reinterpret_cast<void **>(&c->seg_bm),
                      reinterpret_cast<void **>(&c->seg_ai), reinterpret_cast<void **>(&c->seg_bi),
-                     reinterpret_cast<void **>(&c->row_min), reinterpret_cast<void **>(&c->dirs),
+                     reinterpret_cast<void **>(&c->blocks), reinterpret_cast<void **>(&c->cseg), reinterpret_cast<void **>(&c->dirs),
                      reinterpret_cast<void **>(&c->items), reinterpret_cast<void **>(&c->pairs),
                      reinterpret_cast<void **>(&c->pseg), reinterpret_cast<void **>(&c->player)};
     for (void **p : ptrs) {
@@ -531,21 +517,24 @@ void free_plan(rt3d_ctx *c)
 }
 
 bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3d::SweepPlan &plan,
-                std::string &msg)
+                std::string &msg, double load, bool columns)
 {
     if (shape < 0 || shape >= n_sweep_shapes()) { msg = "sweep shape out of range"; return false; }
     const SweepShape sh = kSweepShapes[shape];
     // one plan for both precisions: a band's LDS is budgeted for the larger of the two; a grid whose
     // bands do not fit the usual budget (which keeps several workgroups per CU) takes the wide one
-    if (rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytes,
-                               plan, msg))
-        return true;
     std::string msg_wide;
-    if (rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytesWide,
-                               plan, msg_wide))
-        return true;
-    msg = msg_wide;
-    return false;
+    if (!rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytes,
+                                plan, msg) &&
+        !rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytesWide,
+                                plan, msg_wide)) {
+        msg = msg_wide;
+        return false;
+    }
+    // (the window plan decides above which grids are accepted, in either form)
+    if (columns)
+        rt3d::make_column_plan(A, sh.threads, sh.lines, load > 0.0 ? load : rt3d::column_load(g.nx, g.ny, g.nz, A), plan);
+    return true;
 }
 
 int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
@@ -556,7 +545,7 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
         plan = std::move(*built);
     } else {
         std::string msg;
-        if (!build_plan(c->g, c->A, shape, plan, msg)) return fail(c, RT3D_ERR_ARG, msg);
+        if (!build_plan(c->g, c->A, shape, plan, msg, c->sweep_load)) return fail(c, RT3D_ERR_ARG, msg);
     }
     int rc = sync(c);
     if (rc) return rc;
@@ -576,7 +565,7 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
     chk(upload(c, &c->seg_off, P.seg_off)); chk(upload(c, &c->seg_n, P.seg_n));
     chk(upload(c, &c->seg_a, P.seg_a)); chk(upload(c, &c->seg_bb, P.seg_bb)); chk(upload(c, &c->seg_bm, P.seg_bm));
     chk(upload(c, &c->seg_ai, P.seg_ai)); chk(upload(c, &c->seg_bi, P.seg_bi));
-    chk(upload(c, &c->row_min, P.row_min));
+    chk(upload(c, &c->blocks, P.blocks)); chk(upload(c, &c->cseg, P.cseg));
     chk(upload(c, &c->dirs, P.dirs)); chk(upload(c, &c->items, P.items)); chk(upload(c, &c->pairs, P.pairs));
     chk(upload(c, &c->pseg, P.pseg)); chk(upload(c, &c->player, P.player));
     c->plan_bytes = c->device_bytes - before;
@@ -589,7 +578,7 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
 }
 
 int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream_t stream, int shape,
-               std::string &msg)
+               std::string &msg, double load)
 {
     *out = nullptr;
     if (validate_desc(g, msg) != RT3D_OK) return RT3D_ERR_ARG;
@@ -600,12 +589,13 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
     c->g = *g;
     c->precision = precision;
     c->stream = stream;
+    c->sweep_load = load;
     c->real_size = (precision == RT3D_FP64) ? sizeof(double) : sizeof(float);
     c->V = long(g->nx) * g->ny * g->nz;
     if (!rt3d::make_angle_set(g->n_theta, g->n_phi, c->A)) { delete c; msg = "bad angle set"; return RT3D_ERR_ARG; }
     // the sweep plan first: a grid that does not fit the sweep kernel fails before any allocation
     rt3d::SweepPlan plan;
-    if (!build_plan(*g, c->A, shape, plan, msg)) { delete c; return RT3D_ERR_ARG; }
+    if (!build_plan(*g, c->A, shape, plan, msg, load)) { delete c; return RT3D_ERR_ARG; }
     if (const char *e = std::getenv("RT3D_JACOBI_XCD")) c->jacobi_xcd = std::max(0, std::min(4, std::atoi(e)));
     if (const char *e = std::getenv("RT3D_JACOBI_ALTERNATE")) c->jacobi_alternate = std::atoi(e) != 0;
     if (const char *e = std::getenv("RT3D_JACOBI_COLUMN")) {
@@ -654,9 +644,8 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
     if (g->bottom_bc == 2) chk(dev_alloc(c, &c->bot_slope, size_t(g->nx) * g->ny));
     chk(dev_alloc(c, &c->xtab, kExpTab));
     if (!rc) {
-        // 2^(j/kExpTab) rounded to float64 from the 64-bit-mantissa long double exp2
         double tab[kExpTab];
-        for (int j = 0; j < kExpTab; ++j) tab[j] = double(std::exp2(static_cast<long double>(j) / kExpTab));
+        exp_table(tab);
         if (hipMemcpy(c->xtab, tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess)
             rc = fail(c, RT3D_ERR_HIP, "upload of the exponential table");
     }
