@@ -146,14 +146,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     column_sweep_body<real>(a, bi.item, smem_raw);
 }
 
-template <typename real>
+template <typename real, bool COL>
 __global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_batch(const ReduceArgs *args, const PlaneBlock *blocks,
                                                                      const MemberState *st, int want)
 {
     const PlaneBlock b = blocks[blockIdx.x];
     if (st && st[b.member].mode != want) return;
     const ReduceArgs a = args[b.member];
-    reduce_body_pair<real>(a, b.chunk * kPlaneThreads + threadIdx.x, b.k);
+    extern __shared__ double2 reduce_part[];
+    reduce_body<real, COL>(a, b.chunk, b.k, reduce_part);
 }
 
 __global__ void anchor_copy_kernel(const CopyArgs *args, const MemberState *st)
@@ -378,11 +379,12 @@ struct rt3d_batch {
     int jac_M = 0;
     BatchItem *d_items = nullptr;      // bands of the members in the window form, then in the column form
     PlaneBlock *d_planes = nullptr, *d_columns = nullptr;
-    PlaneBlock *d_pplanes = nullptr;   // the reduction's blocks: chunks of voxel pairs of a row
-    int n_window = 0, n_column = 0, n_planes = 0, n_columns = 0, n_pplanes = 0;
+    PlaneBlock *d_pplanes = nullptr;   // the reduction's blocks of a plane: members in the window form first
+    int n_window = 0, n_column = 0, n_planes = 0, n_columns = 0, n_pplanes = 0, n_window_pplanes = 0;
     size_t smem64 = 0, smem32 = 0;     // LDS of the window form's workgroups
     int col_threads = 64, col_rows = 1;   // threads, rows per thread and LDS of the column form's
     size_t col_smem64 = 0, col_smem32 = 0;
+    size_t red_smem = 0;               // LDS of the reduction's
     long max_V = 0;
     bool tables_ok = false;            // argument arrays and block tables match the members
     bool plans_ok = true;              // false after a failed shape change
@@ -528,11 +530,12 @@ int build_tables(rt3d_batch *b)
     std::vector<AaArgs> aa(n);
     std::vector<MemberScalars> sc(n);
     std::vector<std::pair<double, BatchItem>> work, column_work;
-    std::vector<PlaneBlock> planes, columns, pplanes;
+    std::vector<PlaneBlock> planes, columns, pplanes, window_pplanes;
     const SweepShape sh = kSweepShapes[b->shape];
     b->smem64 = b->smem32 = b->col_smem64 = b->col_smem32 = 0;
     b->col_threads = 64;
     b->col_rows = 1;
+    b->red_smem = 0;
     b->max_V = 0;
     for (int i = 0; i < n; ++i) {
         rt3d_ctx *c = b->m[i];
@@ -562,10 +565,12 @@ int build_tables(rt3d_batch *b)
         for (int v = 0; v < 3; ++v) {
             ReduceArgs &a = red[v * n + i];
             a.nx = nx; a.ny = ny; a.nz = nz; a.n_pair = c->plan.n_pair;
-            a.pairs = c->pairs; a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
+            a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
             a.J = c->J; a.Jfs = c->Jfs;
             a.base = v == 1 ? c->Fa : nullptr;
             a.rb = v == 2 ? nullptr : c->r;
+            a.chunk = reduce_chunk_pairs(c->V, a.n_pair);
+            a.waves = reduce_waves(c->V, a.n_pair, a.chunk, kPlaneThreads / 64);
         }
         CopyArgs &k = cp[i];
         k.V = c->V;
@@ -600,10 +605,10 @@ int build_tables(rt3d_batch *b)
         const int chunks = (nx * ny + kPlaneThreads - 1) / kPlaneThreads;
         for (int z = 0; z < nz; ++z)
             for (int ch = 0; ch < chunks; ++ch) planes.push_back(PlaneBlock{i, ch, z, 0});
-        // the reduction takes two neighbouring voxels of a row per thread, as for a single problem
-        const int pchunks = ((nx + 1) / 2 * ny + kPlaneThreads - 1) / kPlaneThreads;
+        b->red_smem = std::max(b->red_smem, reduce_smem_bytes(red[i], kPlaneThreads));
+        const int pchunks = reduce_blocks(red[i], kPlaneThreads);
         for (int z = 0; z < nz; ++z)
-            for (int ch = 0; ch < pchunks; ++ch) pplanes.push_back(PlaneBlock{i, ch, z, 0});
+            for (int ch = 0; ch < pchunks; ++ch) (c->plan.columns ? pplanes : window_pplanes).push_back(PlaneBlock{i, ch, z, 0});
         // the Jacobi sweep's column layers, XCD-aware as in the single-problem grid: each member starts
         // on a multiple of 8 blocks; block b of the member runs on XCD b % 8, which takes the contiguous
         // chunk range [xcd * G, (xcd + 1) * G) of every column layer (G = chunks padded to 8, / 8);
@@ -629,6 +634,9 @@ int build_tables(rt3d_batch *b)
     }
     b->col_smem64 = size_t(b->col_threads) * column_edge<double>(b->col_rows) * sizeof(double);
     b->col_smem32 = size_t(b->col_threads) * column_edge<float>(b->col_rows) * sizeof(float);
+    b->n_window_pplanes = int(window_pplanes.size());
+    b->n_pplanes = int(pplanes.size());
+    pplanes.insert(pplanes.begin(), window_pplanes.begin(), window_pplanes.end());
     int rc = RT3D_OK;
     auto chk = [&](int r) { if (!rc) rc = r; };
     chk(bupload(b, b->d_src, src)); chk(bupload(b, b->d_sw, sw)); chk(bupload(b, b->d_red, red));
@@ -643,7 +651,6 @@ int build_tables(rt3d_batch *b)
     b->n_column = int(column_work.size());
     b->n_planes = int(planes.size());
     b->n_columns = int(columns.size());
-    b->n_pplanes = int(pplanes.size());
     bfree(b->d_jac);
     b->jac_M = 0;
     b->tables_ok = true;
@@ -702,6 +709,19 @@ int launch_check(rt3d_batch *b, const char *what)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return bfail(b, RT3D_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
     return RT3D_OK;
+}
+
+// reduction of one precision for the members in mode 'want' (st null: all members)
+template <typename real>
+void launch_reduce_batch(rt3d_batch *b, const ReduceArgs *args, const MemberState *st, int want)
+{
+    const dim3 blk(kPlaneThreads);
+    if (b->n_window_pplanes)
+        hipLaunchKernelGGL((reduce_kernel_batch<real, false>), dim3(b->n_window_pplanes), blk, b->red_smem, b->stream, args,
+                           b->d_pplanes, st, want);
+    if (b->n_pplanes)
+        hipLaunchKernelGGL((reduce_kernel_batch<real, true>), dim3(b->n_pplanes), blk, b->red_smem, b->stream, args,
+                           b->d_pplanes + b->n_window_pplanes, st, want);
 }
 
 // sweep launch of one precision for the members in mode 'want' (st null: all members)
@@ -763,11 +783,9 @@ int enqueue_iteration(rt3d_batch *b, int M)
     if ((rc = launch_check(b, "source_kernel_batch"))) return rc;
     if ((rc = launch_sweep_batch(b, false, b->d_sw, b->d_state, 1))) return rc;
     if (f32 && (rc = launch_sweep_batch(b, true, b->d_sw + n, b->d_state, 2))) return rc;
-    hipLaunchKernelGGL(reduce_kernel_batch<double>, dim3(b->n_pplanes), dim3(kPlaneThreads), 0, b->stream,
-                       b->d_red, b->d_pplanes, b->d_state, 1);
+    launch_reduce_batch<double>(b, b->d_red, b->d_state, 1);
     if (f32)
-        hipLaunchKernelGGL(reduce_kernel_batch<float>, dim3(b->n_pplanes), dim3(kPlaneThreads), 0, b->stream,
-                           b->d_red + n, b->d_pplanes, b->d_state, 2);
+        launch_reduce_batch<float>(b, b->d_red + n, b->d_state, 2);
     if ((rc = launch_check(b, "reduce_kernel_batch"))) return rc;
     if (f32) {
         hipLaunchKernelGGL(anchor_copy_kernel, aux, dim3(256), 0, b->stream, b->d_copy, b->d_state);
@@ -1036,11 +1054,9 @@ int rt3d_batch_formal_solution(rt3d_batch *b)
     if ((rc = launch_check(b, "source_kernel_batch"))) return rc;
     if ((rc = launch_sweep_batch(b, f32, b->d_sw, nullptr, 0))) return rc;
     if (f32)
-        hipLaunchKernelGGL(reduce_kernel_batch<float>, dim3(b->n_pplanes), dim3(kPlaneThreads), 0, b->stream,
-                           b->d_red + 2 * b->n, b->d_pplanes, nullptr, 0);
+        launch_reduce_batch<float>(b, b->d_red + 2 * b->n, nullptr, 0);
     else
-        hipLaunchKernelGGL(reduce_kernel_batch<double>, dim3(b->n_pplanes), dim3(kPlaneThreads), 0, b->stream,
-                           b->d_red + 2 * b->n, b->d_pplanes, nullptr, 0);
+        launch_reduce_batch<double>(b, b->d_red + 2 * b->n, nullptr, 0);
     if ((rc = launch_check(b, "reduce_kernel_batch"))) return rc;
     BHIP_TRY(b, hipStreamSynchronize(b->stream), "sync");
     for (rt3d_ctx *c : b->m) {

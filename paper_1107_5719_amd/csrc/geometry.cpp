@@ -347,13 +347,16 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
         }
     int64_t off = 0;
     std::vector<std::pair<double, WorkItem>> work;
+    P.blocks.resize(size_t(P.n_pair) * nz);
     for (int p = 0; p < P.n_pair; ++p) {
         PairInfo &pi = P.pairs[p];
         pi.p_off = off;
         pi.band_stride = int64_t(nz) * pi.win_rows * nx;
         off += pi.n_bands * pi.band_stride;
         for (int k = 0; k < nz; ++k)
-            P.blocks.push_back(LayerBlock{P.row_min[size_t(pi.dA) * nz + k], pi.win_rows, k * pi.win_rows * nx, 0});
+            P.blocks[size_t(k) * P.n_pair + p] =
+                LayerBlock{pi.p_off + int64_t(k) * pi.win_rows * nx, pi.wmu, P.row_min[size_t(pi.dA) * nz + k],
+                           pi.win_rows - pi.band_rows, nz * pi.win_rows, pi.band_rows << kBlockRows};
         for (int b = 0; b < pi.n_bands; ++b) {
             WorkItem it;
             it.pair = p;
@@ -482,10 +485,13 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
             else P.cseg[prev_end].cover = cover;
             prev_end = P.cseg.size() - 1;
             pi.win_rows = std::max(pi.win_rows, cover);
-            P.blocks[size_t(p) * nz + k] = LayerBlock{P.row_min[ka], cover, int(block), 0};
+            P.blocks[size_t(k) * P.n_pair + p] =
+                LayerBlock{off + block, pi.wmu, P.row_min[ka], jmax - jmin, 0,
+                           (kColumnRows << kBlockRows) | (pi.split ? kBlockSplit : 0) | (pi.ysgn < 0 ? kBlockDown : 0)};
             block += int64_t(cover) * nx;
         }
         pi.band_stride = block;
+        for (int k = 0; k < nz; ++k) P.blocks[size_t(k) * P.n_pair + p].stride = int(block / nx);
         pi.p_off = off;
         off += n_parts * block;
         // the kernel addresses a workgroup's bands with 32-bit byte offsets

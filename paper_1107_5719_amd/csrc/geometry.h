@@ -77,11 +77,14 @@ struct ColumnSeg {
     int flags, cover;
 };
 
-// Where the reduction finds a pair's partial planes of one layer: the layer's first row offset (modulo
-// ny), the rows that a band (split: a line row) touches in it, and its block's offset in that band's part
-// of P.
-struct LayerBlock {
-    int rmin, cover, off, pad;
+// Where the reduction finds a pair's partial planes of one layer, as one 32-byte scalar load: the block of band
+// (split: line row) n starts n * stride rows of nx elements after element off of P, and holds the rows from
+// the band's first plus rmin (modulo ny) on, span more than the band has.
+enum { kBlockSplit = 1, kBlockDown = 2, kBlockRows = 2 };     // flags; the rows of a full band << kBlockRows
+struct alignas(32) LayerBlock {
+    int64_t off;
+    double wmu;
+    int rmin, span, stride, flags;
 };
 
 // Segment s of a pair in one layer, packed for one scalar load: the column offset of direction A
@@ -122,7 +125,7 @@ struct SweepPlan {
     std::vector<PairInfo> pairs;
     std::vector<PairSeg> pseg;            // packed per-pair segments
     std::vector<PairLayer> player;        // per (pair, layer): index pair * nz + k
-    std::vector<LayerBlock> blocks;       // per (pair, layer): index pair * nz + k
+    std::vector<LayerBlock> blocks;       // per (layer, pair): index k * n_pair + pair
     // column form (the window form's pseg and player are empty then)
     bool columns = false;
     int col_rows = 0;                     // most rows per thread of any pair

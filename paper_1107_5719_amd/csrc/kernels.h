@@ -443,7 +443,6 @@ inline void launch_sweep_kernel(const SweepArgs &a, const rt3d::SweepPlan &plan,
 
 struct ReduceArgs {
     int nx, ny, nz, n_pair;
-    const rt3d::PairInfo *pairs;
     const rt3d::LayerBlock *blocks;
     const void *P;            // real
     const double *chi;
@@ -451,207 +450,348 @@ struct ReduceArgs {
     const double *base;       // difference mode: J_fs of the anchor, added (may be null)
     double *Jfs;
     double *rb;               // chi (J_fs - J), the right-hand side of the OS step (may be null)
+    int chunk;                // direction pairs that are summed by themselves (reduce_chunk_pairs)
+    int waves;                // wavefronts that share the chunks of a voxel (reduce_waves)
 };
+
+// The pairs of a voxel are summed in chunks of this many, and the chunks' sums added in order, so that
+// wavefronts can share them.  Only a function of the problem: a batch's members and ranges of pairs
+// sum as a single context does.  Grids beyond 2^19 voxels have wavefronts enough and take one chunk.
+inline int reduce_chunk_pairs(long V, int n_pair)
+{
+    return V > (1L << 19) ? n_pair : std::max(4, (n_pair + 63) / 64 * 4);
+}
+
+// Wavefronts that share the chunks of the same voxels, a power of 2 of at most one per chunk and max_waves:
+// as many as bring the launch (a wavefront takes 128 voxels) up to about 8 wavefronts per SIMD; a
+// chain of pairs that each wait for memory is all that a small grid's reduction spends its time on (65^3 x 64 with
+// limits of 2, 4, 8 and 16: 56, 52, 46 and 50 us).
+inline int reduce_waves(long V, int n_pair, int chunk, int max_waves)
+{
+    int w = 1;
+    while (2 * w <= std::min(max_waves, (n_pair + chunk - 1) / chunk) && V / 128 * w < 8192) w *= 2;
+    return w;
+}
 
 // J_fs(v) = (1/chi_v) sum_pairs W|mu| sum over the bands whose deposit windows cover v.  The band of
 // voxel row j at layer k is found from the row's offset to the layer's window origin; the previous
 // bands (cyclically) still cover the row while the offset stays inside their windows.
-template <typename real>
-struct PairBands {
-    const real *Pq;   // the pair's partial plane of layer k, at the voxel's column
-    long o0, o1;      // elements of the band that starts the row's window offset and of the band before it
-    int b1, off1;     // that earlier band (cyclically) and the row's offset in its window
-    int cover;        // rows of a full band's window in this layer (a shorter last band's has as many fewer)
-    int line_cover;   // rows of one line row's (split pairs)
+__device__ inline rt3d::LayerBlock layer_block(const ReduceArgs &a, int q, int k)
+{
+    // q and k are the same in all lanes and the table is constant while kernels run: a scalar load
+    typedef int v8i __attribute__((ext_vector_type(8)));
+    const v8i w = *(const __attribute__((address_space(4))) v8i *)(uintptr_t)(a.blocks + (long(k) * a.n_pair + q));
+    rt3d::LayerBlock lb;
+    __builtin_memcpy(&lb, &w, sizeof(lb));
+    return lb;
+}
+
+// Bands of rows[0] rows each (COL: kColumnRows), the last one of fewer
+template <bool COL>
+struct BandRow {
+    int rows, nb, last;
+    int b, off;                  // a band, and the row's offset to its first
+    __device__ BandRow(const rt3d::LayerBlock &lb, int ny, int j)
+    {
+        rows = COL ? rt3d::kColumnRows : lb.flags >> rt3d::kBlockRows;
+        nb = (ny + rows - 1) / rows;
+        last = ny - (nb - 1) * rows;
+        int jj = j - lb.rmin;
+        jj += (jj < 0) ? ny : 0;
+        b = jj / rows;
+        off = jj - b * rows;
+    }
+    __device__ int rows_before() const { return b == 0 ? last : rows; }      // of the band before (cyclically)
+    __device__ void back()
+    {
+        off += rows_before();
+        b = (b == 0) ? nb - 1 : b - 1;
+    }
+    // a band of n rows has n + span: a band that one has stepped back to covers the row where this held before
+    __device__ bool before(int span) const { return off < span; }
+    __device__ long at(const rt3d::LayerBlock &lb, int nx) const { return long(unsigned(b * lb.stride + off)) * unsigned(nx); }
 };
 
-template <typename real>
-__device__ inline PairBands<real> pair_bands(const ReduceArgs &a, const rt3d::PairInfo &pi, int q, int i, int j, int k)
-{
-    const int nx = a.nx, ny = a.ny;
-    const int rows = pi.band_rows, nb = pi.n_bands;
-    const rt3d::LayerBlock lb = a.blocks[q * a.nz + k];
-    int jj = j - lb.rmin;
-    jj += (jj < 0) ? ny : 0;
-    int b = min(int((float(jj) + 0.5f) * pi.inv_rows), nb - 1);
-    b -= (b * rows > jj) ? 1 : 0;
-    b += (b < nb - 1 && (b + 1) * rows <= jj) ? 1 : 0;
-    const int off0 = jj - b * rows;
-    PairBands<real> r;
-    r.Pq = static_cast<const real *>(a.P) + pi.p_off + lb.off + i;
-    r.b1 = (b == 0) ? nb - 1 : b - 1;
-    r.off1 = off0 + ((r.b1 == nb - 1) ? pi.last_rows : rows);
-    r.o0 = long(b) * pi.band_stride + long(off0) * nx;
-    r.o1 = long(r.b1) * pi.band_stride + long(r.off1) * nx;
-    r.cover = lb.cover + (pi.split ? rows - 1 : 0);
-    r.line_cover = lb.cover;
-    return r;
-}
+template <typename real> struct ReducePair;      // two neighbours of a row, at any element
+template <> struct ReducePair<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct ReducePair<float> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
 
-// Row offset of the band before b1 (cyclically): it covers the row too when below the window height.
-__device__ inline int pair_bands_next_off(const rt3d::PairInfo &pi, int bb, int off)
+// Adds the sums of the U unsplit pairs from q on, less those that repeat q1 - 1, for the voxels (i, j, k) and
+// (i + 1, j, k) to acc0 and acc1, pair by pair in order.  A pair's bands are added in the order b, the one
+// before, then earlier ones, for lines that drift down from the earliest on (as reduce_split).  The
+// partials of the first two bands of all U pairs are loaded before any is summed (a pair whose row only
+// one band covers loads the first band's again and does not add it), so a wave keeps that many loads in
+// flight instead of waiting on each pair; the rare third and later bands are read where they are added.
+template <typename real, bool COL, int U>
+__device__ inline void reduce_group(const ReduceArgs &a, const rt3d::LayerBlock (&lb)[U], int n, int i, int j,
+                                    double &acc0, double &acc1)
 {
-    bb = (bb == 0) ? pi.n_bands - 1 : bb - 1;
-    return off + ((bb == pi.n_bands - 1) ? pi.last_rows : pi.band_rows);
-}
-
-// Deposits of a split pair's band bb in the row at offset off of its window, for voxels (i, j, k) and the next
-// (d1 apart): its line rows' partials are added in the order that the lines come through the row and in the
-// precision of the sweep, which are the sums that a thread of an unsplit band makes.
-template <typename real>
-__device__ inline void split_band_sum(const PairBands<real> &pb, const rt3d::PairInfo &pi, int nx, int bb, int off,
-                                      int d1, double &s0, double &s1)
-{
-    constexpr int R = rt3d::kColumnRows;
-    const int n = bb == pi.n_bands - 1 ? pi.last_rows : R;
-    const int lo = max(0, off - pb.line_cover + 1), hi = min(n - 1, off);
-    real x[R], y[R];
+    using real2 = typename ReducePair<real>::type;
+    real2 x[U], y[U];
+    bool m1[U], more[U];
+    const real *Pi = static_cast<const real *>(a.P) + i;
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const int l = pi.ysgn > 0 ? max(hi - t, lo) : min(lo + t, hi);
-        const long o = long(bb * R + l) * pi.band_stride + long(off - l) * nx;
-        x[t] = pb.Pq[o];
-        y[t] = pb.Pq[o + d1];
+    for (int u = 0; u < U; ++u) {
+        BandRow<COL> r(lb[u], a.ny, j);
+        const real *Pq = Pi + lb[u].off;
+        const long o0 = r.at(lb[u], a.nx);
+        m1[u] = r.before(lb[u].span);
+        r.back();
+        more[u] = r.before(lb[u].span);
+        x[u] = *reinterpret_cast<const real2 *>(Pq + o0);
+        y[u] = *reinterpret_cast<const real2 *>(Pq + (m1[u] ? r.at(lb[u], a.nx) : o0));
     }
-    real a = x[0], b = y[0];
+    // keep the sums below the group's loads (the scheduler would otherwise interleave them and wait on each
+    // pair's loads before issuing the next pair's)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 1; t < R; ++t) {
-        a = t <= hi - lo ? a + x[t] : a;
-        b = t <= hi - lo ? b + y[t] : b;
+    for (int u = 0; u < U; ++u) {
+        if (u >= n) break;
+        double s0 = double(x[u].x), s1 = double(x[u].y);
+        if (m1[u]) {
+            s0 += double(y[u].x);
+            s1 += double(y[u].y);
+        }
+        if (more[u]) {
+            // bands thinner than the window halo: still earlier bands cover the row
+            const real *Pq = Pi + lb[u].off;
+            BandRow<COL> r(lb[u], a.ny, j);
+            r.back();
+            if (!(lb[u].flags & rt3d::kBlockDown)) {
+                while (r.before(lb[u].span)) {
+                    r.back();
+                    const real2 z = *reinterpret_cast<const real2 *>(Pq + r.at(lb[u], a.nx));
+                    s0 += double(z.x);
+                    s1 += double(z.y);
+                }
+            } else {
+                int m = 0;
+                for (; r.before(lb[u].span); ++m) r.back();
+                s0 = s1 = 0.0;
+                for (; m > 0; --m) {
+                    BandRow<COL> e(lb[u], a.ny, j);
+                    for (int t = 0; t <= m; ++t) e.back();
+                    const real2 z = *reinterpret_cast<const real2 *>(Pq + e.at(lb[u], a.nx));
+                    s0 += double(z.x);
+                    s1 += double(z.y);
+                }
+                s0 = (s0 + double(y[u].x)) + double(x[u].x);
+                s1 = (s1 + double(y[u].y)) + double(x[u].y);
+            }
+        }
+        acc0 = fma(lb[u].wmu, s0, acc0);
+        acc1 = fma(lb[u].wmu, s1, acc1);
     }
-    s0 = double(a);
-    s1 = double(b);
 }
 
-// The angle sum of the direction pairs [q0, q1) for voxels (i, j, k) and (i + d1, j, k) (d1 = 0: one
-// voxel, read twice), added to acc0 / acc1 pair by pair in order, each pair's bands summed in the
-// order band b, b1, then earlier bands.  The partials of the first two bands of kPairGroup pairs are
-// loaded before any is summed (a pair whose row only one band covers loads the first band's element
-// again and does not add it), so a wave keeps that many loads in flight instead of waiting on each
-// pair; the rare third and later bands are read where they are added.  Measured per launch at
-// 129^3 x 256 (bitwise the same sums): 0.665 against 0.682 ms in float64, 0.475 against 0.516 ms in
-// float32; at 65^3 x 256 0.109 against 0.127 and 0.082 against 0.117 ms; groups of 8 pairs 0.657 /
-// 0.493 ms at 129^3.
-constexpr int kPairGroup = 4;
+// The same for a split pair: line row l of the grid has left its deposits for the row t above the layer's
+// first in row t of its own block.  The line rows come through a row in the order of t, from 0 for lines that
+// drift up and towards 0 for lines that drift down; those of one band are added to each other first, in the
+// sweep's precision, which are the sums that a thread of an unsplit band makes.
 template <typename real>
-__device__ inline void reduce_pairs(const ReduceArgs &a, int i, int d1, int j, int k, int q0, int q1, double &acc0,
+__device__ inline void reduce_split(const ReduceArgs &a, const rt3d::LayerBlock &lb, int i, int j, double &acc0,
                                     double &acc1)
 {
-    constexpr int U = kPairGroup;
-    for (int qb = q0; qb < q1; qb += U) {
-        double x0[U], x1[U], y0[U], y1[U];
-        bool m1[U], more[U];
+    using real2 = typename ReducePair<real>::type;
+    constexpr int U = 4;
+    const real *Pq = static_cast<const real *>(a.P) + lb.off + i;
+    const bool up = !(lb.flags & rt3d::kBlockDown);
+    const int ny = a.ny, span = lb.span;
+    // line row l of the step t, its row in its block, and where a line row is the first of its band
+    const int l_step = up ? -1 : 1, t_step = up ? 1 : -1, first = up ? rt3d::kColumnRows - 1 : 0, last = up ? ny - 1 : 0;
+    int t0 = up ? 0 : span, l = j - lb.rmin;
+    l += (l < 0) ? ny : 0;
+    l -= up ? 0 : span % ny;
+    l += (l < 0) ? ny : 0;
+    double s0 = 0.0, s1 = 0.0;
+    real b0 = real(0), b1 = real(0);
+    for (int tb = 0; tb <= span; tb += U, t0 += U * t_step) {
+        real2 x[U];
+        bool fresh[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int q = min(qb + u, q1 - 1);
-            const rt3d::PairInfo pi = a.pairs[q];
-            const PairBands<real> pb = pair_bands<real>(a, pi, q, i, j, k);
-            m1[u] = pb.off1 < pb.cover - (pb.b1 == pi.n_bands - 1 ? pi.band_rows - pi.last_rows : 0);
-            more[u] = m1[u] && pair_bands_next_off(pi, pb.b1, pb.off1) < pb.cover;
-            if (pi.split) {
-                const int b0 = pb.b1 + 1 == pi.n_bands ? 0 : pb.b1 + 1;
-                const int off0 = pb.off1 - (pb.b1 == pi.n_bands - 1 ? pi.last_rows : pi.band_rows);
-                split_band_sum<real>(pb, pi, a.nx, b0, off0, d1, x0[u], x1[u]);
-                y0[u] = y1[u] = 0.0;
-                if (m1[u]) split_band_sum<real>(pb, pi, a.nx, pb.b1, pb.off1, d1, y0[u], y1[u]);
-                continue;
-            }
-            const long o1 = m1[u] ? pb.o1 : pb.o0;
-            x0[u] = double(pb.Pq[pb.o0]);
-            x1[u] = double(pb.Pq[pb.o0 + d1]);
-            y0[u] = double(pb.Pq[o1]);
-            y1[u] = double(pb.Pq[o1 + d1]);
+            // (beyond the last step: the last one again)
+            const int t = t0 + t_step * min(u, span - tb);
+            x[u] = *reinterpret_cast<const real2 *>(Pq + long(unsigned(l * lb.stride + t)) * unsigned(a.nx));
+            fresh[u] = l % rt3d::kColumnRows == first || l == last;
+            const int next = l + (tb + u < span ? l_step : 0);
+            l = next < 0 ? ny - 1 : next >= ny ? 0 : next;
         }
-        // keep the sums below the group's loads (the scheduler would otherwise interleave them and
-        // wait on each pair's loads before issuing the next pair's)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (qb + u >= q1) break;
-            const rt3d::PairInfo pi = a.pairs[qb + u];
-            double s0 = x0[u], s1 = x1[u];
-            if (m1[u]) {
-                s0 += y0[u];
-                s1 += y1[u];
-            }
-            if (more[u]) {
-                // bands thinner than the window halo: still earlier bands cover the row
-                const PairBands<real> pb = pair_bands<real>(a, pi, qb + u, i, j, k);
-                int bb = pb.b1, off = pb.off1;
-                while (true) {
-                    off = pair_bands_next_off(pi, bb, off);
-                    bb = (bb == 0) ? pi.n_bands - 1 : bb - 1;
-                    if (off >= pb.cover - (bb == pi.n_bands - 1 ? pi.band_rows - pi.last_rows : 0)) break;
-                    if (pi.split) {
-                        double z0, z1;
-                        split_band_sum<real>(pb, pi, a.nx, bb, off, d1, z0, z1);
-                        s0 += z0;
-                        s1 += z1;
-                        continue;
-                    }
-                    const long o = long(bb) * pi.band_stride + long(off) * a.nx;
-                    s0 += double(pb.Pq[o]);
-                    s1 += double(pb.Pq[o + d1]);
-                }
-            }
-            acc0 += pi.wmu * s0;
-            acc1 += pi.wmu * s1;
+            if (tb + u > span) break;
+            s0 += fresh[u] ? double(b0) : 0.0;
+            s1 += fresh[u] ? double(b1) : 0.0;
+            b0 = (fresh[u] ? real(0) : b0) + x[u].x;
+            b1 = (fresh[u] ? real(0) : b1) + x[u].y;
         }
     }
+    acc0 = fma(lb.wmu, s0 + double(b0), acc0);
+    acc1 = fma(lb.wmu, s1 + double(b1), acc1);
+}
+
+// The angle sum of the direction pairs [q0, q1) for voxels (i, j, k) and (i + 1, j, k), added to acc0 / acc1.
+template <typename real, bool COL>
+__device__ inline void reduce_pairs(const ReduceArgs &a, int i, int j, int k, int q0, int q1, double &acc0, double &acc1)
+{
+    constexpr int U = 4;
+    for (int q = q0; q < q1; q += U) {
+        rt3d::LayerBlock lb[U];
+        int split = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lb[u] = layer_block(a, min(q + u, q1 - 1), k);
+            split |= lb[u].flags & rt3d::kBlockSplit;
+        }
+        if (!COL || !split) {
+            reduce_group<real, COL, U>(a, lb, q1 - q, i, j, acc0, acc1);
+            continue;
+        }
+        for (int u = 0; u < min(U, q1 - q); ++u) {
+            const rt3d::LayerBlock one[1] = {layer_block(a, q + u, k)};
+            if (one[0].flags & rt3d::kBlockSplit) reduce_split<real>(a, one[0], i, j, acc0, acc1);
+            else reduce_group<real, COL, 1>(a, one, 1, i, j, acc0, acc1);
+        }
+    }
+}
+
+__device__ inline void reduce_finish(const ReduceArgs &a, long v, double acc)
+{
+    const double Jfs = a.base ? a.base[v] + acc / a.chi[v] : acc / a.chi[v];
+    a.Jfs[v] = Jfs;
+    if (a.rb) a.rb[v] = a.chi[v] * (Jfs - a.J[v]);
 }
 
 // Two neighbouring voxels of one row per thread (p2 indexes the (ny, (nx + 1) / 2) voxel pairs of
-// plane k; the batched form takes the same blocks per member): the band lookup is shared and the
-// partials of both are read together.  Measured at 129^3 x 256 against one voxel per thread (before
-// the loads were grouped): 0.69 against 0.74 ms (float64), 0.51 against 0.59 ms (float32).
-// Direction pairs [q0, q1) only: the running sum starts from 0 (first) or from the raw sum a range
-// before left in Jfs, and is finished (divided by chi, the residual formed) only when last, so ranges
-// taken in order give bitwise the sum of one pass over all pairs.
-template <typename real>
-__device__ inline void reduce_body_pair_range(const ReduceArgs &a, int p2, int k, int q0, int q1, bool first,
-                                              bool last)
+// plane k; the last pair of an odd row starts one voxel earlier): the band lookup is shared and the
+// partials of both are read together.
+struct ReduceVoxels {
+    bool in;
+    int i, j, t0;      // first voxel, and the first of the two that is this thread's to write
+    long v;
+};
+__device__ inline ReduceVoxels reduce_voxels(const ReduceArgs &a, int p2, int k)
 {
-    const int nx = a.nx, ny = a.ny;
-    const int hx = (nx + 1) / 2;
-    if (p2 >= hx * ny) return;
-    const int j = p2 / hx, i0 = 2 * (p2 - j * hx);
-    const bool two = i0 + 1 < nx;
-    const int d1 = two ? 1 : 0;          // the second voxel's offset (0: none, reads the first again)
-    const long v0 = long(k) * nx * ny + long(j) * nx + i0;
-    double acc0 = first ? 0.0 : a.Jfs[v0], acc1 = (first || !two) ? 0.0 : a.Jfs[v0 + 1];
-    reduce_pairs<real>(a, i0, d1, j, k, q0, q1, acc0, acc1);
-    for (int t = 0; t < (two ? 2 : 1); ++t) {
-        const long v = v0 + t;
-        const double acc = t ? acc1 : acc0;
-        if (!last) {
-            a.Jfs[v] = acc;
-            continue;
+    const int hx = (a.nx + 1) / 2;
+    ReduceVoxels r;
+    r.in = p2 < hx * a.ny;
+    p2 = min(p2, hx * a.ny - 1);
+    r.j = p2 / hx;
+    const int h = p2 - r.j * hx;
+    r.i = min(2 * h, a.nx - 2);
+    r.t0 = 2 * h - r.i;
+    r.v = long(k) * a.nx * a.ny + long(r.j) * a.nx + r.i;
+    return r;
+}
+
+// Block b of plane k: blockDim.x / a.waves voxel pairs, whose chunks the block's thread groups share
+// (LDS: reduce_smem_bytes).  What bounds it: the partial planes' bytes on large grids (3.1 GB at 129^3 x 256, read at
+// 4.8 TB/s; 4 pairs' loads in flight per wave, a row's address by one scalar load and a few integer operations per
+// pair), the chain of pairs on small ones.  us per launch with one chain of pairs per voxel and the tables read
+// by vector loads, and now: 17^3 x 64 45 and 7, 65^3 x 64 55 and 33, 65^3 x 256 193 and 159, 129^3 x 256 654 and 642,
+// 129 x 129 x 193 x 256 in float32 746 and 645, the benchmark batch of 12 grids up to 97^3 417 and 290.
+template <typename real, bool COL>
+__device__ inline void reduce_body(const ReduceArgs &a, int b, int k, double2 *part)
+{
+    const int W = a.waves, n = int(blockDim.x) / W;          // voxel pairs of this block
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / n), p = int(threadIdx.x) - w * n;
+    const ReduceVoxels r = reduce_voxels(a, b * n + p, k);
+    const int n_chunk = (a.n_pair + a.chunk - 1) / a.chunk, per = (n_chunk + W - 1) / W;
+    double acc0 = 0.0, acc1 = 0.0;
+    for (int c = w * per; c < min(n_chunk, (w + 1) * per); ++c) {
+        double s0 = 0.0, s1 = 0.0;
+        reduce_pairs<real, COL>(a, r.i, r.j, k, c * a.chunk, min(a.n_pair, (c + 1) * a.chunk), s0, s1);
+        if (W > 1) part[c * n + p] = make_double2(s0, s1);
+        acc0 += s0;
+        acc1 += s1;
+    }
+    if (W > 1) {
+        __syncthreads();
+        if (w > 0) return;
+        acc0 = acc1 = 0.0;
+        for (int c = 0; c < n_chunk; ++c) {
+            const double2 s = part[c * n + p];
+            acc0 += s.x;
+            acc1 += s.y;
         }
-        const double Jfs = a.base ? a.base[v] + acc / a.chi[v] : acc / a.chi[v];
-        a.Jfs[v] = Jfs;
-        if (a.rb) a.rb[v] = a.chi[v] * (Jfs - a.J[v]);
+    }
+    if (!r.in) return;
+    if (r.t0 == 0) reduce_finish(a, r.v, acc0);
+    reduce_finish(a, r.v + 1, acc1);
+}
+
+inline int reduce_threads(const ReduceArgs &a) { return std::max(kPlaneThreads, 64 * a.waves); }
+inline size_t reduce_smem_bytes(const ReduceArgs &a, int threads)
+{
+    return a.waves > 1 ? size_t((a.n_pair + a.chunk - 1) / a.chunk) * (threads / a.waves) * sizeof(double2) : 0;
+}
+inline int reduce_blocks(const ReduceArgs &a, int threads)      // per plane
+{
+    const int n = threads / a.waves;
+    return ((a.nx + 1) / 2 * a.ny + n - 1) / n;
+}
+
+template <typename real, bool COL>
+__global__ __launch_bounds__(1024) void reduce_kernel_pair(ReduceArgs a)
+{
+    extern __shared__ double2 reduce_part[];
+    reduce_body<real, COL>(a, blockIdx.x, blockIdx.y, reduce_part);
+}
+
+inline void launch_reduce_kernel(ReduceArgs &a, bool columns, bool f32, hipStream_t stream)
+{
+    const long V = long(a.nx) * a.ny * a.nz;
+    a.chunk = reduce_chunk_pairs(V, a.n_pair);
+    a.waves = reduce_waves(V, a.n_pair, a.chunk, 16);
+    const int threads = reduce_threads(a);
+    const dim3 grid(reduce_blocks(a, threads), a.nz);
+    const size_t smem = reduce_smem_bytes(a, threads);
+    if (columns) {
+        if (f32) hipLaunchKernelGGL((reduce_kernel_pair<float, true>), grid, dim3(threads), smem, stream, a);
+        else hipLaunchKernelGGL((reduce_kernel_pair<double, true>), grid, dim3(threads), smem, stream, a);
+    } else {
+        if (f32) hipLaunchKernelGGL((reduce_kernel_pair<float, false>), grid, dim3(threads), smem, stream, a);
+        else hipLaunchKernelGGL((reduce_kernel_pair<double, false>), grid, dim3(threads), smem, stream, a);
     }
 }
 
-template <typename real>
-__device__ inline void reduce_body_pair(const ReduceArgs &a, int p2, int k)
-{
-    reduce_body_pair_range<real>(a, p2, k, 0, a.n_pair, true, true);
-}
-
-template <typename real>
-__global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_pair(ReduceArgs a)
-{
-    reduce_body_pair<real>(a, blockIdx.x * kPlaneThreads + threadIdx.x, blockIdx.y);
-}
-
-// pairs [q0, q1) only (see reduce_body_pair_range)
-template <typename real>
+// Direction pairs [q0, q1) only: starts from 0 (first) or from what a range before left, the sum of the whole
+// chunks in Jfs and of the chunk begun in carry (may be null where there is one chunk: Jfs holds its sum
+// then), and finishes only when last, so ranges taken in order give bitwise the sum of one pass over all
+// pairs.
+template <bool COL>
 __global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_pair_range(ReduceArgs a, int q0, int q1, int first,
-                                                                          int last)
+                                                                          int last, double *carry)
 {
-    reduce_body_pair_range<real>(a, blockIdx.x * kPlaneThreads + threadIdx.x, blockIdx.y, q0, q1, first != 0,
-                                 last != 0);
+    const int k = blockIdx.y;
+    const ReduceVoxels r = reduce_voxels(a, int(blockIdx.x) * kPlaneThreads + int(threadIdx.x), k);
+    if (!r.in) return;
+    const bool one = a.chunk >= a.n_pair;
+    double *begun = one ? a.Jfs : carry;
+    double acc[2] = {0.0, 0.0}, part[2] = {0.0, 0.0};
+    for (int t = r.t0; t < 2 && !first; ++t) {
+        acc[t] = one ? 0.0 : a.Jfs[r.v + t];
+        part[t] = begun[r.v + t];
+    }
+    for (int q = q0; q < q1;) {
+        const int qe = min(q1, (q / a.chunk + 1) * a.chunk);
+        reduce_pairs<double, COL>(a, r.i, r.j, k, q, qe, part[0], part[1]);
+        if (qe % a.chunk == 0 || qe == a.n_pair)
+            for (int t = 0; t < 2; ++t) {
+                acc[t] += part[t];
+                part[t] = 0.0;
+            }
+        q = qe;
+    }
+    for (int t = r.t0; t < 2; ++t) {
+        if (last) {
+            reduce_finish(a, r.v + t, acc[t]);
+        } else {
+            if (!one) a.Jfs[r.v + t] = acc[t];
+            begun[r.v + t] = part[t];
+        }
+    }
 }
 
 

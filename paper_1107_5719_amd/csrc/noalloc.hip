@@ -107,6 +107,9 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     // every range, then the partial planes of one range of pairs
     std::vector<double> tab(kExpTab);
     exp_table(tab.data());
+    // the reduction's sum of a chunk of pairs that a range leaves unfinished
+    const int chunk = reduce_chunk_pairs(V, plan.n_pair);
+    const size_t carry_bytes = chunk < plan.n_pair ? align256(size_t(V) * sizeof(double)) : 0;
     size_t fixed = 0;
     std::vector<int> q_begin;             // pair ranges [q_begin[r], q_begin[r + 1])
     // ranges of pairs whose partial planes fit what the tables leave of the workspace; 0 where one pair's do
@@ -118,7 +121,7 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
                 align256(plan.pseg.size() * sizeof(rt3d::PairSeg)) +
                 align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg)) +
                 align256(plan.blocks.size() * sizeof(rt3d::LayerBlock)) +
-                align256(plan.items.size() * sizeof(rt3d::WorkItem));
+                align256(plan.items.size() * sizeof(rt3d::WorkItem)) + carry_bytes;
         q_begin.clear();
         if (fixed >= kScratchBytes) return 0;
         const size_t room = (kScratchBytes - fixed) / sizeof(double);
@@ -164,7 +167,10 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     // the offsets of a pair's partial planes, taken from its range's first pair
     for (int r = 0; r < n_range; ++r) {
         const int64_t shift = plan.pairs[q_begin[r]].p_off;
-        for (int q = q_begin[r]; q < q_begin[r + 1]; ++q) plan.pairs[q].p_off -= shift;
+        for (int q = q_begin[r]; q < q_begin[r + 1]; ++q) {
+            plan.pairs[q].p_off -= shift;
+            for (int k = 0; k < nz; ++k) plan.blocks[size_t(k) * plan.n_pair + q].off -= shift;
+        }
     }
 
     void *base = nullptr;
@@ -179,6 +185,7 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     unsigned char *d_cseg = p;       p += align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg));
     unsigned char *d_blocks = p;     p += align256(plan.blocks.size() * sizeof(rt3d::LayerBlock));
     unsigned char *d_items = p;      p += align256(plan.items.size() * sizeof(rt3d::WorkItem));
+    double *d_carry = reinterpret_cast<double *>(p);   p += carry_bytes;
     double *d_P = reinterpret_cast<double *>(p);
     // from here on an early return first drains the stream: the copies read this call's host tables
     auto drain_fail = [&](int code, const std::string &m) {
@@ -212,11 +219,12 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     ReduceArgs ra{};
     ra.nx = nx; ra.ny = ny; ra.nz = nz; ra.n_pair = plan.n_pair;
 
-    ra.pairs = sa.pairs;
     ra.blocks = reinterpret_cast<const rt3d::LayerBlock *>(d_blocks);
     ra.P = d_P;
     ra.chi = chi;
     ra.Jfs = J_fs;
+    ra.chunk = chunk;
+    ra.waves = 1;
     const dim3 red_grid(unsigned(((nx + 1) / 2 * ny + kPlaneThreads - 1) / kPlaneThreads), unsigned(nz));
     for (int r = 0; r < n_range; ++r) {
         const int n_items = item_begin[r + 1] - item_begin[r];
@@ -225,8 +233,8 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
             launch_sweep_kernel(sa, plan, 0, n_items, false, st);
         e = hipGetLastError();
         if (e != hipSuccess) return drain_fail(RT3D_ERR_HIP, std::string("sweep_kernel: ") + hipGetErrorString(e));
-        hipLaunchKernelGGL(reduce_kernel_pair_range<double>, red_grid, dim3(kPlaneThreads), 0, st, ra, q_begin[r],
-                           q_begin[r + 1], r == 0 ? 1 : 0, r == n_range - 1 ? 1 : 0);
+        hipLaunchKernelGGL(plan.columns ? reduce_kernel_pair_range<true> : reduce_kernel_pair_range<false>, red_grid, dim3(kPlaneThreads), 0, st, ra, q_begin[r],
+                           q_begin[r + 1], r == 0 ? 1 : 0, r == n_range - 1 ? 1 : 0, d_carry);
         e = hipGetLastError();
         if (e != hipSuccess) return drain_fail(RT3D_ERR_HIP, std::string("reduce_kernel: ") + hipGetErrorString(e));
     }

@@ -186,12 +186,6 @@ dim3 plane_grid(const rt3d_ctx *c)
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2) in linear order.
 // Padding the chunks of a plane to a multiple of 8 sends a chunk's blocks of every plane to the same
 // XCD, so the plane-below data a Jacobi sweep re-reads is in that XCD's L2.  Padding blocks exit.
-// the reduction's grid: one thread per pair of neighbouring voxels of a row
-dim3 pair_grid(const rt3d_ctx *c)
-{
-    return dim3(((c->g.nx + 1) / 2 * c->g.ny + kPlaneThreads - 1) / kPlaneThreads, c->g.nz);
-}
-
 dim3 plane_grid_xcd(const rt3d_ctx *c)
 {
     const unsigned chunks = (c->g.nx * c->g.ny + kPlaneThreads - 1) / kPlaneThreads;
@@ -239,13 +233,10 @@ int launch_reduce(rt3d_ctx *c, bool with_residual, bool fp32, const double *base
 {
     ReduceArgs a{};
     a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
-    a.pairs = c->pairs; a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
+    a.blocks = c->blocks; a.P = c->P; a.chi = c->chi;
     a.J = c->J; a.base = base; a.Jfs = c->Jfs; a.rb = with_residual ? c->r : nullptr;
     TimedLaunch t(c, K_REDUCE);
-    if (!fp32)
-        hipLaunchKernelGGL(reduce_kernel_pair<double>, pair_grid(c), dim3(kPlaneThreads), 0, c->stream, a);
-    else
-        hipLaunchKernelGGL(reduce_kernel_pair<float>, pair_grid(c), dim3(kPlaneThreads), 0, c->stream, a);
+    launch_reduce_kernel(a, c->plan.columns, fp32, c->stream);
     return check_launch(c, "reduce_kernel");
 }
 

@@ -1,4 +1,4 @@
-"""GPU tests of the column form of the sweep (rows of up to 512 columns) at the edges of its tiles.
+"""GPU tests of the column form of the sweep (rows of up to 512 columns) and its reduction at the edges of their tiles.
 
 Rows around one, two and eight wavefronts and the first row length that takes the other form; bands whose last
 one holds 1, 2, 3 or 4 line rows; pairs split into single line rows (the small grids; shape 1 splits none), whole,
@@ -27,6 +27,10 @@ CASES = [
     ((3, 10, 129), 8, 8, 0.0, 1),
     ((3, 5, 512), 8, 8, 0.2, 0),
     ((3, 5, 513), 8, 8, 0.2, 0),
+    # the reduction's chunks of pairs: 3 pairs, 18 in chunks of 4, 200 in chunks of 16; rows of even and odd length
+    ((4, 7, 10), 2, 12, 0.1, 0),
+    ((5, 12, 11), 6, 12, 0.2, 0),
+    ((3, 6, 8), 20, 20, 0.0, 1),
 ]
 
 
