@@ -189,6 +189,13 @@ __global__ __launch_bounds__(kLstarThreads) void lstar_kernel_batch(const LstarA
     lstar_body(args[b.member], b.chunk * kLstarThreads + threadIdx.x, b.k);
 }
 
+__global__ __launch_bounds__(kLstarTileThreads) __attribute__((amdgpu_waves_per_eu(6))) void lstar_tile_kernel_batch(const LstarArgs *args, const PlaneBlock *blocks)
+{
+    extern __shared__ double2 lstar_ring[];
+    const PlaneBlock b = blocks[blockIdx.x];
+    lstar_tile_body(args[b.member], b.chunk, b.k, lstar_ring);
+}
+
 // Jacobi sweep of the members, column form (b.k is the column layer of kJacCol planes)
 template <typename coef>
 __global__ __launch_bounds__(kPlaneThreads) void jacobi_kernel_batch_column(const JacobiArgs *args,
@@ -469,12 +476,8 @@ int build_lstar_batched(rt3d_batch *b)
         rt3d_ctx *c = b->m[i];
         if (c->have_lstar) continue;
         if (!c->plan_ok) return bfail(b, RT3D_ERR_STATE, "member " + std::to_string(i) + " has no sweep plan");
-        LstarArgs a{};
-        a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
-        a.early_exit = c->lstar_early_exit;
-        a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
-        a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.chi = c->chi; a.L = c->L;
-        a.xtab = c->xtab;
+        LstarArgs a;
+        lstar_args(c, a);
         args.push_back(a);
         who.push_back(i);
     }
@@ -485,7 +488,19 @@ int build_lstar_batched(rt3d_batch *b)
         return long(args[x].nx) * args[x].ny * args[x].nz * args[x].n_pair >
                long(args[y].nx) * args[y].ny * args[y].nz * args[y].n_pair;
     });
+    // members in the tiled form first
+    int n_tile = 0, threads = 64;
+    size_t lds = 0;
     for (int q : order) {
+        if (!args[q].T) continue;
+        for (int k = 0; k < args[q].nz; ++k)
+            for (int ch = 0; ch < lstar_tile_blocks(args[q]); ++ch) blocks.push_back(PlaneBlock{q, ch, k, 0});
+        threads = std::max(threads, lstar_tile_threads(args[q]));
+        lds = std::max(lds, lstar_tile_lds(args[q]));
+        n_tile = int(blocks.size());
+    }
+    for (int q : order) {
+        if (args[q].T) continue;
         const int chunks = (args[q].nx * args[q].ny + kLstarThreads - 1) / kLstarThreads;
         for (int k = 0; k < args[q].nz; ++k)
             for (int ch = 0; ch < chunks; ++ch) blocks.push_back(PlaneBlock{q, ch, k, 0});
@@ -501,8 +516,13 @@ int build_lstar_batched(rt3d_batch *b)
                    hipSuccess) {
         rc = bfail(b, RT3D_ERR_HIP, "upload (Lambda* tables)");
     } else {
-        hipLaunchKernelGGL(lstar_kernel_batch, dim3(unsigned(blocks.size())), dim3(kLstarThreads), 0, b->stream,
-                           d_args, d_blocks);
+        if (n_tile > 0)
+            hipLaunchKernelGGL(lstar_tile_kernel_batch, dim3(unsigned(n_tile)), dim3(threads), lds, b->stream, d_args, d_blocks);
+        for (const LstarArgs &a : args)
+            if (a.T) launch_lstar_fold(a, b->stream);
+        if (int(blocks.size()) > n_tile)
+            hipLaunchKernelGGL(lstar_kernel_batch, dim3(unsigned(blocks.size()) - n_tile), dim3(kLstarThreads), 0, b->stream,
+                               d_args, d_blocks + n_tile);
         rc = launch_check(b, "lstar_kernel_batch");
         if (!rc && hipStreamSynchronize(b->stream) != hipSuccess) rc = bfail(b, RT3D_ERR_HIP, "sync (Lambda*)");
     }

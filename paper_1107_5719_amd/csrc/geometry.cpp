@@ -281,6 +281,8 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
             pi.dB = dB;
             pi.down = P.dirs[dA].down;
             pi.mu = A.mu[dA];
+            pi.xsgn = A.ox[dA] > 0.0 ? 1 : -1;
+            pi.ysgn = A.oy[dA] > 0.0 ? 1 : -1;
             // Band height: about target_seg_per_wg line-segments per layer for the two directions,
             // never thinner than the window's halo, within the line and LDS budgets.
             int rows = int(std::lround(target_seg_per_wg / (2.0 * nx * seg_per_layer[dA])));
@@ -452,8 +454,6 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
         pi.n_bands = (ny + kColumnRows - 1) / kColumnRows;
         pi.last_rows = ny - (pi.n_bands - 1) * kColumnRows;
         pi.inv_rows = 1.0f / float(kColumnRows);
-        pi.xsgn = A.ox[pi.dA] > 0.0 ? 1 : -1;
-        pi.ysgn = A.oy[pi.dA] > 0.0 ? 1 : -1;
         pi.c_off = int(P.cseg.size());
         pi.n_seg = n_seg;
         pi.win_rows = 0;

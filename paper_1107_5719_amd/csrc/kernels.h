@@ -807,6 +807,8 @@ struct LstarArgs {
     const double *seg_len;
     const double *chi;
     double *L;                      // [27][V]
+    double *T;                      // [18][V] scratch of the tiled form (null: not taken)
+    int tx, ty;                     // its tile
     const double *xtab;             // [kExpTab] 2^(j/kExpTab), the float64 exponential's table
 };
 
@@ -940,6 +942,228 @@ __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
         for (int o = 0; o < 9; ++o) a.L[(18 + o) * V + v] = 0.0;
     if (valid)
         for (int o = 0; o < 9; ++o) a.L[(9 + o) * V + v] = acc[o][threadIdx.x];
+}
+
+// Tiled form, for grids whose lines cannot wrap back (early_exit) with at least 16 pairs.
+// K_vu = chi_v Lambda*_vu is symmetric, and the walk of an upward line from v to u is that of the reversed
+// downward line from u to v, so the downward pairs alone give all of it: with D the part that they add,
+// K_vu = D_vu + D_uv for voxels of one layer and K_vu = D_vu, K_uv = D_vu for u in the layer above.
+// A walk crosses at most one face of each axis, so it has at most three steps, and the exponential of a voxel
+// and segment is the same for every walk that comes through it.  So a workgroup takes tx x ty columns of a layer,
+// a thread for each and for one more to each side: for one segment index after another (the last three
+// of the layer above, then the layer's own) each thread computes its voxel's exponential once and leaves it
+// in LDS, where the neighbours' walks find it up to three segments later.  Pairs with the same sign of
+// the y drift follow each other, and of a pair P is the line that drifts to larger x, M the other, so
+// the neighbour that a step reaches is known but for which axes it has crossed: 12 sums in registers.
+// What bounds it: float64 arithmetic, one exponential (about 30 instructions) and one self term per voxel
+// and segment index.  us before (a walk per thread, each step with two exponentials and gathers of its own,
+// both vertical directions) and now, with the fold: 17^3 x 64 222 and 78, 65^3 x 256 1936 and 584, 129^3 x 256
+// 10950 and 3800, the benchmark batch of 12 grids up to 97^3 6845 and 2700.  Workgroups of up to 512, 768 or 1024
+// threads, with less halo, wait longer at their barriers (65^3 x 256: 790, 980 and 790 us against 561 for the sums
+// alone), smaller ones have more halo (192: 678, 128: 687); two segments per barrier 583.
+constexpr int kLstarTileThreads = 256;
+// acc += x y on a tied operand: in the cases of a switch the compiler would copy all sums to merge the paths
+__device__ __forceinline__ void fma_to(double &acc, double x, double y)
+{
+    asm volatile("v_fma_f64 %0, %1, %2, %0" : "+v"(acc) : "v"(x), "v"(y));
+}
+
+__device__ inline void lstar_tile_body(const LstarArgs &a, int tile, int k, double2 *ring)
+{
+    __shared__ double xtab[kExpTab];
+    if (threadIdx.x < kExpTab) xtab[threadIdx.x] = a.xtab[threadIdx.x];
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const long plane = long(nx) * ny, V = plane * nz;
+    const int ntx = (nx + a.tx - 1) / a.tx, by = tile / ntx, bx = tile - by * ntx;
+    const int ex = a.tx + 2, E = ex * (a.ty + 2);
+    const int q = min(int(threadIdx.x), E - 1);
+    const int ly = q / ex, lx = q - ly * ex;
+    const int x0 = bx * a.tx + lx - 1, y0 = by * a.ty + ly - 1;      // in [-1, 2 n)
+    auto wrap = [](int x, int n) {
+        x += x < 0 ? n : 0;
+        return x - (x >= n ? n : 0);
+    };
+    const bool inner = int(threadIdx.x) < E && unsigned(lx - 1) < unsigned(a.tx) && unsigned(ly - 1) < unsigned(a.ty) &&
+                       x0 < nx && y0 < ny;
+    const long p = long(wrap(y0, ny)) * nx + wrap(x0, nx);
+    const double chiv = a.chi[k * plane + p], chiu = a.chi[(k + 1 < nz ? k + 1 : k) * plane + p];
+    // (threads without an output read their neighbours' cells as an inner thread does)
+    const int c = min(max(ly, 1), a.ty) * ex + min(max(lx, 1), a.tx);
+    auto scalar_int = [](const int *x) { return *(const __attribute__((address_space(4))) int *)(uintptr_t)x; };
+    auto scalar_len = [](const double *x) { return *(const __attribute__((address_space(4))) double *)(uintptr_t)x; };
+    double mid[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};     // [layer above][upstream column -1, 0, 1], the voxel's own row
+#pragma unroll 1
+    for (int cls = 0; cls < 2; ++cls) {
+        // lines that drift to larger y (their upstream row is j - 1), then to smaller
+        const int dy = cls == 0 ? -ex : ex;
+        double s000 = 0.0, s010 = 0.0, s001 = 0.0, s011 = 0.0;                         // [x y z crossed]
+        double p100 = 0.0, p110 = 0.0, p101 = 0.0, p111 = 0.0, m100 = 0.0, m110 = 0.0, m101 = 0.0, m111 = 0.0;
+        auto add = [&](int bits, double gP, double cP, double gM, double cM) {
+            switch (bits) {
+            case 1: fma_to(p100, gP, cP); fma_to(m100, gM, cM); break;
+            case 2: fma_to(s010, gP, cP); fma_to(s010, gM, cM); break;
+            case 3: fma_to(p110, gP, cP); fma_to(m110, gM, cM); break;
+            case 4: fma_to(s001, gP, cP); fma_to(s001, gM, cM); break;
+            case 5: fma_to(p101, gP, cP); fma_to(m101, gM, cM); break;
+            case 6: fma_to(s011, gP, cP); fma_to(s011, gM, cM); break;
+            default: fma_to(p111, gP, cP); fma_to(m111, gM, cM); break;
+            }
+        };
+        for (int r = 0; r < a.n_pair; ++r) {
+            const rt3d::PairInfo *pi = a.pairs + r;
+            if (!scalar_int(&pi->down) || (scalar_int(&pi->ysgn) < 0) != (cls == 1)) continue;
+            const int dk = scalar_int(&pi->dA) * nz + k;
+            const double wmu = scalar_len(&pi->wmu);
+            const int off = scalar_int(a.seg_off + dk), n = scalar_int(a.seg_n + dk);
+            const int nu = k + 1 < nz ? scalar_int(a.seg_n + dk + 1) : 0, m = min(nu, 3);
+            const int offu = k + 1 < nz ? scalar_int(a.seg_off + dk + 1) + nu - m : 0;
+            // axes crossed on coming into each of the last three segments
+            int b1 = 0, b2 = 0, b3 = 0, ai = 0, bi = 0, an, bn;
+            auto crossed = [&]() {
+                b3 = b2;
+                b2 = b1;
+                b1 = (an != ai ? 1 : 0) | (bn != bi ? 2 : 0);
+                ai = an;
+                bi = bn;
+            };
+            __syncthreads();
+#pragma unroll 1
+            for (int t = 0; t < m; ++t) {
+                double e, em1;
+                exp_pair_tab(-chiu * scalar_len(a.seg_len + offu + t), xtab, e, em1);
+                an = scalar_int(a.seg_ai + offu + t);
+                bn = scalar_int(a.seg_bi + offu + t);
+                crossed();
+                ring[t * E + q] = make_double2(e, em1);
+            }
+            // the sums of segment t of the layer, whose optical depth and e^-x - 1 are x and em1
+            auto sums = [&](int t, double x, double em1) {
+                fma_to(s000, 2.0 * wmu, self_term(x, em1));
+                const double g = wmu * em1;
+                if (t < 1) return;
+                const int d1 = ((b1 & 2) ? dy : 0) + c, x1 = b1 & 1;
+                const double2 *row = ring + ((t - 1) & 3) * E;
+                const double2 P1 = row[d1 - x1], M1 = row[d1 + x1];
+                add(b1, g, P1.y, g, M1.y);
+                if (t < 2 || (b1 & b2)) return;
+                const int b12 = b1 | b2, d2 = ((b12 & 2) ? dy : 0) + c, x2 = b12 & 1;
+                const double2 *row2 = ring + ((t - 2) & 3) * E;
+                const double2 P2 = row2[d2 - x2], M2 = row2[d2 + x2];
+                const double gP = g * P1.x, gM = g * M1.x;
+                add(b12, gP, P2.y, gM, M2.y);
+                if (t < 3 || (b12 & b3)) return;
+                const int b123 = b12 | b3, d3 = ((b123 & 2) ? dy : 0) + c, x3 = b123 & 1;
+                const double2 *row3 = ring + ((t - 3) & 3) * E;
+                add(b123, gP * P2.x, row3[d3 - x3].y, gM * M2.x, row3[d3 + x3].y);
+            };
+#pragma unroll 1
+            for (int t = m; t < m + n; ++t) {
+                const int idx = off + t - m;
+                const double x = chiv * scalar_len(a.seg_len + idx);
+                double e, em1;
+                exp_pair_tab(-x, xtab, e, em1);
+                an = scalar_int(a.seg_ai + idx);
+                bn = scalar_int(a.seg_bi + idx);
+                crossed();
+                if (t == m) b1 |= 4;
+                // after the barrier no thread reads segment t - 4 any more, whose place this one takes
+                __syncthreads();
+                ring[(t & 3) * E + q] = make_double2(e, em1);
+                sums(t, x, em1);
+            }
+        }
+        if (inner) {
+            // rows j - 1 (lines to larger y) and j + 1 are complete; the voxel's own row has terms of both
+            double *T = a.T + k * plane + p;
+            const int row = cls == 0 ? 0 : 6;
+            T[(row + 0) * V] = p110;
+            T[(row + 1) * V] = s010;
+            T[(row + 2) * V] = m110;
+            T[(9 + row + 0) * V] = p111;
+            T[(9 + row + 1) * V] = s011;
+            T[(9 + row + 2) * V] = m111;
+        }
+        mid[0][0] += p100; mid[0][1] += s000; mid[0][2] += m100;
+        mid[1][0] += p101; mid[1][1] += s001; mid[1][2] += m101;
+    }
+    if (inner) {
+        double *T = a.T + k * plane + p;
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int x = 0; x < 3; ++x) T[(9 * z + 3 + x) * V] = mid[z][x];
+    }
+}
+
+__global__ __launch_bounds__(kLstarTileThreads) __attribute__((amdgpu_waves_per_eu(6))) void lstar_tile_kernel(LstarArgs a)
+{
+    extern __shared__ double2 lstar_ring[];
+    lstar_tile_body(a, blockIdx.x, blockIdx.y, lstar_ring);
+}
+
+// Lambda* from the tiled form's sums: T[0, 9) of the voxel's layer, T[9, 18) of the layer above
+__global__ __launch_bounds__(kPlaneThreads) void lstar_fold_kernel(LstarArgs a)
+{
+    const int nx = a.nx, ny = a.ny, k = blockIdx.y, p = int(blockIdx.x) * kPlaneThreads + int(threadIdx.x);
+    if (p >= nx * ny) return;
+    const int j = p / nx, i = p - j * nx;
+    const long plane = long(nx) * ny, V = plane * a.nz, v = k * plane + p;
+    const int cols[3] = {i == 0 ? nx - 1 : i - 1, i, i == nx - 1 ? 0 : i + 1};
+    const int rows[3] = {j == 0 ? ny - 1 : j - 1, j, j == ny - 1 ? 0 : j + 1};
+    const double inv = 1.0 / a.chi[v];
+#pragma unroll
+    for (int o = 0; o < 9; ++o) {
+        const long u = long(rows[o / 3]) * nx + cols[o % 3];
+        // the voxel's own entry: upward lines add what the downward ones do
+        a.L[(9 + o) * V + v] = inv * (a.T[o * V + v] + a.T[(8 - o) * V + k * plane + u]);
+        a.L[(18 + o) * V + v] = inv * a.T[(9 + o) * V + v];
+        a.L[o * V + v] = k > 0 ? inv * a.T[(17 - o) * V + (k - 1) * plane + u] : 0.0;
+    }
+}
+
+// The tile of the tiled form: the fewest wavefronts that cover a layer with workgroups of at most
+// kLstarTileThreads threads.
+inline void lstar_tile(int nx, int ny, int &tx, int &ty)
+{
+    long best = 0;
+    for (int cx = 1; cx <= nx; ++cx) {
+        const int w = (nx + cx - 1) / cx;
+        if (w + 2 > kLstarTileThreads / 3) continue;
+        for (int h = 1; h <= ny && (w + 2) * (h + 2) <= kLstarTileThreads; ++h) {
+            const long waves = long((nx + w - 1) / w) * ((ny + h - 1) / h) * (((w + 2) * (h + 2) + 63) / 64);
+            if (best == 0 || waves < best) {
+                best = waves;
+                tx = w;
+                ty = h;
+            }
+        }
+    }
+}
+inline int lstar_tile_threads(const LstarArgs &a) { return ((a.tx + 2) * (a.ty + 2) + 63) / 64 * 64; }
+inline int lstar_tile_blocks(const LstarArgs &a) { return ((a.nx + a.tx - 1) / a.tx) * ((a.ny + a.ty - 1) / a.ty); }
+inline size_t lstar_tile_lds(const LstarArgs &a) { return size_t(4) * (a.tx + 2) * (a.ty + 2) * sizeof(double2); }
+
+template <typename Ctx>
+inline void lstar_args(Ctx *c, LstarArgs &a)
+{
+    a = LstarArgs{};
+    a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
+    a.early_exit = c->lstar_early_exit;
+    a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
+    a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.chi = c->chi; a.L = c->L;
+    a.xtab = c->xtab;
+    // the tiled form's 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use
+    if (a.early_exit && c->plan.p_elems >= 18 * c->V) {
+        a.T = static_cast<double *>(c->P);
+        lstar_tile(a.nx, a.ny, a.tx, a.ty);
+    }
+}
+
+// Launches the fold of the tiled form's sums into Lambda*
+inline void launch_lstar_fold(const LstarArgs &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(lstar_fold_kernel, dim3((a.nx * a.ny + kPlaneThreads - 1) / kPlaneThreads, a.nz), dim3(kPlaneThreads), 0,
+                       stream, a);
 }
 
 __global__ __launch_bounds__(kLstarThreads) void lstar_kernel(LstarArgs a)

@@ -22,7 +22,10 @@
 //   reduce_kernel_pair  per voxel (two neighbours of a row per thread), sums the partial planes of
 //                   all directions in a fixed order: J_fs = (1/chi) sum_d W_d |mu_d| sum_bands P, and
 //                   the OS right-hand side chi (J_fs - J).
-//   lstar_kernel    per voxel, the 27 derivatives dJ_v/dS_u along the lines through v (exact band).
+//   lstar_tile_kernel, lstar_fold_kernel  the 27 derivatives dJ_v/dS_u per voxel along the lines through v
+//                   (exact band): half of them per tile of voxels that share their exponentials, then the
+//                   whole by symmetry.  lstar_kernel: all of them voxel by voxel, for grids whose lines
+//                   wrap back within two layers.
 //   coef_kernel     the Jacobi coefficients: chi_v Lambda*_vu for the 13 upper neighbours (the
 //                   lower ones follow by reciprocity) and the per-voxel scalings.
 //   jacobi_kernel_column  one Jacobi sweep of the OS equations (27-point stencil), a thread marching
@@ -281,16 +284,18 @@ int ensure_lstar(rt3d_ctx *c)
 {
     if (c->have_lstar) return RT3D_OK;
     if (!c->plan_ok) return fail(c, RT3D_ERR_STATE, "no sweep plan (a shape change failed)");
-    LstarArgs a{};
-    a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
-    a.early_exit = c->lstar_early_exit;
-    a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
-    a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.chi = c->chi; a.L = c->L;
-    a.xtab = c->xtab;
+    LstarArgs a;
+    lstar_args(c, a);
     {
         TimedLaunch t(c, K_LSTAR);
-        const dim3 grid((c->g.nx * c->g.ny + kLstarThreads - 1) / kLstarThreads, c->g.nz);
-        hipLaunchKernelGGL(lstar_kernel, grid, dim3(kLstarThreads), 0, c->stream, a);
+        if (a.T) {
+            hipLaunchKernelGGL(lstar_tile_kernel, dim3(lstar_tile_blocks(a), a.nz), dim3(lstar_tile_threads(a)), lstar_tile_lds(a),
+                               c->stream, a);
+            launch_lstar_fold(a, c->stream);
+        } else {
+            const dim3 grid((c->g.nx * c->g.ny + kLstarThreads - 1) / kLstarThreads, c->g.nz);
+            hipLaunchKernelGGL(lstar_kernel, grid, dim3(kLstarThreads), 0, c->stream, a);
+        }
     }
     int rc = check_launch(c, "lstar_kernel");
     if (rc) return rc;
