@@ -80,7 +80,7 @@ struct BatchItem {
 };
 
 struct PlaneBlock {
-    int member, chunk, k, pad;
+    int member, chunk, k, xcd;
 };
 
 constexpr int kAuxBlocks = 128;      // blocks per member of the grid-stride copy / combine kernels
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kPlaneThreads) void jacobi_kernel_batch_column(cons
     const PlaneBlock b = blocks[blockIdx.x];
     if (st[b.member].mode == 0) return;
     const JacobiArgs a = args[b.member];
-    jacobi_column_body<coef>(a, b.chunk * kPlaneThreads + threadIdx.x, b.k);
+    jacobi_column_body<coef>(a, xcd_column(a.nx * a.ny, b.xcd, b.chunk * kPlaneThreads + int(threadIdx.x)), b.k);
 }
 
 // The stopping rule of the single-problem solve, per member: a step whose max |dJ|/|J| is below tol
@@ -629,17 +629,14 @@ int build_tables(rt3d_batch *b)
         const int pchunks = reduce_blocks(red[i], kPlaneThreads);
         for (int z = 0; z < nz; ++z)
             for (int ch = 0; ch < pchunks; ++ch) (c->plan.columns ? pplanes : window_pplanes).push_back(PlaneBlock{i, ch, z, 0});
-        // the Jacobi sweep's column layers, XCD-aware as in the single-problem grid: each member starts
-        // on a multiple of 8 blocks; block b of the member runs on XCD b % 8, which takes the contiguous
-        // chunk range [xcd * G, (xcd + 1) * G) of every column layer (G = chunks padded to 8, / 8);
-        // padding blocks have no voxels
-        const int group = (chunks + 7) / 8;
-        while (columns.size() % 8) columns.push_back(PlaneBlock{i, chunks, 0, 0});
+        // the Jacobi sweep's column layers, XCD-aware as in the single-problem grid: block b of the list
+        // runs on XCD b % 8, which takes its range of columns of every column layer (see xcd_column)
+        const int per_xcd = ((nx * ny + 7) / 8 + kPlaneThreads - 1) / kPlaneThreads;
         const int layers = (nz + kJacCol - 1) / kJacCol;
-        for (int bl = 0; bl < 8 * group * layers; ++bl) {
+        for (int bl = 0; bl < 8 * per_xcd * layers; ++bl) {
             const int xcd = bl & 7, slot = bl >> 3;
-            const int kc = slot / group;
-            columns.push_back(PlaneBlock{i, xcd * group + (slot - kc * group), kc, 0});
+            const int kc = slot / per_xcd;
+            columns.push_back(PlaneBlock{i, slot - kc * per_xcd, kc, xcd});
         }
     }
     // dispatch the most expensive bands of all members first

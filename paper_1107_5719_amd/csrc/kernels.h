@@ -1234,7 +1234,7 @@ __device__ inline void jacobi_block_max(const JacobiArgs &a, double q, double di
     __syncthreads();
     if (threadIdx.x == 0) {
         double m = wmax[0][0], md = wmax[1][0];
-        for (int w = 1; w < kPlaneThreads / 64; ++w) { m = fmax(m, wmax[0][w]); md = fmax(md, wmax[1][w]); }
+        for (int w = 1; w < int(blockDim.x) / 64; ++w) { m = fmax(m, wmax[0][w]); md = fmax(md, wmax[1][w]); }
         atomicMax(a.maxrel, static_cast<unsigned long long>(__double_as_longlong(m)));
         if (a.Ja || a.abs_measure) atomicMax(a.maxdist, static_cast<unsigned long long>(__double_as_longlong(md)));
     }
@@ -1350,8 +1350,8 @@ __global__ __launch_bounds__(kPlaneThreads) void jacobi_kernel_tiled(JacobiArgs 
 // Column form: a thread takes H voxels (i, j, k0 .. k0 + H - 1) and marches up them, keeping the
 // previous iterates of three planes in registers, so each voxel loads one new plane of nine iterates
 // instead of 26 neighbours (the coefficient streams and the per-voxel sums are those of jacobi_core,
-// in the same order).  Blocks are dealt to the XCDs in contiguous ranges of chunks per column layer,
-// as in jacobi_kernel_grouped.  H = 4 on grids that fill the chip; smaller grids take shorter columns
+// in the same order).  Every column layer's columns are dealt to the XCDs in contiguous ranges of equal
+// length (xcd_column).  H = 4 on grids that fill the chip; smaller grids take shorter columns
 // (more threads), see jacobi_column_height.
 constexpr int kJacCol = 4;
 // Column layer kc of the columns p (p = j nx + i; p >= nx ny: no voxels).  The whole block must call
@@ -1423,6 +1423,27 @@ __device__ inline void jacobi_column_body(const JacobiArgs &a, int p, int kc)
     if (a.J) jacobi_block_max(a, q, dist, bad);
 }
 
+// The column layers' columns are dealt to the XCDs in contiguous ranges of equal length: column q of XCD xcd's
+// range among n (n: none).  Ranges of whole blocks left XCDs idle (65^2 columns: two of eight, 129^2: one for two
+// thirds of the time).  us per sweep with those and with these: float64 coefficients 17^3 4.0 and 3.3, 33^3 5.3 and
+// 5.1, 65^3 13.1 and 10.8, 97^3 27.4 and 26.5, 113^3 44.6 and 43.4, 129^3 65.3 and 65.3; float32 ones 65^3 9.2 and
+// 7.9, 129^3 35.0 and 33.6.
+__device__ inline int xcd_column(int n, int xcd, int q)
+{
+    const int cols = (n + 7) / 8;
+    return q < cols ? min(xcd * cols + q, n) : n;
+}
+// Threads of a block of the column layout: those that leave the fewest lanes of an XCD's range idle, the
+// more the better.
+inline int jacobi_column_threads(int n)
+{
+    const int cols = (n + 7) / 8;
+    int best = 256;
+    for (int t : {192, 128})
+        if ((cols + t - 1) / t * t < (cols + best - 1) / best * best) best = t;
+    return best;
+}
+
 // reverse: the column layers in descending order (top first).  Consecutive sweeps alternate, so each
 // starts where the previous one ended and finds its most recent planes still in the caches; the order
 // of the blocks does not change any voxel's sum.
@@ -1436,7 +1457,7 @@ __global__ __launch_bounds__(kPlaneThreads) void jacobi_kernel_column(JacobiArgs
     const int xcd = blk & 7, slot = blk >> 3;
     const int kc = slot / group;
     const int kcol = reverse ? int(gridDim.x) / (8 * group) - 1 - kc : kc;
-    const int p = (xcd * group + (slot - kc * group)) * kPlaneThreads + threadIdx.x;
+    const int p = xcd_column(a.nx * a.ny, xcd, (slot - kc * group) * int(blockDim.x) + int(threadIdx.x));
     if (alt_walk && (kcol & 1)) jacobi_column_body<coef, H, true>(a, p, kcol);
     else jacobi_column_body<coef, H, false>(a, p, kcol);
 }
@@ -1501,17 +1522,18 @@ inline void launch_jacobi_sweep(const JacobiArgs &a, int layout, bool f32, hipSt
     const dim3 blk(kPlaneThreads);
     if (layout == 4) {
         const int H = height > 0 ? height : jacobi_column_height(a.nx, a.ny, a.nz);
-        const dim3 grid(unsigned(8 * group) * unsigned((a.nz + H - 1) / H));
+        const int nt = jacobi_column_threads(a.nx * a.ny), per_xcd = ((a.nx * a.ny + 7) / 8 + nt - 1) / nt;
+        const dim3 grid(unsigned(8 * per_xcd) * unsigned((a.nz + H - 1) / H)), cblk(nt);
         const int rev = reverse ? 1 : 0, md = jacobi_alt_walk(walk, f32, H) ? 1 : 0;
         if (H == 1) {
-            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 1>), grid, blk, 0, stream, a, group, rev, md);
-            else hipLaunchKernelGGL((jacobi_kernel_column<double, 1>), grid, blk, 0, stream, a, group, rev, md);
+            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 1>), grid, cblk, 0, stream, a, per_xcd, rev, md);
+            else hipLaunchKernelGGL((jacobi_kernel_column<double, 1>), grid, cblk, 0, stream, a, per_xcd, rev, md);
         } else if (H == 2) {
-            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 2>), grid, blk, 0, stream, a, group, rev, md);
-            else hipLaunchKernelGGL((jacobi_kernel_column<double, 2>), grid, blk, 0, stream, a, group, rev, md);
+            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 2>), grid, cblk, 0, stream, a, per_xcd, rev, md);
+            else hipLaunchKernelGGL((jacobi_kernel_column<double, 2>), grid, cblk, 0, stream, a, per_xcd, rev, md);
         } else {
-            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 4>), grid, blk, 0, stream, a, group, rev, md);
-            else hipLaunchKernelGGL((jacobi_kernel_column<double, 4>), grid, blk, 0, stream, a, group, rev, md);
+            if (f32) hipLaunchKernelGGL((jacobi_kernel_column<float, 4>), grid, cblk, 0, stream, a, per_xcd, rev, md);
+            else hipLaunchKernelGGL((jacobi_kernel_column<double, 4>), grid, cblk, 0, stream, a, per_xcd, rev, md);
         }
     } else if (layout == 3) {
         const int tiles_x = (a.nx + kTileX - 1) / kTileX, tiles_y = (a.ny + kTileY - 1) / kTileY;
