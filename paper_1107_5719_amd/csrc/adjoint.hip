@@ -301,19 +301,21 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
     HIP_TRY(c, hipMemsetAsync(c->d_scal, 0, kScalarBytes, c->stream), "memset");
     const double *in = nullptr;
     double *bufs[2] = {c->dJa, c->dJb};
-    for (int m = 0; m < M; ++m) {
-        const bool last = m == M - 1;
+    for (int m = 0, n = 0; m < M; m += n) {
+        n = jacobi_sweeps_at(c, m, M);
+        const bool last = m + n == M;
         JacobiArgs ja{};
         ja.nx = c->g.nx; ja.ny = c->g.ny; ja.nz = c->g.nz;
         ja.b = c->adj_r;
         ja.Kc = c->coef_fp32 ? static_cast<const void *>(c->Kc32) : static_cast<const void *>(c->Kc);
         ja.invD = c->invD; ja.E = c->Ecoef;
         ja.w_in = in;
-        ja.w_out = last ? nullptr : bufs[m & 1];
+        ja.w_out = last ? nullptr : in == bufs[0] ? bufs[1] : bufs[0];
         ja.J = last ? c->adj_nu : nullptr;
         ja.maxrel = c->d_maxrel; ja.maxdist = c->d_maxdist; ja.nonfinite = c->d_flag;
         ja.abs_measure = 1;
-        launch_jacobi_sweep(ja, c->jacobi_xcd, c->coef_fp32 != 0, c->stream, c->jacobi_alternate && (m & 1) == 0,
+        if (n == 2) launch_jacobi_pair(ja, c->jacobi_tile, c->coef_fp32 != 0, c->stream);
+        else launch_jacobi_sweep(ja, c->jacobi_xcd, c->coef_fp32 != 0, c->stream, c->jacobi_alternate && (m & 1) == 0,
                             c->jacobi_height, c->jacobi_walk);
         if ((rc = check_launch(c, "jacobi_kernel (adjoint)"))) return rc;
         in = ja.w_out;

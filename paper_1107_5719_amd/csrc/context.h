@@ -40,6 +40,7 @@ struct rt3d_ctx {
                                     // orders (RT3D_JACOBI_ALTERNATE=0: always bottom first)
     int jacobi_height = 0;     // column layout: voxels per column, 1, 2 or 4 (0: by grid size;
                                // RT3D_JACOBI_COLUMN)
+    rt3d::JacobiTile jacobi_tile{};   // of the launches of two sweeps
     int jacobi_walk = -1;      // column layout: odd column layers walk top down (1), never (0), or for
                                // float coefficients in columns of 4 (-1) (RT3D_JACOBI_WALK)
     // device buffers (owned)
@@ -123,6 +124,8 @@ int sync(rt3d_ctx *c);
 int check_launch(rt3d_ctx *c, const char *what);
 int ensure_lstar(rt3d_ctx *c);
 int finish_lstar(rt3d_ctx *c);
+// How many Jacobi sweeps, one or two, the launch at sweep m of M does
+int jacobi_sweeps_at(const rt3d_ctx *c, int m, int M);
 int validate_desc(const rt3d_grid_desc *g, std::string &msg);
 int validate_medium_host(long V, const double *chi, const double *eps, const double *B, std::string &msg);
 hipMemcpyKind kind_in(int ptr_kind);

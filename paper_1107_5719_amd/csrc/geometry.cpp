@@ -512,4 +512,42 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
     return true;
 }
 
+JacobiTile choose_jacobi_tile(int nx, int ny, int nz)
+{
+    // A launch takes about 2 us, 3 more for each round of workgroups (24 wavefronts of a CU at once), and for each
+    // wavefront of the fullest CU 0.1 us, as much for every previous iterate per thread and 0.8 / tx for the loads of
+    // rows that end within it (fitted to 17^3 .. 72^3, for instance 65^3 with tiles of 13 x 5 x 5 / 17 x 4 x 4 / 6 x 6 x 6 /
+    // 5 x 5 x 11: 19.6 / 21.6 / 21.3 / 27.3 us for two sweeps).
+    JacobiTile best{};
+    double best_us = 1e300;
+    // the next tile size that divides an axis of n into fewer nearly equal parts
+    auto next = [](int n, int t) {
+        const int parts = (n + t - 1) / t;
+        return parts == 1 ? n + 1 : (n + parts - 2) / (parts - 1);
+    };
+    for (int tx = 1; tx <= nx && (tx + 2) * 9 <= kPairThreads; tx = next(nx, tx))
+        for (int ty = 1; ty <= ny && (tx + 2) * (ty + 2) * 3 <= kPairThreads; ty = next(ny, ty))
+            for (int z = 1; z <= nz && (tx + 2) * (ty + 2) * (z + 2) <= kPairThreads; z = next(nz, z)) {
+                JacobiTile t;
+                t.tx = tx;
+                t.ty = ty;
+                t.z = z;
+                t.ntx = (nx + tx - 1) / tx;
+                t.nty = (ny + ty - 1) / ty;
+                t.ntz = (nz + z - 1) / z;
+                if (t.cells0() > kPairLoads * t.threads()) continue;
+                const int w = t.threads() / 64, at_once = 256 * (24 / w);
+                // (a workgroup that has a CU to itself waits at its barriers with nothing else to run)
+                const int b = t.blocks();
+                const double waves = (b <= 512 ? (b + 255) / 256 : b / 256.0) * w * (24 / w == 1 ? 1.25 : 1.0);
+                const double us = 2.0 + (0.1 + 0.8 / tx + 0.1 * t.cells0() / t.cells()) * waves +
+                                  3.0 * ((t.blocks() + at_once - 1) / at_once);
+                if (us < best_us) {
+                    best_us = us;
+                    best = t;
+                }
+            }
+    return best;
+}
+
 }  // namespace rt3d

@@ -165,4 +165,19 @@ double column_load(int nx, int ny, int nz, const AngleSet &A);
 // Cycles per segment of a wavefront of the column form that has its SIMD to itself, with rows line rows
 inline double column_segment_cycles(int rows) { return 450.0 + 165.0 * rows; }
 
+// The tile of a launch that does two Jacobi sweeps: a workgroup puts out tx x ty x z voxels.
+struct JacobiTile {
+    int tx, ty, z;
+    int ntx, nty, ntz;
+    // its first sweep has a voxel more to each side, the previous iterates two
+    constexpr int cells() const { return (tx + 2) * (ty + 2) * (z + 2); }
+    constexpr int cells0() const { return (tx + 4) * (ty + 4) * (z + 4); }
+    constexpr int threads() const { return (cells() + 63) / 64 * 64; }
+    constexpr int blocks() const { return ntx * nty * ntz; }
+    constexpr size_t lds() const { return size_t(cells0() + cells()) * sizeof(double); }
+};
+constexpr int kPairThreads = 1024;      // most threads of its workgroup
+constexpr int kPairLoads = 3;           // most previous iterates that a thread brings
+JacobiTile choose_jacobi_tile(int nx, int ny, int nz);
+
 }  // namespace rt3d

@@ -1228,7 +1228,7 @@ __device__ inline void jacobi_block_max(const JacobiArgs &a, double q, double di
         q = fmax(q, __shfl_xor(q, offs));
         dist = fmax(dist, __shfl_xor(dist, offs));
     }
-    __shared__ double wmax[2][kPlaneThreads / 64];
+    __shared__ double wmax[2][16];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) { wmax[0][wid] = q; wmax[1][wid] = dist; }
     __syncthreads();
@@ -1478,6 +1478,133 @@ inline int jacobi_column_height(int nx, int ny, int nz)
 // 129^2 x 193 55.2 -> 52.9 us, 65^3 (columns of 2) 9.24 against 9.30 us; float64 coefficients 129^3
 // 67.4 -> 73.3 us (L2 fetches 389 against 384 MB), 65^3 13.5 -> 13.0 us.
 inline bool jacobi_alt_walk(int walk, bool f32, int H) { return walk >= 0 ? walk != 0 : (f32 && H == 4); }
+
+__device__ __forceinline__ double buffer_load(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, double)
+{
+    typedef int int2v __attribute__((ext_vector_type(2)));
+    const int2v x = __builtin_amdgcn_raw_buffer_load_b64(r, int(voff), int(soff), 0);
+    return __hiloint2double(x.y, x.x);
+}
+__device__ __forceinline__ float buffer_load(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float)
+{
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, int(voff), int(soff), 0));
+}
+
+// Two sweeps in one launch: a workgroup puts out tx x ty x z voxels; a thread takes one voxel of these and
+// the layer of voxels around them, computes its first sweep from the previous iterates, which the workgroup has
+// brought to LDS, and, if it is one of those put out, its second from the first sweep's values in LDS, with
+// the coefficients that it still holds.  Bitwise two sweeps of jacobi_core.
+// What bounds a single sweep: on small grids the launch and one wait for memory (3.3 us), on larger ones its whole
+// footprint, since an XCD's L2 keeps nothing from one launch to the next; two sweeps have both once.  Against that stand
+// 1.5 to 3 times the loads of coefficients within an XCD (the tiles' borders).  us per sweep, single and so:
+// 17^3 3.1 and 2.3, 33^3 4.9 and 3.3, 50^3 7.1 and 5.1, 65^3 10.6 and 9.8, 97^3 26.6 and 24.3, 113^3 43.4 and 37.4; but 129^3
+// 65.3 and 65.9, and with float coefficients (half the footprint, the same loads) 33^3 4.3 and 3.2, 50^3 5.5 and 4.6, 56^3
+// 6.4 and 6.1, 65^3 7.9 and 9.0.  (Walking a tile's planes with three of them in LDS: 11.5 us at 65^3, 72 at 129^3; the
+// waits of its steps follow each other.)
+template <typename coef>
+__device__ inline void jacobi_pair_body(const JacobiArgs &a, const rt3d::JacobiTile &T, int block, double *lds)
+{
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const unsigned plane = unsigned(nx) * unsigned(ny), V = plane * unsigned(nz);
+    const int bz = block / (T.ntx * T.nty), bxy = block - bz * (T.ntx * T.nty), by = bxy / T.ntx, bx = bxy - by * T.ntx;
+    const int x0 = bx * T.tx, y0 = by * T.ty, k0 = bz * T.z;
+    const int cx = T.tx + 2, cy = T.ty + 2, cells = T.cells(), wx = T.tx + 4, wy = T.ty + 4, wcells = T.cells0();
+    double *w0 = lds, *w1 = lds + wcells;
+    const int tid = int(threadIdx.x), q = min(tid, cells - 1);
+    const int lz = q / (cx * cy), r = q - lz * (cx * cy), ly = r / cx, lx = r - ly * cx;
+    auto wrap = [](int x, int n) {          // x in [-n, 2n)
+        x += x < 0 ? n : 0;
+        return x - (x >= n ? n : 0);
+    };
+    const int gx = x0 + lx - 1, gy = y0 + ly - 1, k = k0 + lz - 1;
+    const bool live = tid < cells && k >= 0 && k < nz;
+    const bool inner = live && unsigned(lx - 1) < unsigned(T.tx) && unsigned(ly - 1) < unsigned(T.ty) &&
+                       unsigned(lz - 1) < unsigned(T.z) && gx < nx && gy < ny;
+    const int kc = min(max(k, 0), nz - 1);
+    unsigned at[9];               // the nine columns around it, in its plane
+#pragma unroll
+    for (int m = 0; m < 9; ++m)
+        at[m] = unsigned(kc) * plane + unsigned(wrap(wrap(gy, ny) + m / 3 - 1, ny) * nx + wrap(wrap(gx, nx) + m % 3 - 1, nx));
+    const auto rsrc = [](const void *p, unsigned bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, int(bytes), 0x00027000);
+    };
+    const __amdgpu_buffer_rsrc_t rK = rsrc(a.Kc, 13u * V * unsigned(sizeof(coef))), rb = rsrc(a.b, V * 8u), rE = rsrc(a.E, V * 8u);
+    constexpr int U = rt3d::kPairLoads;
+    double wr[U];
+    if (a.w_in) {
+        const __amdgpu_buffer_rsrc_t rw = rsrc(a.w_in, V * 8u);
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int e = min(tid + t * int(blockDim.x), wcells - 1);
+            if (t * int(blockDim.x) >= wcells) break;
+            const int sz = e / (wx * wy), s = e - sz * (wx * wy), sy = s / wx, sx = s - sy * wx;
+            const int kk = min(max(k0 + sz - 2, 0), nz - 1);
+            wr[t] = buffer_load(rw, (unsigned(kk) * plane + unsigned(wrap(y0 + sy - 2, ny) * nx + wrap(x0 + sx - 2, nx))) * 8u, 0, 0.0);
+        }
+    }
+    coef K[26];
+    const unsigned cs = unsigned(sizeof(coef)), down = k > 0 ? plane : 0u;
+#pragma unroll
+    for (int o = 0; o < 9; ++o) K[o] = buffer_load(rK, (at[o] - down) * cs, unsigned(12 - o) * V * cs, coef(0));
+#pragma unroll
+    for (int o = 9; o < 13; ++o) K[o] = buffer_load(rK, at[o - 9] * cs, unsigned(12 - o) * V * cs, coef(0));
+#pragma unroll
+    for (int o = 14; o < 27; ++o) K[o - 1] = buffer_load(rK, at[4] * cs, unsigned(o - 14) * V * cs, coef(0));
+    const double b = buffer_load(rb, at[4] * 8u, 0, 0.0), e = buffer_load(rE, at[4] * 8u, 0, 0.0);
+    // sum over the neighbours in jacobi_core's order, the planes beyond the grid's faces clamped as there
+    auto stencil = [&](const double *w, int sx, int sxy) {
+        double part[3] = {0.0, 0.0, 0.0};
+        const int dz[3] = {k > 0 ? -sxy : 0, 0, k < nz - 1 ? sxy : 0};
+#pragma unroll
+        for (int z = 0; z < 3; ++z)
+#pragma unroll
+            for (int m = 0; m < 9; ++m) {
+                const int o = 9 * z + m;
+                if (o == 13) continue;
+                part[z] = fma(double(K[o < 13 ? o : o - 1]), w[dz[z] + (m / 3 - 1) * sx + m % 3 - 1], part[z]);
+            }
+        return b + ((k > 0 ? part[0] : 0.0) + part[1] + part[2]);
+    };
+    double acc = b;
+    if (a.w_in) {
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+            if (tid + t * int(blockDim.x) < wcells) w0[tid + t * int(blockDim.x)] = wr[t];
+        __syncthreads();
+        if (live) acc = stencil(w0 + ((lz + 1) * wy + ly + 1) * wx + lx + 1, wx, wx * wy);
+    }
+    if (live) w1[q] = acc * e;
+    __syncthreads();
+    double qmax = 0.0, dist = 0.0;
+    bool bad = false;
+    if (inner) {
+        acc = stencil(w1 + q, cx, cx * cy);
+        if (a.w_out) a.w_out[at[4]] = acc * e;
+        if (a.J) jacobi_update(a, at[4], acc, qmax, dist, bad);
+    }
+    if (a.J) jacobi_block_max(a, qmax, dist, bad);
+}
+
+template <typename coef>
+__global__ __launch_bounds__(rt3d::kPairThreads) void jacobi_kernel_pair(JacobiArgs a, rt3d::JacobiTile T)
+{
+    extern __shared__ double pair_lds[];
+    // blocks go round-robin over the 8 XCDs: neighbouring tiles to one of them
+    const int n = int(gridDim.x), per = n / 8, rest = n % 8, x = int(blockIdx.x) & 7, i = int(blockIdx.x) >> 3;
+    jacobi_pair_body<coef>(a, T, x * per + min(x, rest) + i, pair_lds);
+}
+
+// Grids up to these numbers of voxels take two sweeps per launch: between the sizes above where it pays and where it
+// does not.  (Its buffer offsets need 13 coefficients of all voxels to stay below 4 GB.)
+inline bool jacobi_pair_pays(long V, bool f32) { return V <= (f32 ? 3L << 16 : 3L << 19); }
+
+inline void launch_jacobi_pair(const JacobiArgs &a, const rt3d::JacobiTile &t, bool f32, hipStream_t stream)
+{
+    const dim3 grid(t.blocks()), blk(t.threads());
+    const size_t smem = t.lds();
+    if (f32) hipLaunchKernelGGL(jacobi_kernel_pair<float>, grid, blk, smem, stream, a, t);
+    else hipLaunchKernelGGL(jacobi_kernel_pair<double>, grid, blk, smem, stream, a, t);
+}
 
 // Gauss-Seidel colour pass.  The voxels are coloured per axis so that no two 27-point neighbours share
 // a colour: index i has colour i mod 2, except on a periodic axis of odd length, where the last index

@@ -30,7 +30,8 @@
 //                   lower ones follow by reciprocity) and the per-voxel scalings.
 //   jacobi_kernel_column  one Jacobi sweep of the OS equations (27-point stencil), a thread marching
 //                   up a column of 4 voxels; the last sweep also updates J and reduces max |dJ|/|J|
-//                   (and flags NaN/Inf).  jacobi_kernel_colour: one colour pass of the multicolour
+//                   (and flags NaN/Inf); jacobi_kernel_pair: two sweeps, on grids up to 113^3 or so.
+//                   jacobi_kernel_colour: one colour pass of the multicolour
 //                   Gauss-Seidel alternative.
 #include <hip/hip_runtime.h>
 
@@ -322,9 +323,20 @@ int finish_lstar(rt3d_ctx *c)
 }
 
 int launch_jacobi_args(rt3d_ctx *c, const JacobiArgs &a, bool reverse = false);
+
+int jacobi_sweeps_at(const rt3d_ctx *c, int m, int M)
+{
+    // every setting of the layout but the default one asks for single sweeps, as does timing every launch
+    const bool plain = c->jacobi_xcd == 4 && c->jacobi_alternate && c->jacobi_height == 0 && c->jacobi_walk < 0;
+    if (!plain || c->timing == 1 || !jacobi_pair_pays(c->V, c->coef_fp32 != 0)) return 1;
+    // sampled timing keeps the first and the last sweep apart; otherwise an odd number has its first apart
+    const int left = (c->timing == 2 ? M - 1 : M) - m;
+    if (m == 0) return c->timing != 2 && left % 2 == 0 ? 2 : 1;
+    return left >= 2 ? 2 : 1;
+}
 int gauss_seidel_sweeps(rt3d_ctx *c, int M);
 
-int launch_jacobi(rt3d_ctx *c, const double *w_in, double *w_out, bool update, bool chosen, bool reverse)
+int launch_jacobi(rt3d_ctx *c, const double *w_in, double *w_out, bool update, int n, bool chosen, bool reverse)
 {
     JacobiArgs a{};
     const bool f32 = c->precision == RT3D_FP32_SWEEP;
@@ -337,6 +349,11 @@ int launch_jacobi(rt3d_ctx *c, const double *w_in, double *w_out, bool update, b
     a.Ja = (f32 && update) ? c->Ja : nullptr;
     a.maxdist = c->d_maxdist;
     TimedLaunch t(c, K_JACOBI, chosen);
+    if (n == 2) {
+        c->kernel_launches[K_JACOBI] += 1;
+        launch_jacobi_pair(a, c->jacobi_tile, c->coef_fp32 != 0, c->stream);
+        return check_launch(c, "jacobi_kernel_pair");
+    }
     return launch_jacobi_args(c, a, reverse);
 }
 
@@ -586,6 +603,7 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
     c->precision = precision;
     c->stream = stream;
     c->sweep_load = load;
+    c->jacobi_tile = rt3d::choose_jacobi_tile(g->nx, g->ny, g->nz);
     c->real_size = (precision == RT3D_FP64) ? sizeof(double) : sizeof(float);
     c->V = long(g->nx) * g->ny * g->nz;
     if (!rt3d::make_angle_set(g->n_theta, g->n_phi, c->A)) { delete c; msg = "bad angle set"; return RT3D_ERR_ARG; }
@@ -911,16 +929,17 @@ int rt3d_os_step(rt3d_ctx *c, int inner_sweeps, double *max_rel_dJ_out)
         const double *in = nullptr;
         double *bufs[2] = {c->dJa, c->dJb};
         std::optional<TimedGroup> group;
-        for (int m = 0; m < inner_sweeps; ++m) {
-            const bool last = (m == inner_sweeps - 1);
-            double *out = last ? nullptr : bufs[m & 1];
+        for (int m = 0, n = 0; m < inner_sweeps; m += n) {
             // sampled timing: the intermediate sweeps 1 .. M-2 as one group (the first sweep, from
             // dJ = 0, and the last, which updates J, are cheaper and dearer); with M <= 2 the first
             if (m == 1 && inner_sweeps > 2) group.emplace(c, K_JACOBI, inner_sweeps - 2);
+            n = jacobi_sweeps_at(c, m, inner_sweeps);
+            const bool last = m + n == inner_sweeps;
+            double *out = last ? nullptr : in == bufs[0] ? bufs[1] : bufs[0];
             // even sweeps top first: the first reads the right-hand side the reduction wrote last at the
             // top, and each later sweep starts where the one before ended
-            rc = launch_jacobi(c, in, out, last, inner_sweeps <= 2 && m == 0, (m & 1) == 0);
-            if (m == inner_sweeps - 2 && group) group->end();
+            rc = launch_jacobi(c, in, out, last, n, inner_sweeps <= 2 && m == 0, (m & 1) == 0);
+            if (m + n == inner_sweeps - 1 && group) group->end();
             if (rc) return rc;
             in = out;
         }
