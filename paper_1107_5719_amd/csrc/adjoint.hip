@@ -55,12 +55,60 @@ struct AdjLineArgs {
     const double *nu, *eps;       // weights c = (1 - eps) nu W|mu| of the deposits, or nu == null
     double *Qx;                   // [n_dir][nz][ny*nx]: adjoint q leaving layer k along line p
     double *Qstart;               // [n_up][ny*nx]: q at the start of the upward lines (or null)
+    const double *xtab;           // [kExpTab]
 };
 
 __device__ inline int wrap_any(int a, int n)
 {
     const int r = a % n;
     return r < 0 ? r + n : r;
+}
+
+// The segments of one direction and layer: lane l of a wavefront holds segment l, its column and row offsets reduced
+// modulo the grid, so that the reductions (integer divisions) are done once for a layer's segments and the
+// lines only add.  More than 64 segments, which only hundreds of angles have, are read where they are used.
+struct LayerLanes {
+    int off, n, A, B;
+    double len;
+    __device__ LayerLanes(const AdjLineArgs &a, int dk)
+    {
+        off = a.seg_off[dk];
+        n = a.seg_n[dk];
+        const int t = off + min(int(threadIdx.x) & 63, n - 1);
+        A = wrap_any(a.seg_ai[t], a.nx);
+        B = wrap_any(a.seg_bi[t], a.ny);
+        len = a.seg_len[t];
+    }
+    __device__ void get(const AdjLineArgs &a, int s, int &As, int &Bs, double &ls) const
+    {
+        if (n <= 64) {
+            As = __builtin_amdgcn_readlane(A, s);
+            Bs = __builtin_amdgcn_readlane(B, s);
+            ls = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(len), s), __builtin_amdgcn_readlane(__double2loint(len), s));
+        } else {
+            As = wrap_any(a.seg_ai[off + s], a.nx);
+            Bs = wrap_any(a.seg_bi[off + s], a.ny);
+            ls = a.seg_len[off + s];
+        }
+    }
+};
+
+// voxel (in its plane) of the segment with reduced offsets A, B of the line whose top column is (i0, j0)
+__device__ inline int line_voxel(const AdjLineArgs &a, int i0, int j0, int A, int B)
+{
+    int col = i0 + A, row = j0 + B;
+    col -= col >= a.nx ? a.nx : 0;
+    row -= row >= a.ny ? a.ny : 0;
+    return row * a.nx + col;
+}
+
+// the float64 exponential's table (see exp_pair_tab) in LDS; the whole block calls this
+__device__ inline const double *line_exp_table(const AdjLineArgs &a)
+{
+    __shared__ double tab[kExpTab];
+    if (threadIdx.x < kExpTab) tab[threadIdx.x] = a.xtab[threadIdx.x];
+    __syncthreads();
+    return tab;
 }
 
 // voxel of segment s (table index t) of the line whose top column is (i0, j0), in layer k
@@ -72,12 +120,13 @@ __device__ inline long seg_voxel(const AdjLineArgs &a, int i0, int j0, int k, in
 }
 
 // Forward pass: the intensity entering every layer of every line (the formal solution's recurrence).
+// One line per thread; 65^3 x 64 254 us with two integer divisions and a library expm1 per segment, 207 us so (bound by
+// the gathers of the shallowest lines, one after the other; loading a layer's segments ahead changed nothing).
 __global__ __launch_bounds__(kLineThreads) void adj_record_kernel(AdjLineArgs a)
 {
-    const int p = blockIdx.x * kLineThreads + threadIdx.x;
+    const double *tab = line_exp_table(a);
+    const int nxy = a.nx * a.ny, p0 = blockIdx.x * kLineThreads + threadIdx.x, p = min(p0, nxy - 1);
     const int d = blockIdx.y;
-    const int nxy = a.nx * a.ny;
-    if (p >= nxy) return;
     const int i0 = p % a.nx, j0 = p / a.nx;
     const bool down = a.dirs[d].down != 0;
     double I = a.I_top;
@@ -87,11 +136,14 @@ __global__ __launch_bounds__(kLineThreads) void adj_record_kernel(AdjLineArgs a)
     }
     for (int step = 0; step < a.nz; ++step) {
         const int k = down ? a.nz - 1 - step : step;
-        a.Ient[(long(d) * a.nz + k) * nxy + p] = I;
-        const int off = a.seg_off[d * a.nz + k], n = a.seg_n[d * a.nz + k];
-        for (int s = 0; s < n; ++s) {
-            const long v = seg_voxel(a, i0, j0, k, off + s);
-            const double em1 = expm1(-a.chi[v] * a.seg_len[off + s]);
+        const LayerLanes L(a, d * a.nz + k);
+        if (p0 < nxy) a.Ient[(long(d) * a.nz + k) * nxy + p] = I;
+        for (int s = 0; s < L.n; ++s) {
+            int A, B;
+            double len;
+            L.get(a, s, A, B, len);
+            const long v = long(k) * nxy + line_voxel(a, i0, j0, A, B);
+            const double em1 = expm1_nonpos_tab(-a.chi[v] * len, tab);
             I = I + (I - a.S[v]) * em1;
         }
     }
@@ -103,28 +155,32 @@ __device__ inline double deposit_weight(const AdjLineArgs &a, long v, double wmu
 }
 
 // Backward pass: q from the end of every line back to its start, stored where it leaves each layer.
-__global__ __launch_bounds__(kLineThreads) void adj_back_kernel(AdjLineArgs a)
+// Without nu downward lines carry nothing (up_only: blockIdx.y counts the upward directions).  65^3 x 64 294 us before
+// (as adj_record_kernel), 306 with and 174 without nu now.
+__global__ __launch_bounds__(kLineThreads) void adj_back_kernel(AdjLineArgs a, int up_only)
 {
-    const int p = blockIdx.x * kLineThreads + threadIdx.x;
-    const int d = blockIdx.y;
-    const int nxy = a.nx * a.ny;
-    if (p >= nxy) return;
+    const double *tab = line_exp_table(a);
+    const int nxy = a.nx * a.ny, p0 = blockIdx.x * kLineThreads + threadIdx.x, p = min(p0, nxy - 1);
+    const int d = blockIdx.y + (up_only ? a.n_dir / 2 : 0);
     const int i0 = p % a.nx, j0 = p / a.nx;
     const bool down = a.dirs[d].down != 0;
     const double wmu = a.dirs[d].wmu;
     double q = down ? 0.0 : a.g[long(d - a.n_dir / 2) * nxy + p];
     for (int step = 0; step < a.nz; ++step) {
         const int k = down ? step : a.nz - 1 - step;      // reverse travel order
-        a.Qx[(long(d) * a.nz + k) * nxy + p] = q;
-        const int off = a.seg_off[d * a.nz + k], n = a.seg_n[d * a.nz + k];
-        for (int s = n - 1; s >= 0; --s) {
-            const long v = seg_voxel(a, i0, j0, k, off + s);
-            const double em1 = expm1(-a.chi[v] * a.seg_len[off + s]);
+        const LayerLanes L(a, d * a.nz + k);
+        if (p0 < nxy) a.Qx[(long(d) * a.nz + k) * nxy + p] = q;
+        for (int s = L.n - 1; s >= 0; --s) {
+            int A, B;
+            double len;
+            L.get(a, s, A, B, len);
+            const long v = long(k) * nxy + line_voxel(a, i0, j0, A, B);
+            const double em1 = expm1_nonpos_tab(-a.chi[v] * len, tab);
             const double c = deposit_weight(a, v, wmu);
             q = q - (c - q) * em1;                           // q e + c (1 - e)
         }
     }
-    if (!down && a.Qstart) a.Qstart[long(d - a.n_dir / 2) * nxy + p] = q;   // sensitivity to the entry light
+    if (p0 < nxy && !down && a.Qstart) a.Qstart[long(d - a.n_dir / 2) * nxy + p] = q;   // sensitivity to the entry light
 }
 
 // LTE-diffusion inner condition: the entry light B_0 + mu (B_0 - B_1) / dtau of an upward line
@@ -153,48 +209,59 @@ __global__ void adj_bc_kernel(AdjLineArgs a, const double *B, double *pull)
 // Per voxel, over all directions and the segments of its layer that lie in it:
 //   mode 0:  out = a_v / chi_v,  a_v = sum q_out (1 - e)                  (nu == null)
 //   mode 1:  out = sum l (c S + (c - q_out)(I_in - S) e)
+// (mode 0: the upward directions only, downward lines carry nothing.)  65^3 x 64 690 and 1330 us in modes 0 and 1 with
+// integer divisions and library exponentials per segment, 206 and 874 us so.
 __global__ __launch_bounds__(kPlaneThreads) void adj_pull_kernel(AdjLineArgs a, int mode, double *out)
 {
-    const int p = blockIdx.x * kPlaneThreads + threadIdx.x;
+    const double *tab = line_exp_table(a);
+    const int nxy = a.nx * a.ny, p0 = blockIdx.x * kPlaneThreads + threadIdx.x, p = min(p0, nxy - 1);
     const int k = blockIdx.y;
-    const int nxy = a.nx * a.ny;
-    if (p >= nxy) return;
     const int i = p % a.nx, j = p / a.nx;
-    const long v = long(k) * nxy + p;
-    const double chiv = a.chi[v], Sv = a.S[v];
+    const long plane = long(k) * nxy, v = plane + p;
+    const double chiv = a.chi[v], Sv = a.S[v], cv = deposit_weight(a, v, 1.0);
     double acc = 0.0;
-    for (int d = 0; d < a.n_dir; ++d) {
+    for (int d = mode == 0 ? a.n_dir / 2 : 0; d < a.n_dir; ++d) {
         const double wmu = a.dirs[d].wmu;
-        const int off = a.seg_off[d * a.nz + k], n = a.seg_n[d * a.nz + k];
+        const LayerLanes L(a, d * a.nz + k);
+        const int n = L.n;
         for (int s = 0; s < n; ++s) {
             // the line whose segment s lies in v
-            const int i0 = wrap_any(i - a.seg_ai[off + s], a.nx);
-            const int j0 = wrap_any(j - a.seg_bi[off + s], a.ny);
-            const long line = long(j0) * a.nx + i0;
-            const long lk = (long(d) * a.nz + k) * nxy + line;
+            int A, B;
+            double len;
+            L.get(a, s, A, B, len);
+            int i0 = i - A, j0 = j - B;
+            i0 += i0 < 0 ? a.nx : 0;
+            j0 += j0 < 0 ? a.ny : 0;
+            const long lk = (long(d) * a.nz + k) * nxy + long(j0) * a.nx + i0;
             double q = a.Qx[lk];
             for (int s2 = n - 1; s2 > s; --s2) {
-                const long v2 = seg_voxel(a, i0, j0, k, off + s2);
-                const double em1 = expm1(-a.chi[v2] * a.seg_len[off + s2]);
+                int A2, B2;
+                double len2;
+                L.get(a, s2, A2, B2, len2);
+                const long v2 = plane + line_voxel(a, i0, j0, A2, B2);
+                const double em1 = expm1_nonpos_tab(-a.chi[v2] * len2, tab);
                 q = q - (deposit_weight(a, v2, wmu) - q) * em1;
             }
-            const double len = a.seg_len[off + s];
-            const double em1 = expm1(-chiv * len);
+            double e, em1;
+            exp_pair_tab(-chiv * len, tab, e, em1);
             if (mode == 0) {
                 acc -= q * em1;
             } else {
                 double I = a.Ient[lk];
                 for (int s2 = 0; s2 < s; ++s2) {
-                    const long v2 = seg_voxel(a, i0, j0, k, off + s2);
-                    const double em1b = expm1(-a.chi[v2] * a.seg_len[off + s2]);
+                    int A2, B2;
+                    double len2;
+                    L.get(a, s2, A2, B2, len2);
+                    const long v2 = plane + line_voxel(a, i0, j0, A2, B2);
+                    const double em1b = expm1_nonpos_tab(-a.chi[v2] * len2, tab);
                     I = I + (I - a.S[v2]) * em1b;
                 }
-                const double c = deposit_weight(a, v, wmu);
-                acc += len * (c * Sv + (c - q) * (I - Sv) * exp(-chiv * len));
+                const double c = cv * wmu;
+                acc += len * (c * Sv + (c - q) * (I - Sv) * e);
             }
         }
     }
-    out[v] = (mode == 0) ? acc / chiv : acc;
+    if (p0 < nxy) out[v] = (mode == 0) ? acc / chiv : acc;
 }
 
 struct AdjFinalArgs {
@@ -239,6 +306,7 @@ AdjLineArgs line_args(rt3d_ctx *c)
     a.Ient = c->adj_Ient; a.Qx = c->adj_Qx;
     a.g = c->adj_g;
     a.eps = c->eps;
+    a.xtab = c->xtab;
     return a;
 }
 
@@ -366,7 +434,7 @@ int rt3d_adjoint_emergent(rt3d_ctx *c, const double *g_em, double tol, int max_i
     const dim3 lgrid((nxy + kLineThreads - 1) / kLineThreads, c->A.n_dir);
     // a = dL/dS at fixed chi (the transport adjoint of the emergent light); f = a / chi
     la.nu = nullptr;
-    hipLaunchKernelGGL(adj_back_kernel, lgrid, dim3(kLineThreads), 0, c->stream, la);
+    hipLaunchKernelGGL(adj_back_kernel, dim3(lgrid.x, c->A.n_dir / 2), dim3(kLineThreads), 0, c->stream, la, 1);
     if ((rc = check_launch(c, "adj_back_kernel"))) return rc;
     hipLaunchKernelGGL(adj_pull_kernel, planes(c), dim3(kPlaneThreads), 0, c->stream, la, 0, c->adj_f);
     if ((rc = check_launch(c, "adj_pull_kernel"))) return rc;
@@ -417,7 +485,7 @@ int rt3d_adjoint_emergent(rt3d_ctx *c, const double *g_em, double tol, int max_i
     if (final_rel_out) *final_rel_out = rel;
     // the chi terms along the lines with the deposit weights (1 - eps) nu W|mu|, then both gradients
     la.nu = c->adj_nu;
-    hipLaunchKernelGGL(adj_back_kernel, lgrid, dim3(kLineThreads), 0, c->stream, la);
+    hipLaunchKernelGGL(adj_back_kernel, lgrid, dim3(kLineThreads), 0, c->stream, la, 0);
     if ((rc = check_launch(c, "adj_back_kernel"))) return rc;
     hipLaunchKernelGGL(adj_pull_kernel, planes(c), dim3(kPlaneThreads), 0, c->stream, la, 1, c->adj_pull);
     if ((rc = check_launch(c, "adj_pull_kernel"))) return rc;
