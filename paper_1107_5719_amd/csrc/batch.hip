@@ -83,7 +83,9 @@ struct PlaneBlock {
     int member, chunk, k, xcd;
 };
 
-constexpr int kAuxBlocks = 128;      // blocks per member of the grid-stride copy / combine kernels
+// blocks per member of the grid-stride copy / combine kernels (those of the Anderson mixing, 12 grids up to 97^3: 128, 256,
+// 512 and 1024 blocks 152, 101, 92 and 96 us)
+constexpr int kAuxBlocks = 512;
 
 __global__ void ctl_pre_kernel(int n, MemberState *st, const BatchParams *prm)
 {
@@ -313,9 +315,11 @@ __global__ void aa_store_kernel(const AaArgs *args, const MemberState *st, int o
     if (s.mode == 0) return;
     const AaArgs a = args[m];
     const int slot = output ? s.aa_slot[s.aa_count - 1] : s.aa_slot[s.aa_count];
-    double *dst = (output ? const_cast<double *>(a.G) : const_cast<double *>(a.X)) + long(slot) * a.V;
-    for (long v = long(blockIdx.x) * blockDim.x + threadIdx.x; v < a.V; v += long(gridDim.x) * blockDim.x)
-        dst[v] = a.J[v];
+    double *in = const_cast<double *>(a.F) + long(slot) * a.V;
+    for (long v = long(blockIdx.x) * blockDim.x + threadIdx.x; v < a.V; v += long(gridDim.x) * blockDim.x) {
+        if (output) aa_output_body(a, slot, v);
+        else in[v] = a.J[v];
+    }
 }
 
 // the window of member m as the single-problem mixing takes it
@@ -601,7 +605,7 @@ int build_tables(rt3d_batch *b)
         NgArgs &g = ng[i];
         g.V = c->V; g.order = c->ng_order; g.hist = c->ng_hist; g.work = c->ng_work; g.J = c->J;
         AaArgs &w = aa[i];
-        w.V = c->V; w.k = 0; w.X = c->aa_x; w.G = c->aa_g; w.work = c->aa_work; w.J = c->J;
+        w.V = c->V; w.k = 0; w.F = c->aa_x; w.G = c->aa_g; w.work = c->aa_work; w.J = c->J;
         sc[i] = MemberScalars{c->d_maxrel, c->d_maxdist, c->d_flag};
         if (c->plan.columns) {
             // the longest chains of segments first, as in a single problem

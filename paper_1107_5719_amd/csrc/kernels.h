@@ -1825,7 +1825,8 @@ __global__ __launch_bounds__(256) void ng_combine_kernel(NgArgs a, int m)
 
 // ------------------------------------------------------------------------------------------------
 // Anderson mixing of the outer iteration: windows of (input, output) pairs of the OS step in two rings
-// of V-vectors; slot[0..k] are the ring entries of the window, oldest first.  The weighted dot products
+// of V-vectors, the input x of a pair replaced by the step's change f = g - x once its output g is there
+// (the dot products read ten vectors then instead of eighteen); slot[0..k] are the ring entries of the window, oldest first.  The weighted dot products
 // use the fixed two-level partition of the Ng kernels (bitwise reproducible).
 // ------------------------------------------------------------------------------------------------
 
@@ -1841,7 +1842,7 @@ struct AaArgs {
     long V;
     int k;                          // differences in the window (1..kAaMaxDepth)
     int slot[kAaMaxDepth + 1];      // ring entries of the window, oldest first
-    const double *X, *G;            // rings [depth + 1][V] of inputs and outputs
+    const double *F, *G;            // rings [depth + 1][V] of changes (the newest: inputs) and outputs
     double *work;                   // [kAaWork]
     double *J;                      // receives the mixed input of the next step
 };
@@ -1849,6 +1850,47 @@ struct AaArgs {
 // Index of the sum A_ij (i <= j < k) and of b_i in a block's partial sums.
 __host__ __device__ constexpr int aa_a_index(int i, int j) { return j * (j + 1) / 2 + i; }
 __host__ __device__ constexpr int aa_b_index(int i) { return kAaMaxDepth * (kAaMaxDepth + 1) / 2 + i; }
+
+// The step's output J of voxel v joins the pair whose input is in the given slot
+__device__ inline void aa_output_body(const AaArgs &a, int slot, long v)
+{
+    const long o = long(slot) * a.V + v;
+    const double g = a.J[v];
+    const_cast<double *>(a.F)[o] = g - a.F[o];
+    const_cast<double *>(a.G)[o] = g;
+}
+
+__global__ __launch_bounds__(256) void aa_output_kernel(AaArgs a, int slot)
+{
+    const long v = long(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (v < a.V) aa_output_body(a, slot, v);
+}
+
+// The sums of x[0 .. N) over a wavefront, in the order of an xor tree from offs = 32 down: at each level a lane hands
+// half of its sums to its partner and takes over the other half, so N sums cost about N exchanges, not 6 N.
+// (Six exchanges for each of the 44 sums were most of the dot products' time: 65^3 17.8 and 7.3 us, a batch of 12 grids up
+// to 97^3 189 and 105 us, with the changes f stored instead of the inputs.)
+// On return x[0] is sum q where true is returned (six levels leave one sum per lane at most).
+template <int N>
+__device__ __forceinline__ bool wave_sums(double *x, int lane, int offs, int &q)
+{
+    if constexpr (N == 1) {
+        for (; offs > 0; offs >>= 1) x[0] += __shfl_xor(x[0], offs);
+        q = 0;
+        return true;
+    } else {
+        constexpr int M = (N + 1) / 2;
+        const bool hi = (lane & offs) != 0;
+#pragma unroll
+        for (int u = 0; u < M; ++u) {
+            const double a = x[u], b = u + M < N ? x[u + M] : 0.0;
+            x[u] = (hi ? b : a) + __shfl_xor(hi ? a : b, offs);
+        }
+        const bool held = wave_sums<M>(x, lane, offs >> 1, q);
+        q += hi ? M : 0;
+        return held && q < N;
+    }
+}
 
 // One block's share of A_ij = sum_v w df_i df_j and b_i = sum_v w df_i f_k, w = 1/g_k^2, f = g - x,
 // df_j = f_k - f_{k-j}; the sums of a thread, then of a wavefront (xor tree), then of the block's
@@ -1859,17 +1901,17 @@ __device__ inline void aa_dots_body(const AaArgs &a, int blk)
     double acc[kAaSums];
 #pragma unroll
     for (int q = 0; q < kAaSums; ++q) acc[q] = 0.0;
-    const double *gk = a.G + long(a.slot[k]) * a.V, *xk = a.X + long(a.slot[k]) * a.V;
+    const double *gk = a.G + long(a.slot[k]) * a.V, *fkp = a.F + long(a.slot[k]) * a.V;
     for (long v = long(blk) * kAaThreads + threadIdx.x; v < a.V; v += long(kAaBlocks) * kAaThreads) {
         const double g = gk[v];
         const double w = 1.0 / (g * g);
-        const double fk = g - xk[v];
+        const double fk = fkp[v];
         double df[kAaMaxDepth];
 #pragma unroll
         for (int j = 1; j <= kAaMaxDepth; ++j) {
             if (j > k) break;
             const long o = long(a.slot[k - j]) * a.V + v;
-            df[j - 1] = fk - (a.G[o] - a.X[o]);
+            df[j - 1] = fk - a.F[o];
         }
 #pragma unroll
         for (int j = 0; j < kAaMaxDepth; ++j) {
@@ -1879,13 +1921,11 @@ __device__ inline void aa_dots_body(const AaArgs &a, int blk)
             acc[aa_b_index(j)] += w * df[j] * fk;
         }
     }
-#pragma unroll
-    for (int q = 0; q < kAaSums; ++q)
-        for (int offs = 32; offs > 0; offs >>= 1) acc[q] += __shfl_xor(acc[q], offs);
     __shared__ double part[kAaThreads / 64][kAaSums];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0)
-        for (int q = 0; q < kAaSums; ++q) part[wid][q] = acc[q];
+    int q;
+    const bool held = wave_sums<kAaSums>(acc, lane, 32, q);
+    if (held) part[wid][q] = acc[0];
     __syncthreads();
     if (threadIdx.x < kAaSums) {
         double s = part[0][threadIdx.x];
@@ -1896,50 +1936,79 @@ __device__ inline void aa_dots_body(const AaArgs &a, int blk)
 
 __global__ __launch_bounds__(kAaThreads) void aa_dots_kernel(AaArgs a) { aa_dots_body(a, blockIdx.x); }
 
-// Sums the block partials in a fixed order, then thread 0 solves the k x k normal equations A gamma = b
-// by Gaussian elimination with partial pivoting; a singular system or a non-finite solution clears the
-// valid flag (the output g_k is then kept as the next input).  Whole block.
+// Sums the block partials in a fixed order (five runs of blocks, each in order, then the runs), then solves
+// the k x k normal equations A gamma = b by Gaussian elimination with partial pivoting, a thread per entry; a
+// singular system or a non-finite solution clears the valid flag (the output g_k is then kept as the next
+// input).  Whole block.  us with one thread per sum over all blocks and one for the elimination, and so:
+// 20 and 8 on average over the windows of a solve, 59 and 12 for a batch of 12 grids.
 __device__ inline void aa_solve_body(const AaArgs &a)
 {
+    constexpr int R = kAaThreads / kAaSums, per = (kAaBlocks + R - 1) / R, U = 16;
+    constexpr int N = kAaMaxDepth, W = N + 1;
+    __shared__ double run[R][kAaSums];
     __shared__ double tot[kAaSums];
-    if (threadIdx.x < kAaSums) {
+    __shared__ double A[N][W];          // column N: b
+    const int tid = int(threadIdx.x);
+    if (tid < R * kAaSums) {
+        const int r = tid / kAaSums, q = tid - r * kAaSums, b1 = min(kAaBlocks, (r + 1) * per);
         double s = 0.0;
-        for (int b = 0; b < kAaBlocks; ++b) s += a.work[b * kAaSums + threadIdx.x];
-        tot[threadIdx.x] = s;
-        a.work[kAaSumOff + threadIdx.x] = s;
+        for (int b = r * per; b < b1; b += U) {
+            double x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = a.work[min(b + u, b1 - 1) * kAaSums + q];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += b + u < b1 ? x[u] : 0.0;
+        }
+        run[r][q] = s;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    const int n = a.k;
-    double A[kAaMaxDepth][kAaMaxDepth], b[kAaMaxDepth], g[kAaMaxDepth];
-    for (int i = 0; i < n; ++i) {
-        b[i] = tot[aa_b_index(i)];
-        g[i] = 0.0;
-        for (int j = 0; j < n; ++j) A[i][j] = i <= j ? tot[aa_a_index(i, j)] : tot[aa_a_index(j, i)];
+    if (tid < kAaSums) {
+        double s = run[0][tid];
+        for (int r = 1; r < R; ++r) s += run[r][tid];
+        tot[tid] = s;
+        a.work[kAaSumOff + tid] = s;
     }
+    __syncthreads();
+    const int n = a.k, i = tid / W, j = tid - i * W;      // this thread's entry
+    const bool mine = i < n && (j < n || j == N);
+    if (mine) A[i][j] = j == N ? tot[aa_b_index(i)] : i <= j ? tot[aa_a_index(i, j)] : tot[aa_a_index(j, i)];
+    __syncthreads();
     bool ok = true;
-    for (int c = 0; c < n && ok; ++c) {
+    for (int c = 0; c < n; ++c) {
         int p = c;
-        for (int r = c + 1; r < n; ++r) if (fabs(A[r][c]) > fabs(A[p][c])) p = r;
-        if (!(fabs(A[p][c]) > 0.0)) { ok = false; break; }
-        if (p != c) {
-            for (int q = 0; q < n; ++q) { const double t = A[c][q]; A[c][q] = A[p][q]; A[p][q] = t; }
-            const double t = b[c]; b[c] = b[p]; b[p] = t;
+        for (int r = c + 1; r < n; ++r)
+            if (fabs(A[r][c]) > fabs(A[p][c])) p = r;
+        if (!(fabs(A[p][c]) > 0.0)) {
+            ok = false;
+            break;
         }
-        for (int r = c + 1; r < n; ++r) {
-            const double f = A[r][c] / A[c][c];
-            for (int q = c; q < n; ++q) A[r][q] -= f * A[c][q];
-            b[r] -= f * b[c];
+        // rows c and p change places, then every row below loses its multiple of row c
+        const int src = i == c ? p : i == p ? c : i;
+        double x = 0.0;
+        if (mine) {
+            x = A[src][j];
+            if (i > c && j >= c) x -= A[src][c] / A[p][c] * A[p][j];
         }
+        __syncthreads();
+        if (mine) A[i][j] = x;
+        __syncthreads();
     }
-    for (int r = n - 1; r >= 0 && ok; --r) {
-        double t = b[r];
-        for (int q = r + 1; q < n; ++q) t -= A[r][q] * g[q];
+    if (tid != 0) return;
+    double g[N];
+    for (int r = 0; r < N; ++r) g[r] = 0.0;
+#pragma unroll
+    for (int r = N - 1; r >= 0; --r) {
+        if (r >= n || !ok) continue;
+        double t = A[r][N];
+#pragma unroll
+        for (int q = r + 1; q < N; ++q)
+            if (q < n) t -= A[r][q] * g[q];
         g[r] = t / A[r][r];
         if (!isfinite(g[r])) ok = false;
     }
-    for (int i = 0; i < kAaMaxDepth; ++i) a.work[kAaCoefOff + i] = i < n ? g[i] : 0.0;
-    a.work[kAaCoefOff + kAaMaxDepth] = ok ? 1.0 : 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) a.work[kAaCoefOff + q] = q < n ? g[q] : 0.0;
+    a.work[kAaCoefOff + N] = ok ? 1.0 : 0.0;
 }
 
 __global__ __launch_bounds__(kAaThreads) void aa_solve_kernel(AaArgs a) { aa_solve_body(a); }
@@ -1950,8 +2019,15 @@ __device__ inline void aa_combine_body(const AaArgs &a, long v)
     const double *cf = a.work + kAaCoefOff;
     const double gk = a.G[long(a.slot[a.k]) * a.V + v];
     double x = gk;
-    if (cf[kAaMaxDepth] != 0.0)
-        for (int j = 1; j <= a.k; ++j) x -= cf[j - 1] * (gk - a.G[long(a.slot[a.k - j]) * a.V + v]);
+    if (cf[kAaMaxDepth] != 0.0) {
+        // all loads before the sums
+        double g[kAaMaxDepth];
+#pragma unroll
+        for (int j = 1; j <= kAaMaxDepth; ++j) g[j - 1] = a.G[long(a.slot[max(a.k - j, 0)]) * a.V + v];
+#pragma unroll
+        for (int j = 1; j <= kAaMaxDepth; ++j)
+            if (j <= a.k) x -= cf[j - 1] * (gk - g[j - 1]);
+    }
     a.J[v] = x;
 }
 

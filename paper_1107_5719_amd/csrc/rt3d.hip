@@ -432,7 +432,7 @@ int anderson_step(rt3d_ctx *c, int k, const int *slots)
     a.V = c->V;
     a.k = k;
     for (int q = 0; q <= k; ++q) a.slot[q] = slots[q];
-    a.X = c->aa_x;
+    a.F = c->aa_x;
     a.G = c->aa_g;
     a.work = c->aa_work;
     a.J = c->J;
@@ -1006,8 +1006,11 @@ int rt3d_solve_to_convergence(rt3d_ctx *c, double tol, int max_iter, int inner_s
         ++n;
         if (rc != RT3D_OK) break;
         if (c->aa_depth > 0) {
-            HIP_TRY(c, hipMemcpyAsync(c->aa_g + long(aa_slots[aa_count]) * c->V, c->J, vbytes,
-                                      hipMemcpyDeviceToDevice, c->stream), "anderson output");
+            AaArgs pair{};
+            pair.V = c->V; pair.F = c->aa_x; pair.G = c->aa_g; pair.J = c->J;
+            hipLaunchKernelGGL(aa_output_kernel, dim3(unsigned((c->V + 255) / 256)), dim3(256), 0, c->stream, pair,
+                               aa_slots[aa_count]);
+            if ((rc = check_launch(c, "aa_output_kernel"))) return rc;
             ++aa_count;
             // FP32 form: an anchored step starts the window afresh from its own pair; the earlier
             // pairs' outputs carry float32 rounding relative to the previous anchor
