@@ -496,7 +496,7 @@ int build_lstar_batched(rt3d_batch *b)
     int n_tile = 0, threads = 64;
     size_t lds = 0;
     for (int q : order) {
-        if (!args[q].T) continue;
+        if (args[q].tx == 0) continue;
         for (int k = 0; k < args[q].nz; ++k)
             for (int ch = 0; ch < lstar_tile_blocks(args[q]); ++ch) blocks.push_back(PlaneBlock{q, ch, k, 0});
         threads = std::max(threads, lstar_tile_threads(args[q]));
@@ -504,7 +504,7 @@ int build_lstar_batched(rt3d_batch *b)
         n_tile = int(blocks.size());
     }
     for (int q : order) {
-        if (args[q].T) continue;
+        if (args[q].tx > 0) continue;
         const int chunks = (args[q].nx * args[q].ny + kLstarThreads - 1) / kLstarThreads;
         for (int k = 0; k < args[q].nz; ++k)
             for (int ch = 0; ch < chunks; ++ch) blocks.push_back(PlaneBlock{q, ch, k, 0});
@@ -522,11 +522,11 @@ int build_lstar_batched(rt3d_batch *b)
     } else {
         if (n_tile > 0)
             hipLaunchKernelGGL(lstar_tile_kernel_batch, dim3(unsigned(n_tile)), dim3(threads), lds, b->stream, d_args, d_blocks);
-        for (const LstarArgs &a : args)
-            if (a.T) launch_lstar_fold(a, b->stream);
         if (int(blocks.size()) > n_tile)
             hipLaunchKernelGGL(lstar_kernel_batch, dim3(unsigned(blocks.size()) - n_tile), dim3(kLstarThreads), 0, b->stream,
                                d_args, d_blocks + n_tile);
+        for (const LstarArgs &a : args)
+            if (a.T) launch_lstar_fold(a, b->stream);
         rc = launch_check(b, "lstar_kernel_batch");
         if (!rc && hipStreamSynchronize(b->stream) != hipSuccess) rc = bfail(b, RT3D_ERR_HIP, "sync (Lambda*)");
     }

@@ -807,8 +807,8 @@ struct LstarArgs {
     const double *seg_len;
     const double *chi;
     double *L;                      // [27][V]
-    double *T;                      // [18][V] scratch of the tiled form (null: not taken)
-    int tx, ty;                     // its tile
+    double *T;                      // [18][V] scratch for the sums of the downward pairs (null: all pairs into L)
+    int tx, ty;                     // tile of the tiled form (0: not taken)
     const double *xtab;             // [kExpTab] 2^(j/kExpTab), the float64 exponential's table
 };
 
@@ -851,6 +851,8 @@ __device__ inline int wrap_small(int a, int n)
 // runs (all of one vertical direction, then all of the other; the plan checks this).  So a thread
 // keeps 18 accumulators, its own layer's 9 and those of the run's other layer, which are stored and
 // cleared between the runs: every entry sums the same terms in the same order as with 27.
+// With a.T only the downward pairs are walked, chi_v times their part goes there and the rest follows by symmetry
+// (see lstar_tile_body, which grids that cannot wrap take instead): half the time.
 constexpr int kLstarThreads = 64;
 // Columns p (p = j nx + i; p >= nx ny: none) of plane k; the whole block calls this.
 __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
@@ -880,13 +882,14 @@ __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
     bool stored_up = false, stored_down = false;    // the layers k - 1 and k + 1 have been written
     for (int q = 0; q < a.n_pair; ++q) {
         const rt3d::PairInfo pi = a.pairs[q];
-        if (pi.down != run_down) {
+        if (a.T && !pi.down) continue;
+        if (pi.down != run_down && !a.T) {
             store_other(run_down);
             stored_down = stored_down || run_down;
             stored_up = stored_up || !run_down;
             run_down = pi.down;
         }
-        const double fac = pi.wmu / chiv;
+        const double fac = a.T ? pi.wmu : pi.wmu / chiv;
         const int d = pi.dA;
         const int dk = d * nz + k;
         const int off = a.seg_off[dk], n = a.seg_n[dk];
@@ -931,6 +934,11 @@ __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
                 prodB *= eB;
             }
         }
+    }
+    if (a.T) {
+        if (valid)
+            for (int o = 0; o < 18; ++o) a.T[o * V + v] = acc[o][threadIdx.x];
+        return;
     }
     store_other(run_down);
     stored_down = stored_down || run_down;
@@ -1101,7 +1109,7 @@ __global__ __launch_bounds__(kLstarTileThreads) __attribute__((amdgpu_waves_per_
     lstar_tile_body(a, blockIdx.x, blockIdx.y, lstar_ring);
 }
 
-// Lambda* from the tiled form's sums: T[0, 9) of the voxel's layer, T[9, 18) of the layer above
+// Lambda* from the downward pairs' sums: T[0, 9) of the voxel's layer, T[9, 18) of the layer above
 __global__ __launch_bounds__(kPlaneThreads) void lstar_fold_kernel(LstarArgs a)
 {
     const int nx = a.nx, ny = a.ny, k = blockIdx.y, p = int(blockIdx.x) * kPlaneThreads + int(threadIdx.x);
@@ -1152,14 +1160,14 @@ inline void lstar_args(Ctx *c, LstarArgs &a)
     a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
     a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.chi = c->chi; a.L = c->L;
     a.xtab = c->xtab;
-    // the tiled form's 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use
-    if (a.early_exit && c->plan.p_elems >= 18 * c->V) {
+    // the 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use
+    if (c->plan.p_elems >= 18 * c->V) {
         a.T = static_cast<double *>(c->P);
-        lstar_tile(a.nx, a.ny, a.tx, a.ty);
+        if (a.early_exit) lstar_tile(a.nx, a.ny, a.tx, a.ty);
     }
 }
 
-// Launches the fold of the tiled form's sums into Lambda*
+// Launches the fold of the downward pairs' sums into Lambda*
 inline void launch_lstar_fold(const LstarArgs &a, hipStream_t stream)
 {
     hipLaunchKernelGGL(lstar_fold_kernel, dim3((a.nx * a.ny + kPlaneThreads - 1) / kPlaneThreads, a.nz), dim3(kPlaneThreads), 0,

@@ -289,14 +289,14 @@ int ensure_lstar(rt3d_ctx *c)
     lstar_args(c, a);
     {
         TimedLaunch t(c, K_LSTAR);
-        if (a.T) {
+        if (a.tx > 0) {
             hipLaunchKernelGGL(lstar_tile_kernel, dim3(lstar_tile_blocks(a), a.nz), dim3(lstar_tile_threads(a)), lstar_tile_lds(a),
                                c->stream, a);
-            launch_lstar_fold(a, c->stream);
         } else {
             const dim3 grid((c->g.nx * c->g.ny + kLstarThreads - 1) / kLstarThreads, c->g.nz);
             hipLaunchKernelGGL(lstar_kernel, grid, dim3(kLstarThreads), 0, c->stream, a);
         }
+        if (a.T) launch_lstar_fold(a, c->stream);
     }
     int rc = check_launch(c, "lstar_kernel");
     if (rc) return rc;
