@@ -27,7 +27,7 @@ HBM_PEAK_GBS = 8000.0
 # MI355X vector issue: 256 CUs x 4 SIMDs x 2.4 GHz; float64 16 lanes per SIMD and cycle (78.6 TFLOP/s
 # counting an FMA as 2 flops, i.e. 39.3e12 lane-instructions/s), float32 32 lanes (78.6e12)
 VALU_ISSUE_PEAK = {"fp64": 39.3e12, "fp32": 78.6e12}
-SWEEP_KERNEL = {"fp64": "sweep_kernel<double,512,2>", "fp32": "sweep_kernel<float,512,2>"}
+SWEEP_KERNEL = {"fp64": "column_sweep_kernel<double>", "fp32": "column_sweep_kernel<float>"}
 JACOBI_KERNEL = {"fp64": "jacobi_kernel_column<double,4>", "fp32": "jacobi_kernel_column<float,4>"}
 # the (M, Ng order, Ng every) schedules over which time to converged J is summarised (median, worst)
 SCHEDULES = [(12, 3, 6), (20, 3, 6), (30, 3, 6), (40, 3, 6), (12, 3, 8), (20, 3, 8), (30, 3, 8), (40, 3, 8)]
@@ -58,8 +58,10 @@ def jacobi_bytes_per_voxel(coef: str) -> int:
 def _kernel_sha() -> str:
     import hashlib
 
-    src = os.path.join(ROOT, "paper_1107_5719_amd", "csrc", "kernels.h")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for src in ("kernels.h", "sweep_columns.h"):
+        h.update(open(os.path.join(ROOT, "paper_1107_5719_amd", "csrc", src), "rb").read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(kernel: str):
