@@ -344,6 +344,7 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
     sa.scatter_only = 1;
     sa.chi = c->chi; sa.eps = c->eps; sa.B = c->B; sa.J = c->adj_nu;
     sa.cs = c->cs;
+    sa.clear = c->d_scal;
     hipLaunchKernelGGL(source_kernel<double>, planes(c), dim3(kPlaneThreads), 0, c->stream, sa);
     int rc = check_launch(c, "source_kernel (adjoint)");
     if (rc) return rc;
@@ -366,7 +367,6 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
     ra.J = c->adj_nu; ra.base = c->adj_f; ra.Jfs = c->adj_fs; ra.rb = c->adj_r;
     launch_reduce_kernel(ra, c->plan.columns, false, c->stream);
     if ((rc = check_launch(c, "reduce_kernel_pair (adjoint)"))) return rc;
-    HIP_TRY(c, hipMemsetAsync(c->d_scal, 0, kScalarBytes, c->stream), "memset");
     const double *in = nullptr;
     double *bufs[2] = {c->dJa, c->dJb};
     for (int m = 0, n = 0; m < M; m += n) {
@@ -388,8 +388,8 @@ int adjoint_os_step(rt3d_ctx *c, int M, double *dmax, double *numax, int *bad)
         if ((rc = check_launch(c, "jacobi_kernel (adjoint)"))) return rc;
         in = ja.w_out;
     }
-    unsigned long long scal[3] = {0, 0, 0};
-    HIP_TRY(c, hipMemcpyAsync(scal, c->d_scal, kScalarBytes, hipMemcpyDeviceToHost, c->stream), "scalars");
+    const unsigned long long *scal = c->h_scal;
+    HIP_TRY(c, hipMemcpyAsync(c->h_scal, c->d_scal, kScalarBytes, hipMemcpyDeviceToHost, c->stream), "scalars");
     rc = sync(c);
     if (rc) return rc;
     const unsigned long long b1 = scal[0], b2 = scal[1];

@@ -193,12 +193,14 @@ struct SourceArgs {
     int scatter_only;
     const double *chi, *eps, *B, *J, *S_given, *Ja;
     void *cs;                     // Vec2<real>
+    unsigned long long *clear;    // the step's three scalars, set to 0 (may be null); spares a memset launch
 };
 
 template <typename real>
 __device__ inline void source_body(const SourceArgs &a, int p, int k)
 {
     if (p >= a.nx * a.ny) return;
+    if (a.clear && k == 0 && p < 3) a.clear[p] = 0;
     const long v = long(k) * a.nx * a.ny + p;
     double S;
     if (a.S_given) S = a.S_given[v];

@@ -202,6 +202,7 @@ int launch_source(rt3d_ctx *c, const double *S_given, const double *Ja, bool fp3
     a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz;
     a.chi = c->chi; a.eps = c->eps; a.B = c->B; a.J = c->J; a.S_given = S_given; a.Ja = Ja;
     a.cs = c->cs;
+    a.clear = c->d_scal;
     TimedLaunch t(c, K_SOURCE);
     if (!fp32)
         hipLaunchKernelGGL(source_kernel<double>, plane_grid(c), dim3(kPlaneThreads), 0, c->stream, a);
@@ -457,6 +458,7 @@ void free_all(rt3d_ctx *c)
                     c->adj_f, c->adj_pull, c->adj_g, c->adj_qs};
     for (void *p : ptrs)
         if (p) hipFree(p);
+    if (c->h_scal) hipHostFree(c->h_scal);
     for (auto &p : c->pending) {
         hipEventDestroy(p.a);
         hipEventDestroy(p.b);
@@ -650,6 +652,10 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
         chk(dev_alloc(c, &c->Iem_a, size_t(c->A.n_dir / 2) * g->nx * g->ny));
     }
     chk(dev_alloc(c, &c->d_scal, kScalarBytes / sizeof(unsigned long long)));
+    if (!rc && hipHostMalloc(reinterpret_cast<void **>(&c->h_scal), kScalarBytes, hipHostMallocDefault) != hipSuccess) {
+        c->h_scal = nullptr;
+        rc = fail(c, RT3D_ERR_OOM, "hipHostMalloc");
+    }
     if (!rc) {
         c->d_maxrel = c->d_scal;
         c->d_maxdist = c->d_scal + 1;
@@ -790,9 +796,10 @@ int rt3d_set_medium(rt3d_ctx *c, const double *chi, const double *eps, const dou
                            c->dJa, c->dJb, c->Sbuf, c->d_flag);
         int rc = check_launch(c, "check_medium_kernel");
         if (rc) return rc;
-        int flag = 0;
-        HIP_TRY(c, hipMemcpyAsync(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream), "flag");
+        HIP_TRY(c, hipMemcpyAsync(c->h_scal, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream), "flag");
         HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+        int flag = 0;
+        std::memcpy(&flag, c->h_scal, sizeof(flag));
         if (flag) return fail(c, RT3D_ERR_ARG, "device medium: chi must be finite > 0, eps in (0,1], B finite");
     }
     std::swap(c->chi, c->dJa);
@@ -837,15 +844,16 @@ int rt3d_set_J(rt3d_ctx *c, const double *J, int ptr_kind)
     hipLaunchKernelGGL(check_finite_kernel, dim3((V + 255) / 256), dim3(256), 0, c->stream, V, c->dJa, c->d_flag);
     int rc = check_launch(c, "check_finite_kernel");
     if (rc) return rc;
+    HIP_TRY(c, hipMemcpyAsync(c->h_scal, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream), "flag");
+    if ((rc = sync(c))) return rc;
     int flag = 0;
-    HIP_TRY(c, hipMemcpyAsync(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream), "flag");
-    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+    std::memcpy(&flag, c->h_scal, sizeof(flag));
     if (flag) return fail(c, RT3D_ERR_ARG, "J must be finite");
     std::swap(c->J, c->dJa);
     c->anchor_valid = false;
     c->c_last = INFINITY;
     c->history.clear();
-    return sync(c);
+    return RT3D_OK;
 }
 
 int rt3d_get_J(rt3d_ctx *c, double *J_out, int ptr_kind)
@@ -918,8 +926,7 @@ int rt3d_os_step(rt3d_ctx *c, int inner_sweeps, double *max_rel_dJ_out)
         rc = run_fs(c, nullptr, true, false);
     }
     if (rc) return rc;
-    // the three convergence scalars share one allocation: one clear, one read-back per step
-    HIP_TRY(c, hipMemsetAsync(c->d_scal, 0, kScalarBytes, c->stream), "memset");
+    // the three convergence scalars share one allocation: one clear (by the source kernel), one read-back per step
     if (c->os_method == RT3D_OS_GAUSS_SEIDEL) {
         rc = gauss_seidel_sweeps(c, inner_sweeps);
         if (rc) return rc;
@@ -944,8 +951,8 @@ int rt3d_os_step(rt3d_ctx *c, int inner_sweeps, double *max_rel_dJ_out)
             in = out;
         }
     }
-    unsigned long long scal[3] = {0, 0, 0};
-    HIP_TRY(c, hipMemcpyAsync(scal, c->d_scal, kScalarBytes, hipMemcpyDeviceToHost, c->stream), "scalars");
+    const unsigned long long *scal = c->h_scal;
+    HIP_TRY(c, hipMemcpyAsync(c->h_scal, c->d_scal, kScalarBytes, hipMemcpyDeviceToHost, c->stream), "scalars");
     rc = sync(c);
     if (rc) return rc;
     const unsigned long long bits = scal[0], dbits = scal[1];
