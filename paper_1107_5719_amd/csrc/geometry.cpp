@@ -202,6 +202,35 @@ static void sort_work(std::vector<std::pair<double, WorkItem>> &work, SweepPlan 
     for (auto &w : work) P.items.push_back(w.second);
 }
 
+namespace {
+
+// The pairs' segments in sweep order, with what follows each (the rows that a band touches are the column
+// plan's to add)
+void append_column_segments(SweepPlan &P)
+{
+    P.cseg.clear();
+    for (PairInfo &pi : P.pairs) {
+        pi.c_off = int(P.cseg.size());
+        int prev_i = 0, prev_j = 0;
+        for (int st = 0; st < P.nz; ++st) {
+            const size_t ka = size_t(pi.dA) * P.nz + (pi.down ? P.nz - 1 - st : st);
+            const int o = P.seg_off[ka], n = P.seg_n[ka];
+            for (int s = o; s < o + n; ++s) {
+                if (st > 0 || s > o) {
+                    if (P.seg_ai[s] != prev_i) P.cseg.back().flags |= kNextColumn;
+                    if (P.seg_bi[s] != prev_j) P.cseg.back().flags |= kNextRow;
+                }
+                P.cseg.push_back(ColumnSeg{P.seg_len[s], s + 1 == o + n ? kLayerEnd : 0, 0});
+                prev_i = P.seg_ai[s];
+                prev_j = P.seg_bi[s];
+            }
+        }
+        pi.n_seg = int(P.cseg.size()) - pi.c_off;
+    }
+}
+
+}  // namespace
+
 bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
                       size_t lds_bytes_max, SweepPlan &P, std::string &err)
 {
@@ -370,6 +399,7 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
     }
     P.p_elems = off;
     sort_work(work, P);
+    append_column_segments(P);
     return true;
 }
 
@@ -428,7 +458,6 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
     SweepPlan P = plan;
     const int nx = P.nx, ny = P.ny, nz = P.nz;
     P.columns = true;
-    P.cseg.clear();
     P.pseg.clear();
     P.player.clear();
     P.blocks.assign(size_t(P.n_pair) * nz, LayerBlock{});
@@ -454,36 +483,25 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
         pi.n_bands = (ny + kColumnRows - 1) / kColumnRows;
         pi.last_rows = ny - (pi.n_bands - 1) * kColumnRows;
         pi.inv_rows = 1.0f / float(kColumnRows);
-        pi.c_off = int(P.cseg.size());
-        pi.n_seg = n_seg;
         pi.win_rows = 0;
         int64_t block = 0;
-        int prev_i = 0, prev_j = 0;
-        size_t prev_end = 0;                   // the last segment of the layer before
+        size_t end = size_t(pi.c_off);         // end of the layer in the segment list
         for (int st = 0; st < nz; ++st) {
             const int k = pi.down ? nz - 1 - st : st;
             const size_t ka = size_t(pi.dA) * nz + k;
             const int o = P.seg_off[ka], n = P.seg_n[ka];
             int jmin = P.seg_bi[o], jmax = jmin;
             for (int s = 0; s < n; ++s) {
-                const int i = P.seg_ai[o + s], j = P.seg_bi[o + s];
+                const int j = P.seg_bi[o + s];
                 jmin = std::min(jmin, j);
                 jmax = std::max(jmax, j);
-                if (st == 0 && s == 0) {
-                    pi.row0 = pos_mod(j, ny);
-                } else {
-                    if (i != prev_i) P.cseg.back().flags |= kNextColumn;
-                    if (j != prev_j) P.cseg.back().flags |= kNextRow;
-                }
-                P.cseg.push_back(ColumnSeg{P.seg_len[o + s], s + 1 == n ? kLayerEnd : 0, 0});
-                prev_i = i;
-                prev_j = j;
+                if (st == 0 && s == 0) pi.row0 = pos_mod(j, ny);
                 pi.sa_last = P.seg_a[o + s];
             }
             const int cover = rows + jmax - jmin;
             if (st == 0) pi.cover0 = cover;
-            else P.cseg[prev_end].cover = cover;
-            prev_end = P.cseg.size() - 1;
+            else P.cseg[end - 1].cover = cover;
+            end += size_t(n);
             pi.win_rows = std::max(pi.win_rows, cover);
             P.blocks[size_t(k) * P.n_pair + p] =
                 LayerBlock{off + block, pi.wmu, P.row_min[ka], jmax - jmin, 0,

@@ -807,6 +807,7 @@ struct LstarArgs {
     const rt3d::PairInfo *pairs;    // x-mirrored direction pairs (the tables of direction dA are read)
     const int *seg_off, *seg_n, *seg_ai, *seg_bi;
     const double *seg_len;
+    const rt3d::ColumnSeg *cseg;    // the pairs' segments in sweep order, with what follows each
     const double *chi;
     double *L;                      // [27][V]
     double *T;                      // [18][V] scratch for the sums of the downward pairs (null: all pairs into L)
@@ -966,11 +967,13 @@ __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
 // the y drift follow each other, and of a pair P is the line that drifts to larger x, M the other, so
 // the neighbour that a step reaches is known but for which axes it has crossed: 12 sums in registers.
 // What bounds it: float64 arithmetic, one exponential (about 30 instructions) and one self term per voxel
-// and segment index.  us before (a walk per thread, each step with two exponentials and gathers of its own,
-// both vertical directions) and now, with the fold: 17^3 x 64 222 and 78, 65^3 x 256 1936 and 584, 129^3 x 256
-// 10950 and 3800, the benchmark batch of 12 grids up to 97^3 6845 and 2700.  Workgroups of up to 512, 768 or 1024
-// threads, with less halo, wait longer at their barriers (65^3 x 256: 790, 980 and 790 us against 561 for the sums
-// alone), smaller ones have more halo (192: 678, 128: 687); two segments per barrier 583.
+// and segment index, and beside it the scalar unit (the walk's branches and addresses; a segment is one 16-byte
+// scalar load: with three loads and the crossings worked out here 561 us at 65^3 x 256 against 495).  us before (a walk
+// per thread, each step with two exponentials and gathers of its own, both vertical directions) and now, with the
+// fold: 17^3 x 64 222 and 75, 65^3 x 256 1936 and 517, 129^3 x 256 10950 and 3350, the benchmark batch of 12 grids up to
+// 97^3 6845 and 2280.  Workgroups of up to 512, 768 or 1024 threads, with less halo, waited longer at their barriers
+// (65^3 x 256: 790, 980 and 790 us against 561 at 256), smaller ones had more halo (192: 678, 128: 687); two segments per
+// barrier 583.
 constexpr int kLstarTileThreads = 256;
 // acc += x y on a tied operand: in the cases of a switch the compiler would copy all sums to merge the paths
 __device__ __forceinline__ void fma_to(double &acc, double x, double y)
@@ -1024,26 +1027,29 @@ __device__ inline void lstar_tile_body(const LstarArgs &a, int tile, int k, doub
             if (!scalar_int(&pi->down) || (scalar_int(&pi->ysgn) < 0) != (cls == 1)) continue;
             const int dk = scalar_int(&pi->dA) * nz + k;
             const double wmu = scalar_len(&pi->wmu);
-            const int off = scalar_int(a.seg_off + dk), n = scalar_int(a.seg_n + dk);
-            const int nu = k + 1 < nz ? scalar_int(a.seg_n + dk + 1) : 0, m = min(nu, 3);
-            const int offu = k + 1 < nz ? scalar_int(a.seg_off + dk + 1) + nu - m : 0;
-            // axes crossed on coming into each of the last three segments
-            int b1 = 0, b2 = 0, b3 = 0, ai = 0, bi = 0, an, bn;
-            auto crossed = [&]() {
+            const int n = scalar_int(a.seg_n + dk), m = k + 1 < nz ? min(scalar_int(a.seg_n + dk + 1), 3) : 0;
+            // the pair's list in sweep order, from the last m segments of the layer above on
+            const int before = scalar_int(&pi->n_seg) - n - (scalar_int(a.seg_off + dk) - scalar_int(a.seg_off + dk - k));
+            const rt3d::ColumnSeg *sp = a.cseg + (scalar_int(&pi->c_off) + before - m);
+            // axes crossed on coming into each of the last three segments: the flags of the one before each
+            int b1 = 0, b2 = 0, b3 = 0, flags = 0;
+            auto advance = [&](double &len) {
+                typedef int v4i __attribute__((ext_vector_type(4)));
+                const v4i w = *(const __attribute__((address_space(4))) v4i *)(uintptr_t)sp;
+                ++sp;
                 b3 = b2;
                 b2 = b1;
-                b1 = (an != ai ? 1 : 0) | (bn != bi ? 2 : 0);
-                ai = an;
-                bi = bn;
+                b1 = flags;
+                flags = w.z;
+                len = __hiloint2double(w.y, w.x);
             };
+            double len;
             __syncthreads();
 #pragma unroll 1
             for (int t = 0; t < m; ++t) {
+                advance(len);
                 double e, em1;
-                exp_pair_tab(-chiu * scalar_len(a.seg_len + offu + t), xtab, e, em1);
-                an = scalar_int(a.seg_ai + offu + t);
-                bn = scalar_int(a.seg_bi + offu + t);
-                crossed();
+                exp_pair_tab(-chiu * len, xtab, e, em1);
                 ring[t * E + q] = make_double2(e, em1);
             }
             // the sums of segment t of the layer, whose optical depth and e^-x - 1 are x and em1
@@ -1068,14 +1074,10 @@ __device__ inline void lstar_tile_body(const LstarArgs &a, int tile, int k, doub
             };
 #pragma unroll 1
             for (int t = m; t < m + n; ++t) {
-                const int idx = off + t - m;
-                const double x = chiv * scalar_len(a.seg_len + idx);
+                advance(len);
+                const double x = chiv * len;
                 double e, em1;
                 exp_pair_tab(-x, xtab, e, em1);
-                an = scalar_int(a.seg_ai + idx);
-                bn = scalar_int(a.seg_bi + idx);
-                crossed();
-                if (t == m) b1 |= 4;
                 // after the barrier no thread reads segment t - 4 any more, whose place this one takes
                 __syncthreads();
                 ring[(t & 3) * E + q] = make_double2(e, em1);
@@ -1160,7 +1162,7 @@ inline void lstar_args(Ctx *c, LstarArgs &a)
     a.nx = c->g.nx; a.ny = c->g.ny; a.nz = c->g.nz; a.n_pair = c->plan.n_pair;
     a.early_exit = c->lstar_early_exit;
     a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
-    a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.chi = c->chi; a.L = c->L;
+    a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.cseg = c->cseg; a.chi = c->chi; a.L = c->L;
     a.xtab = c->xtab;
     // the 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use
     if (c->plan.p_elems >= 18 * c->V) {

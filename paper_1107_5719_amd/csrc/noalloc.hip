@@ -115,6 +115,7 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     // ranges of pairs whose partial planes fit what the tables leave of the workspace; 0 where one pair's do
     // not
     auto ranges = [&]() {
+        if (!plan.columns) plan.cseg.clear();          // (not read by the window form)
         fixed = align256(tab.size() * sizeof(double)) + align256(size_t(V) * sizeof(double2)) +
                 align256(plan.pairs.size() * sizeof(rt3d::PairInfo)) +
                 align256(plan.player.size() * sizeof(rt3d::PairLayer)) +
