@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 #include <numeric>
 
 namespace rt3d {
@@ -272,6 +273,8 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
                 P.seg_ai.push_back(L.di[s]);
                 P.seg_bi.push_back(L.dj[s]);
                 P.seg_len.push_back(L.len[s]);
+                // heights of crossings are rounded to a few eps nz
+                P.slivers = P.slivers || L.len[s] * std::fabs(A.mu[d]) < 64.0 * std::numeric_limits<double>::epsilon() * nz;
             }
             nseg += n;
         }

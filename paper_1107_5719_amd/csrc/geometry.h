@@ -131,6 +131,9 @@ struct SweepPlan {
     int col_rows = 0;                     // most rows per thread of any pair
     int block_threads = 0;                // threads of a workgroup
     std::vector<ColumnSeg> cseg;
+    // a segment so short that rounding made it (a line through voxel edges: n_phi = 4, 12, 20, ... and about 1000
+    // layers or more).  Opposite directions need not share it, and it may lie in the voxel of its neighbour.
+    bool slivers = false;
     std::vector<WorkItem> items;          // in dispatch order (most expensive first)
     int64_t p_elems = 0;                  // size of the partial-plane buffer P in elements
     int max_win_rows = 0;

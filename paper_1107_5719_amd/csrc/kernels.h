@@ -1164,8 +1164,11 @@ inline void lstar_args(Ctx *c, LstarArgs &a)
     a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
     a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.cseg = c->cseg; a.chi = c->chi; a.L = c->L;
     a.xtab = c->xtab;
-    // the 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use
-    if (c->plan.p_elems >= 18 * c->V) {
+    // The 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use.  The symmetry holds between
+    // tables of opposite directions that mirror each other, and the tile's walks cross a face at every step: with slivers
+    // neither is so (8 x 20 angles, 3000 layers of chi = 30: corner entries off by 2% in tiles; 4 x 12, 1200 layers: entries of 5e-9
+    // of their row off by 8e-6 by symmetry), and all pairs are walked voxel by voxel.
+    if (c->plan.p_elems >= 18 * c->V && !c->plan.slivers) {
         a.T = static_cast<double *>(c->P);
         if (a.early_exit) lstar_tile(a.nx, a.ny, a.tx, a.ty);
     }
