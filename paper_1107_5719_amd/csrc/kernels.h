@@ -955,7 +955,7 @@ __device__ inline void lstar_body(const LstarArgs &a, int p, int k)
         for (int o = 0; o < 9; ++o) a.L[(9 + o) * V + v] = acc[o][threadIdx.x];
 }
 
-// Tiled form, for grids whose lines cannot wrap back (early_exit) with at least 16 pairs.
+// Tiled form, for grids whose lines cannot wrap back (early_exit).
 // K_vu = chi_v Lambda*_vu is symmetric, and the walk of an upward line from v to u is that of the reversed
 // downward line from u to v, so the downward pairs alone give all of it: with D the part that they add,
 // K_vu = D_vu + D_uv for voxels of one layer and K_vu = D_vu, K_uv = D_vu for u in the layer above.
@@ -1155,6 +1155,20 @@ inline int lstar_tile_threads(const LstarArgs &a) { return ((a.tx + 2) * (a.ty +
 inline int lstar_tile_blocks(const LstarArgs &a) { return ((a.nx + a.tx - 1) / a.tx) * ((a.ny + a.ty - 1) / a.ty); }
 inline size_t lstar_tile_lds(const LstarArgs &a) { return size_t(4) * (a.tx + 2) * (a.ty + 2) * sizeof(double2); }
 
+// Whether the downward pairs' sums, folded by symmetry, give Lambda*.  A function of the problem alone: the two forms round
+// differently, and a batch's member builds what a single context does, whatever the sweep's shape and splits.
+// The sums' 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use and which is made that large
+// (lstar_scratch): 12 pairs have 16 to 23 V elements of their own, 8 at most 17.3, and would need half as much memory again
+// (65^3, new medium and Lambda*, both forms: 2 x 12 angles 232 and 141 us; 4 x 4, in the full form, 140).
+// Symmetry holds between tables of opposite directions that mirror each other, and the tile's walks cross a face at every
+// step: with slivers neither is so (8 x 20 angles, 3000 layers of chi = 30: corner entries off by 2% in tiles; 4 x 12, 1200
+// layers: entries of 5e-9 of their row off by 8e-6 by symmetry), and all pairs are walked voxel by voxel.
+inline bool lstar_by_symmetry(const rt3d::SweepPlan &plan) { return plan.n_pair >= 12 && !plan.slivers; }
+inline int64_t lstar_scratch(const rt3d::SweepPlan &plan)
+{
+    return lstar_by_symmetry(plan) ? 18 * int64_t(plan.nx) * plan.ny * plan.nz : 0;
+}
+
 template <typename Ctx>
 inline void lstar_args(Ctx *c, LstarArgs &a)
 {
@@ -1164,11 +1178,7 @@ inline void lstar_args(Ctx *c, LstarArgs &a)
     a.pairs = c->pairs; a.seg_off = c->seg_off; a.seg_n = c->seg_n; a.seg_ai = c->seg_ai;
     a.seg_bi = c->seg_bi; a.seg_len = c->seg_len64; a.cseg = c->cseg; a.chi = c->chi; a.L = c->L;
     a.xtab = c->xtab;
-    // The 18 planes lie in the partial planes' buffer, which only a sweep and its reduction use.  The symmetry holds between
-    // tables of opposite directions that mirror each other, and the tile's walks cross a face at every step: with slivers
-    // neither is so (8 x 20 angles, 3000 layers of chi = 30: corner entries off by 2% in tiles; 4 x 12, 1200 layers: entries of 5e-9
-    // of their row off by 8e-6 by symmetry), and all pairs are walked voxel by voxel.
-    if (c->plan.p_elems >= 18 * c->V && !c->plan.slivers) {
+    if (lstar_by_symmetry(c->plan)) {
         a.T = static_cast<double *>(c->P);
         if (a.early_exit) lstar_tile(a.nx, a.ny, a.tx, a.ty);
     }

@@ -572,7 +572,7 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
     auto chk = [&](int r) { if (!rc) rc = r; };
     {
         double *Pp = nullptr;
-        chk(dev_alloc(c, &Pp, size_t(P.p_elems)));
+        chk(dev_alloc(c, &Pp, size_t(std::max(P.p_elems, lstar_scratch(P)))));
         c->P = Pp;
     }
     chk(upload(c, &c->seg_len64, P.seg_len));
