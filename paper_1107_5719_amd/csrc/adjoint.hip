@@ -55,7 +55,7 @@ struct AdjLineArgs {
     const double *nu, *eps;       // weights c = (1 - eps) nu W|mu| of the deposits, or nu == null
     double *Qx;                   // [n_dir][nz][ny*nx]: adjoint q leaving layer k along line p
     double *Qstart;               // [n_up][ny*nx]: q at the start of the upward lines (or null)
-    const double *xtab;           // [kExpTab]
+    const double *xtab;           // [kExpTabSize]
 };
 
 __device__ inline int wrap_any(int a, int n)
@@ -102,11 +102,11 @@ __device__ inline int line_voxel(const AdjLineArgs &a, int i0, int j0, int A, in
     return row * a.nx + col;
 }
 
-// the float64 exponential's table (see exp_pair_tab) in LDS; the whole block calls this
+// the float64 exponential's tables (see exp_pair_ulp) in LDS; the whole block calls this
 __device__ inline const double *line_exp_table(const AdjLineArgs &a)
 {
-    __shared__ double tab[kExpTab];
-    if (threadIdx.x < kExpTab) tab[threadIdx.x] = a.xtab[threadIdx.x];
+    __shared__ double tab[kExpTabSize];
+    if (threadIdx.x < kExpTabSize) tab[threadIdx.x] = a.xtab[threadIdx.x];
     __syncthreads();
     return tab;
 }
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kLineThreads) void adj_record_kernel(AdjLineArgs a)
             double len;
             L.get(a, s, A, B, len);
             const long v = long(k) * nxy + line_voxel(a, i0, j0, A, B);
-            const double em1 = expm1_nonpos_tab(-a.chi[v] * len, tab);
+            const double em1 = expm1_ulp(-a.chi[v] * len, tab);
             I = I + (I - a.S[v]) * em1;
         }
     }
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kLineThreads) void adj_back_kernel(AdjLineArgs a, i
             double len;
             L.get(a, s, A, B, len);
             const long v = long(k) * nxy + line_voxel(a, i0, j0, A, B);
-            const double em1 = expm1_nonpos_tab(-a.chi[v] * len, tab);
+            const double em1 = expm1_ulp(-a.chi[v] * len, tab);
             const double c = deposit_weight(a, v, wmu);
             q = q - (c - q) * em1;                           // q e + c (1 - e)
         }
@@ -239,11 +239,11 @@ __global__ __launch_bounds__(kPlaneThreads) void adj_pull_kernel(AdjLineArgs a, 
                 double len2;
                 L.get(a, s2, A2, B2, len2);
                 const long v2 = plane + line_voxel(a, i0, j0, A2, B2);
-                const double em1 = expm1_nonpos_tab(-a.chi[v2] * len2, tab);
+                const double em1 = expm1_ulp(-a.chi[v2] * len2, tab);
                 q = q - (deposit_weight(a, v2, wmu) - q) * em1;
             }
             double e, em1;
-            exp_pair_tab(-chiv * len, tab, e, em1);
+            exp_pair_ulp(-chiv * len, tab, e, em1);
             if (mode == 0) {
                 acc -= q * em1;
             } else {
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kPlaneThreads) void adj_pull_kernel(AdjLineArgs a, 
                     double len2;
                     L.get(a, s2, A2, B2, len2);
                     const long v2 = plane + line_voxel(a, i0, j0, A2, B2);
-                    const double em1b = expm1_nonpos_tab(-a.chi[v2] * len2, tab);
+                    const double em1b = expm1_ulp(-a.chi[v2] * len2, tab);
                     I = I + (I - a.S[v2]) * em1b;
                 }
                 const double c = cv * wmu;

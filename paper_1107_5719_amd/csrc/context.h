@@ -49,7 +49,7 @@ struct rt3d_ctx {
     double *Kc = nullptr, *invD = nullptr, *Ecoef = nullptr;   // Jacobi coefficients (float64 form)
     double *Sbuf = nullptr;
     double *bot_slope = nullptr;        // [ny][nx] LTE-diffusion gradient (bottom_bc 2)
-    double *xtab = nullptr;             // [kExpTab] 2^(j/kExpTab) for the float64 exponential of the sweep
+    double *xtab = nullptr;             // [kExpTabSize] the float64 exponential's tables (exp_table)
     void *cs = nullptr, *P = nullptr;       // sized for float64; float sweeps use the first half
     double *seg_len64 = nullptr;
     float *seg_len32 = nullptr;

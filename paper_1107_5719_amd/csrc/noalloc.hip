@@ -105,7 +105,7 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
 
     // workspace layout: exponential table, {chi, S}, pair tables, segments, layer blocks, work items of
     // every range, then the partial planes of one range of pairs
-    std::vector<double> tab(kExpTab);
+    std::vector<double> tab(kExpTabSize);
     exp_table(tab.data());
     // the reduction's sum of a chunk of pairs that a range leaves unfinished
     const int chunk = reduce_chunk_pairs(V, plan.n_pair);

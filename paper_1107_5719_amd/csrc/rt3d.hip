@@ -662,9 +662,9 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
         c->d_flag = reinterpret_cast<int *>(c->d_scal + 2);
     }
     if (g->bottom_bc == 2) chk(dev_alloc(c, &c->bot_slope, size_t(g->nx) * g->ny));
-    chk(dev_alloc(c, &c->xtab, kExpTab));
+    chk(dev_alloc(c, &c->xtab, kExpTabSize));
     if (!rc) {
-        double tab[kExpTab];
+        double tab[kExpTabSize];
         exp_table(tab);
         if (hipMemcpy(c->xtab, tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess)
             rc = fail(c, RT3D_ERR_HIP, "upload of the exponential table");
