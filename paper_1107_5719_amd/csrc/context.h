@@ -52,7 +52,6 @@ struct rt3d_ctx {
     double *xtab = nullptr;             // [kExpTabSize] the float64 exponential's tables (exp_table)
     void *cs = nullptr, *P = nullptr;       // sized for float64; float sweeps use the first half
     double *seg_len64 = nullptr;
-    float *seg_len32 = nullptr;
     // FP32 form: anchor iterate, its float64 formal solution and top-plane light, float coefficients
     double *Ja = nullptr, *Fa = nullptr, *Iem_a = nullptr;
     float *Kc32 = nullptr;                                     // Jacobi coefficients stored in float32
@@ -61,8 +60,7 @@ struct rt3d_ctx {
     bool anchor_valid = false, force_refresh = false, last_step_anchored = false;
     double c_last = INFINITY, da_last = 0.0;
     long fp64_sweeps = 0, fp32_sweeps = 0;
-    int *seg_off = nullptr, *seg_n = nullptr, *seg_a = nullptr, *seg_bb = nullptr, *seg_bm = nullptr;
-    int *seg_ai = nullptr, *seg_bi = nullptr;
+    int *seg_off = nullptr, *seg_n = nullptr, *seg_ai = nullptr, *seg_bi = nullptr;
     rt3d::LayerBlock *blocks = nullptr;
     rt3d::ColumnSeg *cseg = nullptr;
     rt3d::DirInfo *dirs = nullptr;

@@ -127,8 +127,8 @@ void face_crossings(int nz, double x0, double t, double z_in, double z_out, std:
         zc = std::min(std::max(zc, lo), hi);
         z.push_back(zc);
     }
-    std::sort(z.begin(), z.end());
-    if (z_out < z_in) std::reverse(z.begin(), z.end());
+    // in the order of m the heights rise or fall with the sign of t (rounding keeps the order)
+    if ((t < 0.0) != (z_out < z_in)) std::reverse(z.begin(), z.end());
 }
 
 }  // namespace
@@ -138,7 +138,7 @@ void layer_segments(int nz, double mu, double ox, double oy, int k, LayerSegment
     const double tx = ox / mu, ty = oy / mu;                  // horizontal drift per unit height
     const double z_in = (mu < 0.0) ? k + 1.0 : double(k);
     const double z_out = (mu < 0.0) ? double(k) : k + 1.0;
-    std::vector<double> zx, zy;
+    std::vector<double> &zx = out.zx, &zy = out.zy, &zb = out.zb;
     face_crossings(nz, 0.5, tx, z_in, z_out, zx);
     face_crossings(nz, 0.5, ty, z_in, z_out, zy);
     // merge the two ordered crossing lists along the travel direction; crossings closer than
@@ -146,8 +146,7 @@ void layer_segments(int nz, double mu, double ox, double oy, int k, LayerSegment
     // otherwise leave a rounding-sized sliver between the x and the y crossing)
     constexpr double kCornerTol = 1e-12;
     const bool down = z_out < z_in;
-    std::vector<double> zb;
-    zb.reserve(zx.size() + zy.size() + 2);
+    zb.clear();
     zb.push_back(z_in);
     size_t p = 0, q = 0;
     while (p < zx.size() || q < zy.size()) {
@@ -200,6 +199,8 @@ static void sort_work(std::vector<std::pair<double, WorkItem>> &work, SweepPlan 
                      [](const std::pair<double, WorkItem> &x, const std::pair<double, WorkItem> &y) {
                          return x.first > y.first;
                      });
+    P.items.clear();
+    P.items.reserve(work.size());
     for (auto &w : work) P.items.push_back(w.second);
 }
 
@@ -230,155 +231,137 @@ void append_column_segments(SweepPlan &P)
     }
 }
 
+// Rows, less one, that a line of the pair comes through in layer k
+int layer_span(const SweepPlan &P, const PairInfo &pi, int k)
+{
+    const size_t ka = size_t(pi.dA) * P.nz + k;
+    const auto first = P.seg_bi.begin() + P.seg_off[ka];
+    const auto mm = std::minmax_element(first, first + P.seg_n[ka]);
+    return *mm.second - *mm.first;
+}
+
 }  // namespace
 
-bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
-                      size_t lds_bytes_max, SweepPlan &P, std::string &err)
+void segment_plan(int nx, int ny, int nz, const AngleSet &A, SweepPlan &P)
 {
     P = SweepPlan();
     P.nx = nx;
     P.ny = ny;
     P.nz = nz;
     P.n_dir = A.n_dir;
-    P.lines_per_wg = lines_per_wg;
-    const int max_rows = lines_per_wg / nx;
-    if (max_rows < 1) {
-        err = "nx exceeds the lines one sweep workgroup can hold";
-        return false;
-    }
-    P.seg_off.assign(size_t(A.n_dir) * nz, 0);
-    P.seg_n.assign(size_t(A.n_dir) * nz, 0);
-    P.row_min.assign(size_t(A.n_dir) * nz, 0);
+    const size_t n_dk = size_t(A.n_dir) * nz;
+    P.seg_off.resize(n_dk);
+    P.seg_n.resize(n_dk);
+    P.row_min.resize(n_dk);
     P.dirs.resize(A.n_dir);
-    std::vector<int> span(A.n_dir, 0);
-    std::vector<double> seg_per_layer(A.n_dir, 0.0);
+    // heights of crossings are rounded to a few eps nz
+    const double sliver = 64.0 * std::numeric_limits<double>::epsilon() * nz;
     LayerSegments L;
-    long total_segments = 0;
     for (int d = 0; d < A.n_dir; ++d) {
-        long nseg = 0;
-        for (int k = 0; k < nz; ++k) {
-            direction_segments(nz, A, d, k, L);
-            const int n = int(L.di.size());
-            const int bmin = *std::min_element(L.dj.begin(), L.dj.end());
-            const int bmax = *std::max_element(L.dj.begin(), L.dj.end());
-            span[d] = std::max(span[d], bmax - bmin);
-            const size_t dk = size_t(d) * nz + k;
-            P.seg_off[dk] = int(P.seg_a.size());
-            P.seg_n[dk] = n;
-            P.row_min[dk] = pos_mod(bmin, ny);
-            for (int s = 0; s < n; ++s) {
-                P.seg_a.push_back(pos_mod(L.di[s], nx));
-                P.seg_bb.push_back(L.dj[s] - bmin);
-                P.seg_bm.push_back(pos_mod(L.dj[s] - bmin, ny));
-                P.seg_ai.push_back(L.di[s]);
-                P.seg_bi.push_back(L.dj[s]);
-                P.seg_len.push_back(L.len[s]);
-                // heights of crossings are rounded to a few eps nz
-                P.slivers = P.slivers || L.len[s] * std::fabs(A.mu[d]) < 64.0 * std::numeric_limits<double>::epsilon() * nz;
-            }
-            nseg += n;
-        }
-        total_segments += nseg;
-        seg_per_layer[d] = double(nseg) / nz;
         P.dirs[d].wmu = A.w[d] * std::fabs(A.mu[d]);
         P.dirs[d].down = A.mu[d] < 0.0 ? 1 : 0;
         P.dirs[d].pad = 0;
         P.dirs[d].mu = A.mu[d];
+        const int b = d % A.n_phi, bm = mirror_x(b, A.n_phi);
+        if (bm < b) {
+            // the second of a pair mirrored in x has the first one's table with negated columns (direction_segments)
+            const size_t k0 = size_t(d - b + bm) * nz, k1 = size_t(d) * nz, at = P.seg_len.size();
+            const size_t s0 = size_t(P.seg_off[k0]), n = size_t(P.seg_off[k0 + nz - 1] + P.seg_n[k0 + nz - 1]) - s0;
+            for (int k = 0; k < nz; ++k) {
+                P.seg_off[k1 + k] = P.seg_off[k0 + k] + int(at - s0);
+                P.seg_n[k1 + k] = P.seg_n[k0 + k];
+                P.row_min[k1 + k] = P.row_min[k0 + k];
+            }
+            P.seg_ai.resize(at + n);
+            P.seg_bi.resize(at + n);
+            P.seg_len.resize(at + n);
+            for (size_t s = 0; s < n; ++s) {
+                P.seg_ai[at + s] = -P.seg_ai[s0 + s];
+                P.seg_bi[at + s] = P.seg_bi[s0 + s];
+                P.seg_len[at + s] = P.seg_len[s0 + s];
+            }
+            continue;
+        }
+        for (int k = 0; k < nz; ++k) {
+            direction_segments(nz, A, d, k, L);
+            const size_t dk = size_t(d) * nz + k;
+            P.seg_off[dk] = int(P.seg_len.size());
+            P.seg_n[dk] = int(L.di.size());
+            P.row_min[dk] = pos_mod(*std::min_element(L.dj.begin(), L.dj.end()), ny);
+            P.seg_ai.insert(P.seg_ai.end(), L.di.begin(), L.di.end());
+            P.seg_bi.insert(P.seg_bi.end(), L.dj.begin(), L.dj.end());
+            P.seg_len.insert(P.seg_len.end(), L.len.begin(), L.len.end());
+            for (double l : L.len) P.slivers = P.slivers || l * std::fabs(A.mu[d]) < sliver;
+        }
     }
-    P.mean_segments = double(total_segments) / (double(A.n_dir) * nz);
-    // pairs mirrored in x: the partner's tables must equal the owner's up to negated columns
-    for (int a = 0; a < A.n_theta; ++a) {
+    P.mean_segments = double(P.seg_len.size()) / (double(A.n_dir) * nz);
+    for (int a = 0; a < A.n_theta; ++a)
         for (int b = 0; b < A.n_phi; ++b) {
             const int bm = mirror_x(b, A.n_phi);
             if (bm < b) continue;
-            const int dA = a * A.n_phi + b, dB = a * A.n_phi + bm;
-            for (int k = 0; k < nz; ++k) {
-                const size_t ka = size_t(dA) * nz + k, kb = size_t(dB) * nz + k;
-                if (P.seg_n[ka] != P.seg_n[kb] || P.row_min[ka] != P.row_min[kb]) {
-                    err = "mirrored directions do not share their segment structure";
-                    return false;
-                }
-                for (int s = 0; s < P.seg_n[ka]; ++s) {
-                    const int ia = P.seg_off[ka] + s, ib = P.seg_off[kb] + s;
-                    if (P.seg_ai[ia] != -P.seg_ai[ib] || P.seg_bi[ia] != P.seg_bi[ib] ||
-                        P.seg_len[ia] != P.seg_len[ib]) {
-                        err = "mirrored directions do not share their segment structure";
-                        return false;
-                    }
-                }
-            }
             PairInfo pi{};
-            pi.wmu = P.dirs[dA].wmu;
-            pi.dA = dA;
-            pi.dB = dB;
-            pi.down = P.dirs[dA].down;
-            pi.mu = A.mu[dA];
-            pi.xsgn = A.ox[dA] > 0.0 ? 1 : -1;
-            pi.ysgn = A.oy[dA] > 0.0 ? 1 : -1;
-            // Band height: about target_seg_per_wg line-segments per layer for the two directions,
-            // never thinner than the window's halo, within the line and LDS budgets.
-            int rows = int(std::lround(target_seg_per_wg / (2.0 * nx * seg_per_layer[dA])));
-            rows = std::max(rows, std::max(1, span[dA]));
-            rows = std::min(rows, max_rows);
-            auto lds = [&](int r) {
-                return std::max(sweep_lds_bytes(r + span[dA], r, nx, false),
-                                sweep_lds_bytes(r + span[dA], r, nx, true));
-            };
-            while (rows > 1 && lds(rows) > lds_bytes_max) --rows;
-            rows = std::min(rows, ny);
-            if (lds(rows) > lds_bytes_max) {
-                err = "the deposit window of one band exceeds the LDS budget";
-                return false;
-            }
-            pi.band_rows = rows;
-            pi.n_bands = (ny + rows - 1) / rows;
-            pi.win_rows = rows + span[dA];
-            pi.last_rows = ny - (pi.n_bands - 1) * rows;
-            pi.inv_rows = 1.0f / float(rows);
-            P.max_win_rows = std::max(P.max_win_rows, pi.win_rows);
+            pi.dA = a * A.n_phi + b;
+            pi.dB = a * A.n_phi + bm;
+            pi.wmu = P.dirs[pi.dA].wmu;
+            pi.down = P.dirs[pi.dA].down;
+            pi.mu = A.mu[pi.dA];
+            pi.xsgn = A.ox[pi.dA] > 0.0 ? 1 : -1;
+            pi.ysgn = A.oy[pi.dA] > 0.0 ? 1 : -1;
             P.pairs.push_back(pi);
-            const size_t pl0 = P.player.size();
-            for (int k = 0; k < nz; ++k) {
-                const size_t ka = size_t(dA) * nz + k;
-                PairLayer pl{int(P.pseg.size()), P.seg_n[ka], P.row_min[ka], 0};
-                P.player.push_back(pl);
-                for (int s = 0; s < P.seg_n[ka]; ++s) {
-                    const int ia = P.seg_off[ka] + s;
-                    PairSeg ps{};
-                    ps.saA = P.seg_a[ia];
-                    ps.shB = 0;
-                    ps.smnx = P.seg_bm[ia] * nx;
-                    ps.sbnx = P.seg_bb[ia] * nx;
-                    ps.len = P.seg_len[ia];
-                    ps.len32 = float(P.seg_len[ia]);
-                    P.pseg.push_back(ps);
-                }
-            }
-            // moves of the B lines: a slot holds the B line whose top column is its A line's plus
-            // 2 dA, so when dA changes by delta to the next segment in sweep order (layers top down
-            // for downward pairs) the B line moves by -2 delta columns
-            std::vector<int> order;            // the pair's segments in sweep order, unreduced dA
-            std::vector<size_t> at;
-            for (int st = 0; st < nz; ++st) {
-                const int k = pi.down ? nz - 1 - st : st;
-                const size_t ka = size_t(dA) * nz + k;
-                const size_t base = size_t(P.player[pl0 + k].off);
-                for (int s = 0; s < P.seg_n[ka]; ++s) {
-                    order.push_back(P.seg_ai[P.seg_off[ka] + s]);
-                    at.push_back(base + size_t(s));
-                }
-            }
-            for (size_t i = 0; i + 1 < order.size(); ++i)
-                P.pseg[at[i]].shB = pos_mod(-2 * (order[i + 1] - order[i]), nx);
         }
-    }
     P.n_pair = int(P.pairs.size());
+    append_column_segments(P);
+}
+
+bool window_row_fits(int lines_per_wg, int nx, std::string &err)
+{
+    if (nx <= lines_per_wg) return true;
+    err = "nx exceeds the lines one sweep workgroup can hold";
+    return false;
+}
+
+bool window_bands(int lines_per_wg, int target_seg_per_wg, size_t lds_bytes_max, SweepPlan &P, std::string &err)
+{
+    const int nx = P.nx, ny = P.ny, nz = P.nz;
+    if (!window_row_fits(lines_per_wg, nx, err)) return false;
+    const int max_rows = lines_per_wg / nx;
+    P.lines_per_wg = lines_per_wg;
+    P.max_win_rows = 0;
     // the Lambda* kernel takes the pairs as two runs, all of one vertical direction, then the other
     for (int p = 1, changes = 0; p < P.n_pair; ++p)
         if (P.pairs[p].down != P.pairs[p - 1].down && ++changes > 1) {
             err = "direction pairs are not ordered by their vertical direction";
             return false;
         }
+    for (PairInfo &pi : P.pairs) {
+        int span = 0;
+        for (int k = 0; k < nz; ++k) span = std::max(span, layer_span(P, pi, k));
+        // Band height: about target_seg_per_wg line-segments per layer for the two directions,
+        // never thinner than the window's halo, within the line and LDS budgets.
+        const double seg_per_layer = double(pi.n_seg) / nz;
+        int rows = int(std::lround(target_seg_per_wg / (2.0 * nx * seg_per_layer)));
+        rows = std::max(rows, std::max(1, span));
+        rows = std::min(rows, max_rows);
+        auto lds = [&](int r) {
+            return std::max(sweep_lds_bytes(r + span, r, nx, false), sweep_lds_bytes(r + span, r, nx, true));
+        };
+        while (rows > 1 && lds(rows) > lds_bytes_max) --rows;
+        rows = std::min(rows, ny);
+        if (lds(rows) > lds_bytes_max) {
+            err = "the deposit window of one band exceeds the LDS budget";
+            return false;
+        }
+        pi.band_rows = rows;
+        pi.n_bands = (ny + rows - 1) / rows;
+        pi.win_rows = rows + span;
+        P.max_win_rows = std::max(P.max_win_rows, pi.win_rows);
+    }
+    return true;
+}
+
+void window_plan(SweepPlan &P)
+{
+    const int nx = P.nx, ny = P.ny, nz = P.nz;
     int64_t off = 0;
     std::vector<std::pair<double, WorkItem>> work;
     P.blocks.resize(size_t(P.n_pair) * nz);
@@ -387,22 +370,59 @@ bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_w
         pi.p_off = off;
         pi.band_stride = int64_t(nz) * pi.win_rows * nx;
         off += pi.n_bands * pi.band_stride;
-        for (int k = 0; k < nz; ++k)
+        const size_t pl0 = P.player.size();
+        for (int k = 0; k < nz; ++k) {
+            const size_t ka = size_t(pi.dA) * nz + k;
+            const int o = P.seg_off[ka], n = P.seg_n[ka];
+            const int bmin = *std::min_element(P.seg_bi.begin() + o, P.seg_bi.begin() + o + n);
+            P.player.push_back(PairLayer{int(P.pseg.size()), n, P.row_min[ka], 0});
+            for (int s = o; s < o + n; ++s) {
+                PairSeg ps{};
+                ps.saA = pos_mod(P.seg_ai[s], nx);
+                ps.shB = 0;
+                ps.smnx = pos_mod(P.seg_bi[s] - bmin, ny) * nx;
+                ps.sbnx = (P.seg_bi[s] - bmin) * nx;
+                ps.len = P.seg_len[s];
+                ps.len32 = float(P.seg_len[s]);
+                P.pseg.push_back(ps);
+            }
             P.blocks[size_t(k) * P.n_pair + p] =
-                LayerBlock{pi.p_off + int64_t(k) * pi.win_rows * nx, pi.wmu, P.row_min[size_t(pi.dA) * nz + k],
+                LayerBlock{pi.p_off + int64_t(k) * pi.win_rows * nx, pi.wmu, P.row_min[ka],
                            pi.win_rows - pi.band_rows, nz * pi.win_rows, pi.band_rows << kBlockRows};
+        }
+        // moves of the B lines: a slot holds the B line whose top column is its A line's plus
+        // 2 dA, so when dA changes by delta to the next segment in sweep order (layers top down
+        // for downward pairs) the B line moves by -2 delta columns
+        PairSeg *before = nullptr;
+        int dA = 0;
+        for (int st = 0; st < nz; ++st) {
+            const int k = pi.down ? nz - 1 - st : st;
+            const int o = P.seg_off[size_t(pi.dA) * nz + k];
+            for (int s = 0; s < P.player[pl0 + k].ns; ++s) {
+                if (before) before->shB = pos_mod(-2 * (P.seg_ai[o + s] - dA), nx);
+                before = &P.pseg[P.player[pl0 + k].off + s];
+                dA = P.seg_ai[o + s];
+            }
+        }
         for (int b = 0; b < pi.n_bands; ++b) {
             WorkItem it;
             it.pair = p;
             it.band = b;
             it.j0 = b * pi.band_rows;
             it.rows = std::min(pi.band_rows, ny - it.j0);
-            work.push_back({it.rows * seg_per_layer[pi.dA], it});
+            work.push_back({it.rows * double(pi.n_seg) / nz, it});
         }
     }
     P.p_elems = off;
     sort_work(work, P);
-    append_column_segments(P);
+}
+
+bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
+                      size_t lds_bytes_max, SweepPlan &P, std::string &err)
+{
+    segment_plan(nx, ny, nz, A, P);
+    if (!window_bands(lines_per_wg, target_seg_per_wg, lds_bytes_max, P, err)) return false;
+    window_plan(P);
     return true;
 }
 
@@ -455,81 +475,70 @@ double column_load(int nx, int ny, int nz, const AngleSet &A)
     return 0.5 * seg * nz * (double(nx) * ny / 64.0);
 }
 
-bool make_column_plan(const AngleSet &A, int threads, int lines, double load, SweepPlan &plan)
+bool make_column_plan(const AngleSet &A, int threads, int lines, double load, SweepPlan &P)
 {
-    if (plan.nx > kColumnMaxNx) return false;
-    SweepPlan P = plan;
     const int nx = P.nx, ny = P.ny, nz = P.nz;
-    P.columns = true;
-    P.pseg.clear();
-    P.player.clear();
-    P.blocks.assign(size_t(P.n_pair) * nz, LayerBlock{});
-    P.items.clear();
-    P.max_win_rows = 0;
-    P.block_threads = 64;
-    P.col_rows = 1;
+    if (nx > kColumnMaxNx) return false;
+    std::vector<PairInfo> pairs = P.pairs;
+    std::vector<LayerBlock> blocks(size_t(P.n_pair) * nz);
+    std::vector<std::pair<double, WorkItem>> work;
+    int max_cover = 0, block_threads = 64, col_rows = 1;
     // waves per SIMD of the launch, if its other members are like this one
     const double fill = double(nx) * ny / 64.0 * P.n_pair / 1024.0 * load / column_load(nx, ny, nz, A);
-    std::vector<std::pair<double, WorkItem>> work;
     int64_t off = 0;
     for (int p = 0; p < P.n_pair; ++p) {
-        PairInfo &pi = P.pairs[p];
-        int n_seg = 0;
-        for (int k = 0; k < nz; ++k) n_seg += P.seg_n[size_t(pi.dA) * nz + k];
-        pi.split = lines <= 2 && column_split(n_seg, load) ? 1 : 0;
+        PairInfo &pi = pairs[p];
+        pi.split = lines <= 2 && column_split(pi.n_seg, load) ? 1 : 0;
         const int rows = pi.split ? 1 : kColumnRows;
         const int n_parts = (ny + rows - 1) / rows;       // bands, or line rows
         const int G = column_bands(nx, n_parts, fill, std::max(1, threads / 64));
-        P.block_threads = std::max(P.block_threads, (G * nx + 63) / 64 * 64);
-        P.col_rows = std::max(P.col_rows, rows);
+        block_threads = std::max(block_threads, (G * nx + 63) / 64 * 64);
+        col_rows = std::max(col_rows, rows);
         pi.band_rows = kColumnRows;
         pi.n_bands = (ny + kColumnRows - 1) / kColumnRows;
-        pi.last_rows = ny - (pi.n_bands - 1) * kColumnRows;
-        pi.inv_rows = 1.0f / float(kColumnRows);
         pi.win_rows = 0;
+        pi.row0 = pos_mod(P.seg_bi[P.seg_off[size_t(pi.dA) * nz + (pi.down ? nz - 1 : 0)]], ny);
+        const size_t ka_end = size_t(pi.dA) * nz + (pi.down ? 0 : nz - 1);
+        pi.sa_last = pos_mod(P.seg_ai[P.seg_off[ka_end] + P.seg_n[ka_end] - 1], nx);
         int64_t block = 0;
         size_t end = size_t(pi.c_off);         // end of the layer in the segment list
         for (int st = 0; st < nz; ++st) {
             const int k = pi.down ? nz - 1 - st : st;
             const size_t ka = size_t(pi.dA) * nz + k;
-            const int o = P.seg_off[ka], n = P.seg_n[ka];
-            int jmin = P.seg_bi[o], jmax = jmin;
-            for (int s = 0; s < n; ++s) {
-                const int j = P.seg_bi[o + s];
-                jmin = std::min(jmin, j);
-                jmax = std::max(jmax, j);
-                if (st == 0 && s == 0) pi.row0 = pos_mod(j, ny);
-                pi.sa_last = P.seg_a[o + s];
-            }
-            const int cover = rows + jmax - jmin;
+            const int span = layer_span(P, pi, k), cover = rows + span;
             if (st == 0) pi.cover0 = cover;
             else P.cseg[end - 1].cover = cover;
-            end += size_t(n);
+            end += size_t(P.seg_n[ka]);
             pi.win_rows = std::max(pi.win_rows, cover);
-            P.blocks[size_t(k) * P.n_pair + p] =
-                LayerBlock{off + block, pi.wmu, P.row_min[ka], jmax - jmin, 0,
+            blocks[size_t(k) * P.n_pair + p] =
+                LayerBlock{off + block, pi.wmu, P.row_min[ka], span, 0,
                            (kColumnRows << kBlockRows) | (pi.split ? kBlockSplit : 0) | (pi.ysgn < 0 ? kBlockDown : 0)};
             block += int64_t(cover) * nx;
         }
         pi.band_stride = block;
-        for (int k = 0; k < nz; ++k) P.blocks[size_t(k) * P.n_pair + p].stride = int(block / nx);
+        for (int k = 0; k < nz; ++k) blocks[size_t(k) * P.n_pair + p].stride = int(block / nx);
         pi.p_off = off;
         off += n_parts * block;
         // the kernel addresses a workgroup's bands with 32-bit byte offsets
         if (G * block * int64_t(sizeof(double)) >= (int64_t(1) << 32) - 16) return false;
-        P.max_win_rows = std::max(P.max_win_rows, pi.win_rows);
+        max_cover = std::max(max_cover, pi.win_rows);
         for (int b = 0; b < n_parts; b += G) {
             WorkItem it;
             it.pair = p;
             it.band = b;
             it.j0 = b * rows;
             it.rows = std::min(G, n_parts - b);
-            work.push_back({n_seg * column_segment_cycles(rows), it});
+            work.push_back({pi.n_seg * column_segment_cycles(rows), it});
         }
     }
+    P.columns = true;
+    P.pairs = std::move(pairs);
+    P.blocks = std::move(blocks);
+    P.max_win_rows = max_cover;
+    P.block_threads = block_threads;
+    P.col_rows = col_rows;
     P.p_elems = off;
     sort_work(work, P);
-    plan = std::move(P);
     return true;
 }
 

@@ -23,6 +23,7 @@ bool make_angle_set(int n_theta, int n_phi, AngleSet &out);
 struct LayerSegments {
     std::vector<int> di, dj;
     std::vector<double> len;
+    std::vector<double> zx, zy, zb;      // working space: crossings of the x and y faces, and all of them
 };
 void layer_segments(int nz, double mu, double ox, double oy, int k, LayerSegments &out);
 
@@ -54,8 +55,6 @@ struct PairInfo {
     int band_rows;     // Bj: line rows per band (last band may be shorter)
     int n_bands;       // nb
     int win_rows;      // Hw = Bj + span: rows of the deposit window of one band
-    int last_rows;     // rows of the last band: ny - (nb - 1) * Bj
-    float inv_rows;    // 1 / Bj (band lookup; corrected exactly in the kernel)
     int64_t p_off;     // element offset of this pair's partial planes in P
     double mu;         // direction cosine with the z axis (the same for both)
     int64_t band_stride;   // elements of P per band
@@ -115,10 +114,7 @@ struct SweepPlan {
     int lines_per_wg = 0;                 // lines of one direction in one workgroup
     // segment tables, flat; index of (d, k) is d * nz + k
     std::vector<int> seg_off, seg_n;      // per (d, k)
-    std::vector<int> seg_a;               // column offset modulo nx, in [0, nx)
-    std::vector<int> seg_bb;              // row offset minus the layer's minimum, in [0, span]
-    std::vector<int> seg_bm;              // seg_bb modulo ny
-    std::vector<int> seg_ai, seg_bi;      // unreduced column / row offsets (for Lambda*)
+    std::vector<int> seg_ai, seg_bi;      // column / row offsets from the line's top column
     std::vector<double> seg_len;
     std::vector<int> row_min;             // per (d, k): minimum row offset modulo ny
     std::vector<DirInfo> dirs;
@@ -126,7 +122,7 @@ struct SweepPlan {
     std::vector<PairSeg> pseg;            // packed per-pair segments
     std::vector<PairLayer> player;        // per (pair, layer): index pair * nz + k
     std::vector<LayerBlock> blocks;       // per (layer, pair): index k * n_pair + pair
-    // column form (the window form's pseg and player are empty then)
+    // column form (it has no pseg and player)
     bool columns = false;
     int col_rows = 0;                     // most rows per thread of any pair
     int block_threads = 0;                // threads of a workgroup
@@ -148,18 +144,25 @@ inline size_t sweep_lds_bytes(int win_rows, int band_rows, int nx, bool f32)
     return (cells + 2 * lines) * (f32 ? sizeof(float) : sizeof(double));
 }
 
-// Build segment tables and the band plan.  lines_per_wg bounds the lines of one direction in one
-// band; lds_bytes_max bounds a band's LDS in either precision (sweep_lds_bytes).
+// A plan is made in three steps: the segment tables and direction pairs (which every form of the sweep, Lambda* and the
+// adjoint read), the window form's bands, which decide what grids are accepted, and then the tables of one of the two forms.
+void segment_plan(int nx, int ny, int nz, const AngleSet &A, SweepPlan &plan);
+// lines_per_wg bounds the lines of one direction in one band; lds_bytes_max bounds a band's LDS in either
+// precision (sweep_lds_bytes).  May be called again with other limits.
+bool window_row_fits(int lines_per_wg, int nx, std::string &err);
+bool window_bands(int lines_per_wg, int target_seg_per_wg, size_t lds_bytes_max, SweepPlan &plan, std::string &err);
+void window_plan(SweepPlan &plan);
+// All three for the window form
 bool build_sweep_plan(int nx, int ny, int nz, const AngleSet &A, int lines_per_wg, int target_seg_per_wg,
                       size_t lds_bytes_max, SweepPlan &plan, std::string &err);
 
-// Turns a plan into the column form: a thread per column of a band (or, where the pair is split, of a line
+// The column form's tables: a thread per column of a band (or, where the pair is split, of a line
 // row), workgroups of at most about threads threads that hold several bands (line rows) of a pair; a work
 // item's band and rows count those.  load: what the launch that sweeps this plan has to do (this plan's own,
 // or the sum over the members of a batch), see column_load.  lines > 2: no pair is split.  The sums of a
 // voxel's deposits have the same order whether a pair is split or not.  Rows of more than kColumnMaxNx
-// columns keep the window form (false is returned and the plan left as it is): there one row fills a workgroup
-// by itself.
+// columns keep the window form (false is returned and the plan's bands left as they are): there one row fills
+// a workgroup by itself.
 constexpr int kColumnMaxNx = 512;
 constexpr int kColumnRows = 4;
 bool make_column_plan(const AngleSet &A, int threads, int lines, double load, SweepPlan &plan);

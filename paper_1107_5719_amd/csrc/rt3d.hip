@@ -187,15 +187,6 @@ dim3 plane_grid(const rt3d_ctx *c)
     return dim3((c->g.nx * c->g.ny + kPlaneThreads - 1) / kPlaneThreads, c->g.nz);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2) in linear order.
-// Padding the chunks of a plane to a multiple of 8 sends a chunk's blocks of every plane to the same
-// XCD, so the plane-below data a Jacobi sweep re-reads is in that XCD's L2.  Padding blocks exit.
-dim3 plane_grid_xcd(const rt3d_ctx *c)
-{
-    const unsigned chunks = (c->g.nx * c->g.ny + kPlaneThreads - 1) / kPlaneThreads;
-    return dim3((chunks + 7) / 8 * 8, c->g.nz);
-}
-
 int launch_source(rt3d_ctx *c, const double *S_given, const double *Ja, bool fp32)
 {
     SourceArgs a{};
@@ -515,9 +506,7 @@ std::string device_key()
 void free_plan(rt3d_ctx *c)
 {
     void **ptrs[] = {reinterpret_cast<void **>(&c->P), reinterpret_cast<void **>(&c->seg_len64),
-                     reinterpret_cast<void **>(&c->seg_len32), reinterpret_cast<void **>(&c->seg_off),
-                     reinterpret_cast<void **>(&c->seg_n), reinterpret_cast<void **>(&c->seg_a),
-                     reinterpret_cast<void **>(&c->seg_bb), reinterpret_cast<void **>(&c->seg_bm),
+                     reinterpret_cast<void **>(&c->seg_off), reinterpret_cast<void **>(&c->seg_n),
                      reinterpret_cast<void **>(&c->seg_ai), reinterpret_cast<void **>(&c->seg_bi),
                      reinterpret_cast<void **>(&c->blocks), reinterpret_cast<void **>(&c->cseg), reinterpret_cast<void **>(&c->dirs),
                      reinterpret_cast<void **>(&c->items), reinterpret_cast<void **>(&c->pairs),
@@ -539,16 +528,18 @@ bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3
     // one plan for both precisions: a band's LDS is budgeted for the larger of the two; a grid whose
     // bands do not fit the usual budget (which keeps several workgroups per CU) takes the wide one
     std::string msg_wide;
-    if (!rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytes,
-                                plan, msg) &&
-        !rt3d::build_sweep_plan(g.nx, g.ny, g.nz, A, sh.threads * sh.lines, 16 * sh.threads, kWindowBytesWide,
-                                plan, msg_wide)) {
+    const int lines = sh.threads * sh.lines, target = 16 * sh.threads;
+    if (!rt3d::window_row_fits(lines, g.nx, msg)) return false;
+    rt3d::segment_plan(g.nx, g.ny, g.nz, A, plan);
+    if (!rt3d::window_bands(lines, target, kWindowBytes, plan, msg) &&
+        !rt3d::window_bands(lines, target, kWindowBytesWide, plan, msg_wide)) {
         msg = msg_wide;
         return false;
     }
-    // (the window plan decides above which grids are accepted, in either form)
-    if (columns)
-        rt3d::make_column_plan(A, sh.threads, sh.lines, load > 0.0 ? load : rt3d::column_load(g.nx, g.ny, g.nz, A), plan);
+    // (the window form's bands decide above which grids are accepted, in either form)
+    if (!columns ||
+        !rt3d::make_column_plan(A, sh.threads, sh.lines, load > 0.0 ? load : rt3d::column_load(g.nx, g.ny, g.nz, A), plan))
+        rt3d::window_plan(plan);
     return true;
 }
 
@@ -576,9 +567,7 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
         c->P = Pp;
     }
     chk(upload(c, &c->seg_len64, P.seg_len));
-    chk(upload(c, &c->seg_len32, std::vector<float>(P.seg_len.begin(), P.seg_len.end())));
     chk(upload(c, &c->seg_off, P.seg_off)); chk(upload(c, &c->seg_n, P.seg_n));
-    chk(upload(c, &c->seg_a, P.seg_a)); chk(upload(c, &c->seg_bb, P.seg_bb)); chk(upload(c, &c->seg_bm, P.seg_bm));
     chk(upload(c, &c->seg_ai, P.seg_ai)); chk(upload(c, &c->seg_bi, P.seg_bi));
     chk(upload(c, &c->blocks, P.blocks)); chk(upload(c, &c->cseg, P.cseg));
     chk(upload(c, &c->dirs, P.dirs)); chk(upload(c, &c->items, P.items)); chk(upload(c, &c->pairs, P.pairs));
