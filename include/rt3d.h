@@ -19,7 +19,9 @@
  * every sweep bottom first instead of alternating; same iterates), RT3D_JACOBI_COLUMN (voxels per
  * thread of the column layout, 1, 2 or 4; default by grid size; same iterates), RT3D_JACOBI_WALK
  * (1: odd column layers walk top down, 0: never, -1 (default): for float coefficients in columns of 4;
- * same iterates), RT3D_ANCHOR_RATIO (re-anchoring ratio of the RT3D_FP32_SWEEP form, default 1e-2).
+ * same iterates), RT3D_ANCHOR_RATIO (re-anchoring ratio of the RT3D_FP32_SWEEP form, default 1e-2),
+ * RT3D_DEVICE_BYTES (the most device memory that a context, or a batch's members when it is created,
+ * may hold: beyond it allocations fail as they do when the device has no more; default no limit).
  *
  * Discretisation (the paper defers it to earlier papers of its series; these are the readings):
  *   voxels    unit cubes (i,j,k), i fastest; k = 0 is the bottom (inner boundary), k = nz-1 the top;
@@ -95,6 +97,9 @@ typedef struct rt3d_ctx rt3d_ctx;
  * 1024 for up to 24 x 24 angles, 832 for 32 x 32 and 587 for 48 x 48 (ny and nz are limited by
  * memory only).
  * rt3d_validate checks the same without a device.
+ * Where device memory does not suffice, here or for what a later call allocates, the sweep plan is replaced
+ * by one with smaller partial planes: first the same sums with fewer, longer chains of work, then that of
+ * wider rows, whose sums differ by rounding (rt3d_get_stats: "plan_level" 0, 1, 2).
  * Errors: RT3D_ERR_ARG (bad descriptor or precision, out == NULL, a grid beyond the sweep's limits),
  * RT3D_ERR_OOM, RT3D_ERR_HIP; the reason is in rt3d_last_error(NULL). */
 int rt3d_create(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, void *hip_stream);

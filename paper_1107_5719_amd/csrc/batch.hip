@@ -925,9 +925,20 @@ int rt3d_batch_create(rt3d_batch **out, int n_members, const rt3d_grid_desc *des
         if (rt3d::make_angle_set(descs[i].n_theta, descs[i].n_phi, A))
             load += rt3d::column_load(descs[i].nx, descs[i].ny, descs[i].nz, A);
     }
-    for (int i = 0; i < n_members && !rc; ++i) {
-        rc = create_ctx(&b->m[i], &descs[i], precision, b->stream, sweep_shape, msg, load);
-        if (rc) msg = "member " + std::to_string(i) + ": " + msg;
+    // where device memory does not suffice for all members, they all take a plan with smaller partial planes
+    for (int level = 0; level <= 2; ++level) {
+        size_t bytes = 0;
+        rc = RT3D_OK;
+        for (int i = 0; i < n_members && !rc; ++i) {
+            rc = create_ctx(&b->m[i], &descs[i], precision, b->stream, sweep_shape, msg, load, level, bytes);
+            if (rc) msg = "member " + std::to_string(i) + ": " + msg;
+            else bytes += b->m[i]->device_bytes;
+        }
+        if (rc != RT3D_ERR_OOM || level == 2) break;
+        for (rt3d_ctx *&c : b->m) {
+            rt3d_destroy(c);
+            c = nullptr;
+        }
     }
     if (!rc) {
         rc = build_tables(b);

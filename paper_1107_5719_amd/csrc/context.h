@@ -32,6 +32,10 @@ struct rt3d_ctx {
     int lstar_early_exit = 0;
     int sweep_shape = 0;       // index into kSweepShapes
     double sweep_load = 0.0;   // work of the launch that holds this context's sweep (0: its own; see column_load)
+    // Plans from this level on are tried: 0 splits pairs as the load asks, 1 none, 2 takes the window form (65^3 x 256: partial
+    // planes of 609, 406 and 375 MB).  Raised where device memory does not suffice.
+    int plan_level = 0;
+    size_t bytes_max = 0;      // device bytes that the context may hold (0: no limit)
     int os_method = RT3D_OS_JACOBI;   // inner solve of the OS step
     double anchor_ratio = kAnchorRatioDefault;   // FP32 form: re-anchor when c < ratio * max|J - Ja|/|J|
     int jacobi_xcd = 4;        // Jacobi grid: 0 plain, 1 chunks padded to 8 per plane, 2 contiguous chunk
@@ -133,17 +137,20 @@ hipMemcpyKind kind_in(int ptr_kind);
 hipMemcpyKind kind_out(int ptr_kind);
 int n_sweep_shapes();
 
-// New context with the given sweep shape (index into the shape table); stream may be null.
+// New context with the given sweep shape (index into the shape table); stream may be null.  load, plan_level: as the
+// fields; others: device bytes that the limit also covers (a batch's earlier members).
 int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream_t stream, int shape,
-               std::string &msg, double load = 0.0);
+               std::string &msg, double load = 0.0, int plan_level = 0, size_t others = 0);
 // The sweep plan of a grid and angle set for a shape, on the host (no device work); false with the
 // reason in msg when the grid does not fit the sweep kernel's line and LDS budgets.
-// load: as rt3d_ctx::sweep_load.  columns: take the column form of the sweep where the grid allows it.
+// load, level: as rt3d_ctx::sweep_load, plan_level.
 bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3d::SweepPlan &plan,
-                std::string &msg, double load = 0.0, bool columns = true);
+                std::string &msg, double load = 0.0, int level = 0);
 // (Re)build the sweep plan for a shape (or take the given one) and upload its tables; Lambda* and
 // the state are kept.
 int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built = nullptr);
+// Installs the plan of the next level whose partial planes are smaller; false when there is none
+bool shrink_plan(rt3d_ctx *c);
 // Message of the calling thread's last failed context or batch creation ("" after a success).
 void set_thread_error(const std::string &msg);
 const char *thread_error();
@@ -161,17 +168,28 @@ std::string device_key();
         if (e_ != hipSuccess) return rt3d_host::hip_fail(ctx, e_, what); \
     } while (0)
 
+// Device memory of a context; where it is short, the sweep plan gives up what a smaller one does without.
 template <typename T>
 int dev_alloc(rt3d_ctx *c, T **p, size_t count)
 {
     const size_t bytes = (count ? count : 1) * sizeof(T);
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
-    if (e != hipSuccess) {
+    while (true) {
+        int rc = RT3D_OK;
         *p = nullptr;
-        return hip_fail(c, e, "hipMalloc");
+        if (c->bytes_max && c->device_bytes + bytes > c->bytes_max) {
+            rc = fail(c, RT3D_ERR_OOM, "the limit on device memory (RT3D_DEVICE_BYTES) is reached");
+        } else {
+            const hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+            if (e != hipSuccess) {
+                *p = nullptr;
+                hipGetLastError();         // the next launch's check must not find this one
+                rc = hip_fail(c, e, "hipMalloc");
+            }
+        }
+        if (rc == RT3D_ERR_OOM && shrink_plan(c)) continue;
+        if (!rc) c->device_bytes += bytes;
+        return rc;
     }
-    c->device_bytes += bytes;
-    return RT3D_OK;
 }
 
 template <typename T>

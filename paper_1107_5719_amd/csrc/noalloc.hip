@@ -146,7 +146,7 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     // for the shallowest directions smaller still in the window form: grids that only fit so take it
     for (int t = 0; t < 2 && n_range == 0 && plan.columns; ++t) {
         plan = rt3d::SweepPlan();
-        if (!build_plan(*g, A, 0, plan, msg, t == 0 ? 1e30 : 0.0, t == 0)) return noalloc_fail(RT3D_ERR_ARG, msg);
+        if (!build_plan(*g, A, 0, plan, msg, 0.0, t + 1)) return noalloc_fail(RT3D_ERR_ARG, msg);
         n_range = ranges();
     }
     if (fixed >= kScratchBytes)

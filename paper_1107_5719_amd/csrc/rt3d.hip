@@ -521,7 +521,7 @@ void free_plan(rt3d_ctx *c)
 }
 
 bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3d::SweepPlan &plan,
-                std::string &msg, double load, bool columns)
+                std::string &msg, double load, int level)
 {
     if (shape < 0 || shape >= n_sweep_shapes()) { msg = "sweep shape out of range"; return false; }
     const SweepShape sh = kSweepShapes[shape];
@@ -537,11 +537,53 @@ bool build_plan(const rt3d_grid_desc &g, const rt3d::AngleSet &A, int shape, rt3
         return false;
     }
     // (the window form's bands decide above which grids are accepted, in either form)
-    if (!columns ||
-        !rt3d::make_column_plan(A, sh.threads, sh.lines, load > 0.0 ? load : rt3d::column_load(g.nx, g.ny, g.nz, A), plan))
-        rt3d::window_plan(plan);
+    if (level == 1) load = 1e30;      // (a launch that large splits no pair)
+    else if (!(load > 0.0)) load = rt3d::column_load(g.nx, g.ny, g.nz, A);
+    if (level > 1 || !rt3d::make_column_plan(A, sh.threads, sh.lines, load, plan)) rt3d::window_plan(plan);
     return true;
 }
+
+namespace {
+
+int upload_plan(rt3d_ctx *c)
+{
+    const auto &P = c->plan;
+    const size_t before = c->device_bytes;
+    int rc = RT3D_OK;
+    auto chk = [&](int r) { if (!rc) rc = r; };
+    {
+        double *Pp = nullptr;
+        chk(dev_alloc(c, &Pp, size_t(std::max(P.p_elems, lstar_scratch(P)))));
+        c->P = Pp;
+    }
+    if (!rc) chk(upload(c, &c->seg_len64, P.seg_len));
+    if (!rc) chk(upload(c, &c->seg_off, P.seg_off));
+    if (!rc) chk(upload(c, &c->seg_n, P.seg_n));
+    if (!rc) chk(upload(c, &c->seg_ai, P.seg_ai));
+    if (!rc) chk(upload(c, &c->seg_bi, P.seg_bi));
+    if (!rc) chk(upload(c, &c->blocks, P.blocks));
+    if (!rc) chk(upload(c, &c->cseg, P.cseg));
+    if (!rc) chk(upload(c, &c->dirs, P.dirs));
+    if (!rc) chk(upload(c, &c->items, P.items));
+    if (!rc) chk(upload(c, &c->pairs, P.pairs));
+    if (!rc) chk(upload(c, &c->pseg, P.pseg));
+    if (!rc) chk(upload(c, &c->player, P.player));
+    c->plan_bytes = c->device_bytes - before;
+    if (rc) free_plan(c);
+    else c->plan_ok = true;
+    return rc;
+}
+
+// The plan of the next level above c's whose partial planes are smaller than those of c's plan
+bool smaller_plan(const rt3d_ctx *c, rt3d::SweepPlan &plan, int &level)
+{
+    std::string msg;
+    for (level = c->plan_level + 1; level <= 2 && c->plan.columns; ++level)
+        if (build_plan(c->g, c->A, c->sweep_shape, plan, msg, c->sweep_load, level) && plan.p_elems < c->plan.p_elems) return true;
+    return false;
+}
+
+}  // namespace
 
 int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
 {
@@ -551,38 +593,36 @@ int install_plan(rt3d_ctx *c, int shape, rt3d::SweepPlan *built)
         plan = std::move(*built);
     } else {
         std::string msg;
-        if (!build_plan(c->g, c->A, shape, plan, msg, c->sweep_load)) return fail(c, RT3D_ERR_ARG, msg);
+        if (!build_plan(c->g, c->A, shape, plan, msg, c->sweep_load, c->plan_level)) return fail(c, RT3D_ERR_ARG, msg);
     }
     int rc = sync(c);
     if (rc) return rc;
     free_plan(c);
-    c->plan = std::move(plan);
     c->sweep_shape = shape;
-    const auto &P = c->plan;
-    const size_t before = c->device_bytes;
-    auto chk = [&](int r) { if (!rc) rc = r; };
-    {
-        double *Pp = nullptr;
-        chk(dev_alloc(c, &Pp, size_t(std::max(P.p_elems, lstar_scratch(P)))));
-        c->P = Pp;
-    }
-    chk(upload(c, &c->seg_len64, P.seg_len));
-    chk(upload(c, &c->seg_off, P.seg_off)); chk(upload(c, &c->seg_n, P.seg_n));
-    chk(upload(c, &c->seg_ai, P.seg_ai)); chk(upload(c, &c->seg_bi, P.seg_bi));
-    chk(upload(c, &c->blocks, P.blocks)); chk(upload(c, &c->cseg, P.cseg));
-    chk(upload(c, &c->dirs, P.dirs)); chk(upload(c, &c->items, P.items)); chk(upload(c, &c->pairs, P.pairs));
-    chk(upload(c, &c->pseg, P.pseg)); chk(upload(c, &c->player, P.player));
-    c->plan_bytes = c->device_bytes - before;
-    if (rc) {
-        free_plan(c);
-        return rc;
-    }
-    c->plan_ok = true;
-    return RT3D_OK;
+    const int level0 = c->plan_level;
+    int level = level0;
+    do {
+        c->plan = std::move(plan);
+        c->plan_level = level;
+        rc = upload_plan(c);
+    } while (rc == RT3D_ERR_OOM && smaller_plan(c, plan, level));
+    if (rc) c->plan_level = level0;
+    return rc;
+}
+
+bool shrink_plan(rt3d_ctx *c)
+{
+    rt3d::SweepPlan plan;
+    int level;
+    if (!c->plan_ok || !smaller_plan(c, plan, level) || sync(c) != RT3D_OK) return false;
+    free_plan(c);
+    c->plan = std::move(plan);
+    c->plan_level = level;
+    return upload_plan(c) == RT3D_OK;
 }
 
 int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream_t stream, int shape,
-               std::string &msg, double load)
+               std::string &msg, double load, int plan_level, size_t others)
 {
     *out = nullptr;
     if (validate_desc(g, msg) != RT3D_OK) return RT3D_ERR_ARG;
@@ -594,13 +634,14 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
     c->precision = precision;
     c->stream = stream;
     c->sweep_load = load;
+    c->plan_level = plan_level;
     c->jacobi_tile = rt3d::choose_jacobi_tile(g->nx, g->ny, g->nz);
     c->real_size = (precision == RT3D_FP64) ? sizeof(double) : sizeof(float);
     c->V = long(g->nx) * g->ny * g->nz;
     if (!rt3d::make_angle_set(g->n_theta, g->n_phi, c->A)) { delete c; msg = "bad angle set"; return RT3D_ERR_ARG; }
     // the sweep plan first: a grid that does not fit the sweep kernel fails before any allocation
     rt3d::SweepPlan plan;
-    if (!build_plan(*g, c->A, shape, plan, msg, load)) { delete c; return RT3D_ERR_ARG; }
+    if (!build_plan(*g, c->A, shape, plan, msg, load, plan_level)) { delete c; return RT3D_ERR_ARG; }
     if (const char *e = std::getenv("RT3D_JACOBI_XCD")) c->jacobi_xcd = std::max(0, std::min(4, std::atoi(e)));
     if (const char *e = std::getenv("RT3D_JACOBI_ALTERNATE")) c->jacobi_alternate = std::atoi(e) != 0;
     if (const char *e = std::getenv("RT3D_JACOBI_COLUMN")) {
@@ -608,6 +649,10 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
         c->jacobi_height = (h == 1 || h == 2 || h == 4) ? h : 0;
     }
     if (const char *e = std::getenv("RT3D_JACOBI_WALK")) c->jacobi_walk = std::max(-1, std::min(1, std::atoi(e)));
+    if (const char *e = std::getenv("RT3D_DEVICE_BYTES")) {
+        const double most = std::atof(e);
+        if (most > 0.0) c->bytes_max = most > double(others) ? size_t(most) - others : 1;
+    }
     if (const char *e = std::getenv("RT3D_ANCHOR_RATIO")) c->anchor_ratio = std::max(0.0, std::atof(e));
     // Lambda* walk may stop at the first non-neighbour only if no line wraps back within two layers
     {
@@ -1177,14 +1222,14 @@ int rt3d_get_stats(rt3d_ctx *c, char *buf, int buflen)
                   "\"nx\":%d,\"ny\":%d,\"nz\":%d,\"n_dir\":%d,\"precision\":\"%s\",\"outer_iters\":%ld,"
                   "\"inner_sweeps\":%ld,\"fp64_sweeps\":%ld,\"fp32_sweeps\":%ld,\"device_bytes\":%zu,\"partial_plane_bytes\":%lld,"
                   "\"sweep_workgroups\":%zu,\"sweep_shape\":%d,\"sweep_threads\":%d,\"sweep_lines\":%d,\"mean_segments\":%.6f,"
-                  "\"max_window_rows\":%d,\"sweep_lds_bytes\":%zu,"
+                  "\"max_window_rows\":%d,\"sweep_lds_bytes\":%zu,\"plan_level\":%d,"
                   "\"os_method\":\"%s\",\"coef_storage\":\"%s\",\"jacobi_layout\":%d,\"jacobi_column\":%d,\"jacobi_alt_walk\":%d,"
                   "\"timing\":%d,\"kernels\":{",
                   c->g.nx, c->g.ny, c->g.nz, c->A.n_dir, c->precision == RT3D_FP64 ? "fp64" : "fp32_sweep",
                   c->outer_iters, c->inner_sweeps, c->fp64_sweeps, c->fp32_sweeps, c->device_bytes,
                   (long long)(c->plan.p_elems * (long long)sizeof(double)), c->plan.items.size(),
                   c->sweep_shape, kSweepShapes[c->sweep_shape].threads, kSweepShapes[c->sweep_shape].lines, c->plan.mean_segments,
-                  c->plan.max_win_rows, sweep_smem_bytes(c->plan, c->precision != RT3D_FP64),
+                  c->plan.max_win_rows, sweep_smem_bytes(c->plan, c->precision != RT3D_FP64), c->plan_level,
                   c->os_method == RT3D_OS_GAUSS_SEIDEL ? "gauss_seidel" : "jacobi", c->coef_fp32 ? "fp32" : "fp64",
                   c->jacobi_xcd, jcol,
                   (c->jacobi_xcd == 4 && jacobi_alt_walk(c->jacobi_walk, c->coef_fp32 != 0, jcol)) ? 1 : 0, c->timing);
