@@ -542,6 +542,127 @@ bool make_column_plan(const AngleSet &A, int threads, int lines, double load, Sw
     return true;
 }
 
+namespace {
+
+// Elements of pair q's partial planes of the layer at a step (column form)
+int64_t layer_elems(const SweepPlan &P, int q, int step)
+{
+    const PairInfo &pi = P.pairs[q];
+    const int rows = pi.split ? 1 : kColumnRows, k = pi.down ? P.nz - 1 - step : step;
+    return int64_t(rows + P.blocks[size_t(k) * P.n_pair + q].span) * P.nx * ((P.ny + rows - 1) / rows);
+}
+
+}  // namespace
+
+std::vector<LayerStart> layer_starts(const SweepPlan &P)
+{
+    std::vector<LayerStart> start(P.blocks.size());
+    for (int q = 0; q < P.n_pair; ++q) {
+        int s = P.pairs[q].c_off;
+        for (int step = 0; step < P.nz; ++step) {
+            const int k = P.pairs[q].down ? P.nz - 1 - step : step;
+            const size_t ka = size_t(P.pairs[q].dA) * P.nz + k;
+            start[size_t(k) * P.n_pair + q] = LayerStart{s, pos_mod(P.seg_bi[P.seg_off[ka]], P.ny)};
+            s += P.seg_n[ka];
+        }
+    }
+    return start;
+}
+
+int64_t lay_out(SweepPlan &P, const SweepPart &part)
+{
+    int64_t off = 0;
+    if (!P.columns) {
+        for (int q = part.q0; q < part.q1; ++q) {
+            PairInfo &pi = P.pairs[q];
+            for (int k = 0; k < P.nz; ++k) P.blocks[size_t(k) * P.n_pair + q].off += off - pi.p_off;
+            pi.p_off = off;
+            off += pi.n_bands * pi.band_stride;
+        }
+        return off;
+    }
+    for (int q = part.q0; q < part.q1; ++q) {
+        PairInfo &pi = P.pairs[q];
+        const int rows = pi.split ? 1 : kColumnRows, n = (P.ny + rows - 1) / rows;
+        int64_t block = 0;
+        for (int pass = 0; pass < 2; ++pass) {
+            // first the rows of a band (line row) in all layers, then every layer's place
+            int64_t at = 0;
+            for (int step = part.step0; step < part.step0 + part.layers; ++step) {
+                LayerBlock &lb = P.blocks[size_t(pi.down ? P.nz - 1 - step : step) * P.n_pair + q];
+                if (pass == 1) {
+                    lb.off = off + at;
+                    lb.stride = int(block / P.nx);
+                }
+                at += int64_t(rows + lb.span) * P.nx;
+            }
+            block = at;
+        }
+        if (part.layers == P.nz) {
+            pi.p_off = off;
+            pi.band_stride = block;
+        }
+        off += n * block;
+    }
+    return off;
+}
+
+std::vector<SweepPart> layer_parts(const SweepPlan &P, int64_t room)
+{
+    std::vector<SweepPart> parts;
+    for (int run0 = 0; run0 < P.n_pair;) {
+        int run1 = run0;
+        while (run1 < P.n_pair && P.pairs[run1].down == P.pairs[run0].down) ++run1;
+        for (int group = run1 - run0;; group = (group + 1) / 2) {
+            const size_t before = parts.size();
+            const int64_t free = room - int64_t(group) * 2 * P.nx * P.ny;
+            bool fits = true;
+            for (int q0 = run0; q0 < run1 && fits; q0 += group) {
+                const int q1 = std::min(q0 + group, run1);
+                std::vector<int64_t> elems(P.nz, 0);
+                int64_t sum = 0;
+                for (int step = 0; step < P.nz; ++step) {
+                    for (int q = q0; q < q1; ++q) elems[step] += layer_elems(P, q, step);
+                    sum += elems[step];
+                }
+                if (sum <= room) {
+                    parts.push_back(SweepPart{q0, q1, 0, P.nz, P.pairs[q0].down != 0});
+                    continue;
+                }
+                for (int step = 0; step < P.nz && fits;) {
+                    int n = 0;
+                    int64_t used = 0;
+                    while (step + n < P.nz && used + elems[step + n] <= free) used += elems[step + n++];
+                    fits = n >= (group > 1 ? std::min(2, P.nz - step) : 1);
+                    parts.push_back(SweepPart{q0, q1, step, n, P.pairs[q0].down != 0});
+                    step += n;
+                }
+            }
+            if (fits) break;
+            parts.resize(before);
+            if (group == 1) return {};
+        }
+        run0 = run1;
+    }
+    return parts;
+}
+
+std::vector<SweepPart> pair_parts(const SweepPlan &P, int64_t room)
+{
+    std::vector<SweepPart> parts;
+    for (int q = 0; q < P.n_pair;) {
+        int q1 = q;
+        for (int64_t used = 0; q1 < P.n_pair; ++q1) {
+            used += P.pairs[q1].n_bands * P.pairs[q1].band_stride;
+            if (used > room) break;
+        }
+        if (q1 == q) return {};
+        parts.push_back(SweepPart{q, q1, 0, P.nz});
+        q = q1;
+    }
+    return parts;
+}
+
 JacobiTile choose_jacobi_tile(int nx, int ny, int nz)
 {
     // A launch takes about 2 us, 3 more for each round of workgroups (24 wavefronts of a CU at once), and for each

@@ -171,6 +171,29 @@ double column_load(int nx, int ny, int nz, const AngleSet &A);
 // Cycles per segment of a wavefront of the column form that has its SIMD to itself, with rows line rows
 inline double column_segment_cycles(int rows) { return 450.0 + 165.0 * rows; }
 
+// A part of a sweep whose partial planes do not all fit a buffer: layers [step0, step0 + layers), counted in sweep order, of
+// direction pairs [q0, q1); its work items in a list.
+struct SweepPart {
+    int q0, q1, step0, layers;
+    bool down = false;
+    int item0 = 0, n_items = 0;
+};
+// Parts of layers (column form) of as many pairs of one vertical direction as leave room for two layers (one, where it is a
+// single pair); empty where that does not fit.  room: elements for the partial planes and the lines' intensities.
+std::vector<SweepPart> layer_parts(const SweepPlan &plan, int64_t room);
+// Parts of pairs, all their layers (window form)
+std::vector<SweepPart> pair_parts(const SweepPlan &plan, int64_t room);
+// Gives the partial planes of a part's pairs and layers their places from the start of the buffer on; their elements.
+int64_t lay_out(SweepPlan &plan, const SweepPart &part);
+// Elements that the intensities of its lines take between parts
+inline int64_t line_elems(const SweepPlan &plan, const SweepPart &part)
+{
+    return part.layers < plan.nz ? int64_t(part.q1 - part.q0) * 2 * plan.nx * plan.ny : 0;
+}
+// Per (layer, pair) as SweepPlan::blocks: the layer's first segment in cseg and its row offset modulo ny
+struct LayerStart { int seg, row; };
+std::vector<LayerStart> layer_starts(const SweepPlan &plan);
+
 // The tile of a launch that does two Jacobi sweeps: a workgroup puts out tx x ty x z voxels.
 struct JacobiTile {
     int tx, ty, z;

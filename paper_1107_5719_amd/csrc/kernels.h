@@ -783,15 +783,15 @@ inline void launch_reduce_kernel(ReduceArgs &a, bool columns, bool f32, hipStrea
     }
 }
 
-// Direction pairs [q0, q1) only: starts from 0 (first) or from what a range before left, the sum of the whole
+// Direction pairs [q0, q1) and the layers from k0 on only: starts from 0 (first) or from what a range before left, the sum of the whole
 // chunks in Jfs and of the chunk begun in carry (may be null where there is one chunk: Jfs holds its sum
 // then), and finishes only when last, so ranges taken in order give bitwise the sum of one pass over all
 // pairs.
 template <bool COL>
-__global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_pair_range(ReduceArgs a, int q0, int q1, int first,
+__global__ __launch_bounds__(kPlaneThreads) void reduce_kernel_pair_range(ReduceArgs a, int q0, int q1, int k0, int first,
                                                                           int last, double *carry)
 {
-    const int k = blockIdx.y;
+    const int k = k0 + int(blockIdx.y);
     const ReduceVoxels r = reduce_voxels(a, int(blockIdx.x) * kPlaneThreads + int(threadIdx.x), k);
     if (!r.in) return;
     const bool one = a.chunk >= a.n_pair;

@@ -6,8 +6,12 @@
 // caller passes chi, S, the bottom-plane light and the output on the device, and everything else the
 // kernels need -- the packed {chi, S} field, the exponential's table, the plan's tables and the partial
 // planes of the direction pairs -- lives in one file-scope device array of kScratchBytes.  When the
-// partial planes of all pairs do not fit beside the rest, the pairs are swept in ranges that do, and
-// the angle sum is carried from range to range in J_fs in the order of a single pass.
+// partial planes of all pairs do not fit beside the rest, the sweep goes in parts and the angle sum is carried
+// from part to part in J_fs in the order of a single pass.  A part is some layers of all downward (then all upward)
+// pairs, whose lines leave their intensities in the array from part to part: as many lines are under way as in a
+// single pass, and a layer's planes are small.  In the window form (rows of more than 512 columns) a part is some pairs.
+// us per call, in parts of pairs and so: 65^3 x 256 3353 and 1765, 129^3 x 64 6600 and 1349, 129^3 x 256 31055 and 7015 (of which
+// the plan, made on the host in every call, was about 3000, 700 and 6000 and is half of that now).
 //
 // The array is a host-side stand-in in host code: the kernels get its device address, taken once per
 // device with hipGetSymbolAddress while that device is current, never the array's name.  Every call on
@@ -103,75 +107,68 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     const int nx = g->nx, ny = g->ny, nz = g->nz;
     const long V = long(nx) * ny * nz;
 
-    // workspace layout: exponential table, {chi, S}, pair tables, segments, layer blocks, work items of
-    // every range, then the partial planes of one range of pairs
+    // workspace layout: exponential table, {chi, S}, pair tables, segments, layer blocks and starts, work items, the
+    // carried sums and intensities, then the partial planes of one part
     std::vector<double> tab(kExpTabSize);
     exp_table(tab.data());
-    // the reduction's sum of a chunk of pairs that a range leaves unfinished
+    // the reduction's sum of a chunk of pairs that a part leaves unfinished
     const int chunk = reduce_chunk_pairs(V, plan.n_pair);
     const size_t carry_bytes = chunk < plan.n_pair ? align256(size_t(V) * sizeof(double)) : 0;
+    const size_t start_bytes = align256(plan.blocks.size() * sizeof(int2));
     size_t fixed = 0;
-    std::vector<int> q_begin;             // pair ranges [q_begin[r], q_begin[r + 1])
-    // ranges of pairs whose partial planes fit what the tables leave of the workspace; 0 where one pair's do
-    // not
-    auto ranges = [&]() {
+    auto measure = [&]() {
         if (!plan.columns) plan.cseg.clear();          // (not read by the window form)
         fixed = align256(tab.size() * sizeof(double)) + align256(size_t(V) * sizeof(double2)) +
                 align256(plan.pairs.size() * sizeof(rt3d::PairInfo)) +
                 align256(plan.player.size() * sizeof(rt3d::PairLayer)) +
                 align256(plan.pseg.size() * sizeof(rt3d::PairSeg)) +
                 align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg)) +
-                align256(plan.blocks.size() * sizeof(rt3d::LayerBlock)) +
+                align256(plan.blocks.size() * sizeof(rt3d::LayerBlock)) + (plan.columns ? start_bytes : 0) +
                 align256(plan.items.size() * sizeof(rt3d::WorkItem)) + carry_bytes;
-        q_begin.clear();
-        if (fixed >= kScratchBytes) return 0;
-        const size_t room = (kScratchBytes - fixed) / sizeof(double);
-        for (int q = 0; q < plan.n_pair;) {
-            const int64_t base = plan.pairs[q].p_off;
-            int q1 = q;
-            while (q1 < plan.n_pair) {
-                const int64_t end = q1 + 1 < plan.n_pair ? plan.pairs[q1 + 1].p_off : plan.p_elems;
-                if (size_t(end - base) > room) break;
-                ++q1;
-            }
-            if (q1 == q) return 0;
-            q_begin.push_back(q);
-            q = q1;
-        }
-        q_begin.push_back(plan.n_pair);
-        return int(q_begin.size()) - 1;
+        return fixed < kScratchBytes ? (kScratchBytes - fixed) / sizeof(double) : 0;
     };
-    int n_range = ranges();
-    // a pair's planes are smaller when it is not split (as in a large launch), with the same result, and
-    // for the shallowest directions smaller still in the window form: grids that only fit so take it
-    for (int t = 0; t < 2 && n_range == 0 && plan.columns; ++t) {
-        plan = rt3d::SweepPlan();
-        if (!build_plan(*g, A, 0, plan, msg, 0.0, t + 1)) return noalloc_fail(RT3D_ERR_ARG, msg);
-        n_range = ranges();
+    std::vector<rt3d::SweepPart> parts;
+    size_t room = measure();
+    if (int64_t(room) >= plan.p_elems) {
+        parts.push_back(rt3d::SweepPart{0, plan.n_pair, 0, nz});
+    } else if (plan.columns) {
+        // the launches hold half of the pairs; where a pair's planes of one layer do not fit, no pair is split
+        for (int t = 0; t < 2 && parts.empty(); ++t) {
+            rt3d::make_column_plan(A, kSweepShapes[0].threads, kSweepShapes[0].lines,
+                                   t == 0 ? 0.5 * rt3d::column_load(nx, ny, nz, A) : 1e30, plan);
+            room = measure();
+            parts = rt3d::layer_parts(plan, int64_t(room));
+        }
+        if (parts.empty() && room > 0) {
+            // few layers of very many rows, near the limit: only the window form's planes fit
+            if (!build_plan(*g, A, 0, plan, msg, 0.0, 2)) return noalloc_fail(RT3D_ERR_ARG, msg);
+            room = measure();
+        }
     }
-    if (fixed >= kScratchBytes)
+    if (parts.empty() && room > 0) parts = rt3d::pair_parts(plan, int64_t(room));
+    if (room == 0)
         return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution: its tables need " +
                                               std::to_string(fixed) + " of " + std::to_string(kScratchBytes) +
                                               " workspace bytes");
-    if (n_range == 0)
+    if (parts.empty())
         return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution: the partial "
                                           "planes of one direction pair exceed its workspace");
-    // the work items of each range, in the plan's dispatch order
+    std::vector<int2> start;
+    if (plan.columns)
+        for (const rt3d::LayerStart &ls : rt3d::layer_starts(plan)) start.push_back(make_int2(ls.seg, ls.row));
+    // the partial planes of every part from the start of the buffer, and the work items of its pairs in the plan's dispatch
+    // order (parts of the same pairs share them)
     std::vector<rt3d::WorkItem> items;
-    std::vector<int> item_begin;
-    for (int r = 0; r < n_range; ++r) {
-        item_begin.push_back(int(items.size()));
-        for (const rt3d::WorkItem &it : plan.items)
-            if (it.pair >= q_begin[r] && it.pair < q_begin[r + 1]) items.push_back(it);
-    }
-    item_begin.push_back(int(items.size()));
-    // the offsets of a pair's partial planes, taken from its range's first pair
-    for (int r = 0; r < n_range; ++r) {
-        const int64_t shift = plan.pairs[q_begin[r]].p_off;
-        for (int q = q_begin[r]; q < q_begin[r + 1]; ++q) {
-            plan.pairs[q].p_off -= shift;
-            for (int k = 0; k < nz; ++k) plan.blocks[size_t(k) * plan.n_pair + q].off -= shift;
-        }
+    for (size_t r = 0; r < parts.size(); ++r) {
+        rt3d::SweepPart &part = parts[r];
+        const bool same = r > 0 && parts[r - 1].q0 == part.q0;
+        part.item0 = same ? parts[r - 1].item0 : int(items.size());
+        if (!same)
+            for (const rt3d::WorkItem &it : plan.items)
+                if (it.pair >= part.q0 && it.pair < part.q1) items.push_back(it);
+        part.n_items = same ? parts[r - 1].n_items : int(items.size()) - part.item0;
+        if (rt3d::lay_out(plan, part) + rt3d::line_elems(plan, part) > int64_t(room))
+            return noalloc_fail(RT3D_ERR_ARG, "grid too large for the allocation-free formal solution");
     }
 
     void *base = nullptr;
@@ -185,9 +182,10 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     unsigned char *d_pseg = p;       p += align256(plan.pseg.size() * sizeof(rt3d::PairSeg));
     unsigned char *d_cseg = p;       p += align256(plan.cseg.size() * sizeof(rt3d::ColumnSeg));
     unsigned char *d_blocks = p;     p += align256(plan.blocks.size() * sizeof(rt3d::LayerBlock));
+    unsigned char *d_start = p;      p += plan.columns ? start_bytes : 0;
     unsigned char *d_items = p;      p += align256(plan.items.size() * sizeof(rt3d::WorkItem));
     double *d_carry = reinterpret_cast<double *>(p);   p += carry_bytes;
-    double *d_P = reinterpret_cast<double *>(p);
+    double *d_P = reinterpret_cast<double *>(p);       // room elements; a part's line intensities at their end
     // from here on an early return first drains the stream: the copies read this call's host tables
     auto drain_fail = [&](int code, const std::string &m) {
         hipStreamSynchronize(st);
@@ -195,7 +193,8 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     };
     if ((rc = upload(d_tab, tab, st)) || (rc = upload(d_pairs, plan.pairs, st)) ||
         (rc = upload(d_player, plan.player, st)) || (rc = upload(d_pseg, plan.pseg, st)) ||
-        (rc = upload(d_cseg, plan.cseg, st)) || (rc = upload(d_blocks, plan.blocks, st)) || (rc = upload(d_items, items, st)))
+        (rc = upload(d_cseg, plan.cseg, st)) || (rc = upload(d_blocks, plan.blocks, st)) ||
+        (rc = upload(d_start, start, st)) || (rc = upload(d_items, items, st)))
         return drain_fail(rc, thread_error());
     hipLaunchKernelGGL(pack_kernel, dim3(unsigned((V + kPlaneThreads - 1) / kPlaneThreads)), dim3(kPlaneThreads), 0,
                        st, V, chi, S, reinterpret_cast<double2 *>(d_cs));
@@ -217,25 +216,32 @@ int rt3d_formal_solution_noalloc(const rt3d_grid_desc *g, const double *chi, con
     sa.Iem = nullptr;
     sa.Iem_base = nullptr;
     sa.xtab = reinterpret_cast<const double *>(d_tab);
+
     ReduceArgs ra{};
     ra.nx = nx; ra.ny = ny; ra.nz = nz; ra.n_pair = plan.n_pair;
-
     ra.blocks = reinterpret_cast<const rt3d::LayerBlock *>(d_blocks);
     ra.P = d_P;
     ra.chi = chi;
     ra.Jfs = J_fs;
     ra.chunk = chunk;
     ra.waves = 1;
-    const dim3 red_grid(unsigned(((nx + 1) / 2 * ny + kPlaneThreads - 1) / kPlaneThreads), unsigned(nz));
-    for (int r = 0; r < n_range; ++r) {
-        const int n_items = item_begin[r + 1] - item_begin[r];
-        sa.items = reinterpret_cast<const rt3d::WorkItem *>(d_items) + item_begin[r];
-        if (n_items > 0)
-            launch_sweep_kernel(sa, plan, 0, n_items, false, st);
+    for (const rt3d::SweepPart &part : parts) {
+        sa.items = reinterpret_cast<const rt3d::WorkItem *>(d_items) + part.item0;
+        if (part.layers < nz) {
+            const LayerRange lr{part.down ? nz - 1 - part.step0 : part.step0, part.layers, part.q0, plan.n_pair, part.step0 == 0,
+                                ra.blocks, reinterpret_cast<const int2 *>(d_start), d_P + room - rt3d::line_elems(plan, part)};
+            hipLaunchKernelGGL(column_sweep_layers_kernel<double>, dim3(unsigned(part.n_items)), dim3(plan.block_threads),
+                               sweep_smem_bytes(plan, false), st, sa, lr);
+        } else {
+            launch_sweep_kernel(sa, plan, 0, part.n_items, false, st);
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return drain_fail(RT3D_ERR_HIP, std::string("sweep_kernel: ") + hipGetErrorString(e));
-        hipLaunchKernelGGL(plan.columns ? reduce_kernel_pair_range<true> : reduce_kernel_pair_range<false>, red_grid, dim3(kPlaneThreads), 0, st, ra, q_begin[r],
-                           q_begin[r + 1], r == 0 ? 1 : 0, r == n_range - 1 ? 1 : 0, d_carry);
+        const dim3 red_grid(unsigned(((nx + 1) / 2 * ny + kPlaneThreads - 1) / kPlaneThreads), unsigned(part.layers));
+        const int k0 = part.down ? nz - part.step0 - part.layers : part.step0;
+        hipLaunchKernelGGL(plan.columns ? reduce_kernel_pair_range<true> : reduce_kernel_pair_range<false>, red_grid,
+                           dim3(kPlaneThreads), 0, st, ra, part.q0, part.q1, k0, part.q0 == 0 ? 1 : 0,
+                           part.q1 == plan.n_pair ? 1 : 0, d_carry);
         e = hipGetLastError();
         if (e != hipSuccess) return drain_fail(RT3D_ERR_HIP, std::string("reduce_kernel: ") + hipGetErrorString(e));
     }

@@ -83,9 +83,19 @@ template <typename T> __device__ __forceinline__ T uniform_copy(const T &v)
     return r;
 }
 
-template <typename real, int R, bool PARTIAL>
+// A part of a sweep: n layers from k_first on in sweep order, of pairs q0 .. whose lines have left their intensities in state
+// ([pair - q0][P, M][line row][column], where the next segment starts) unless first, and leave them there.  The layers'
+// blocks hold only these layers.
+struct LayerRange {
+    int k_first, n, q0, n_pair, first;
+    const rt3d::LayerBlock *blocks;
+    const int2 *start;            // per (layer, pair), as blocks: the layer's first segment in the list, its row offset modulo ny
+    double *state;
+};
+
+template <typename real, int R, bool PARTIAL, bool LAYERS>
 __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkItem &it, const rt3d::PairInfo &pi,
-                                                 real *edge, const double *xtab)
+                                                 real *edge, const double *xtab, const LayerRange &lr)
 {
     using real2 = typename Vec2<real>::type;
     const unsigned nx = a.nx, ny = a.ny, plane = nx * ny;
@@ -109,7 +119,8 @@ __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkI
     unsigned rown = unsigned((yup ? j0 + R + pi.row0 : j0 + rows - 1 - R + pi.row0 + R * int(ny)) % int(ny)) * nx;
     const unsigned cb = unsigned(c) * unsigned(sizeof(real2));
     const int dk = pi.down ? -1 : 1;
-    const char *csk = reinterpret_cast<const char *>(static_cast<const real2 *>(a.cs) + long(pi.down ? a.nz - 1 : 0) * plane);
+    const char *csk = reinterpret_cast<const char *>(static_cast<const real2 *>(a.cs) +
+                                                     long(LAYERS ? lr.k_first : pi.down ? a.nz - 1 : 0) * plane);
     const long pstep = long(dk) * plane * long(sizeof(real2));
     real chi[R], S2[R], Pi[R], Mi[R];
     // deposits of the row that a slot is in: its own line's, and those of the slots that were there before
@@ -133,7 +144,18 @@ __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkI
             S2[r] = vl[r].y + vl[r].y;
         }
     };
-    {
+    // the lines' place in the state; slots beyond the band's last row have none
+    auto line_state = [&](int r) {
+        const int row = yup ? j0 + r : j0 + rows - 1 - r;
+        return lr.state + long(it.pair - lr.q0) * 2 * plane + long(min(max(row, 0), int(ny) - 1)) * nx + c;
+    };
+    if (LAYERS && !lr.first) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            Pi[r] = real(line_state(r)[0]);
+            Mi[r] = real(line_state(r)[plane]);
+        }
+    } else {
         unsigned x = rown;
 #pragma unroll
         for (int r = R - 1; r >= 0; --r) {
@@ -166,7 +188,7 @@ __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkI
     auto store_row = [&](real v, unsigned drop) { buffer_store(v, prsrc, pw | drop); pw += pstep_row; };
     bool moved = false;
     int buf = 0, s = 0;
-    for (int layer = 0; layer < a.nz; ++layer) {
+    for (int layer = 0; layer < (LAYERS ? lr.n : a.nz); ++layer) {
         load_layer();
 #pragma unroll
         for (int r = 0; r < R; ++r) now[r] = before[r] = real(0);
@@ -240,6 +262,22 @@ __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkI
         pw = pbase + (yup ? 0u : unsigned(cover - 1 - (R - rows)) * nx * unsigned(sizeof(real)));
         csk += pstep;
     }
+    if constexpr (LAYERS) {
+        if (moved) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) Pi[r] = from_lo[buf + r];
+#pragma unroll
+            for (int r = 0; r < R; ++r) Mi[r] = from_hi[buf + r];
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!active || (PARTIAL && r >= rows)) continue;
+            line_state(r)[0] = double(Pi[r]);
+            line_state(r)[plane] = double(Mi[r]);
+        }
+        return;
+    }
     if (!pi.down && a.Iem && active) {
         const int sa = pi.sa_last;
         // the last segment's column is c: the lines of A entered the top at column c - sa, of B at c + sa
@@ -256,28 +294,41 @@ __device__ __forceinline__ void column_sweep_run(const SweepArgs &a, const WorkI
     }
 }
 
-template <typename real, int R>
+template <typename real, int R, bool LAYERS>
 __device__ __forceinline__ void column_sweep_rows(const SweepArgs &a, const WorkItem &it, const rt3d::PairInfo &pi,
-                                                  real *edge, const double *xtab)
+                                                  real *edge, const double *xtab, const LayerRange &lr)
 {
     const int w0 = __builtin_amdgcn_readfirstlane(int(threadIdx.x) & ~63);
     if (w0 >= it.rows * a.nx) return;      // a wave without lines
     // bands of this wave that reach beyond the grid's last row
     const int last = min(w0 + 63, it.rows * a.nx - 1) / a.nx;
-    if ((it.band + last + 1) * R > a.ny) column_sweep_run<real, R, true>(a, it, pi, edge, xtab);
-    else column_sweep_run<real, R, false>(a, it, pi, edge, xtab);
+    if ((it.band + last + 1) * R > a.ny) column_sweep_run<real, R, true, LAYERS>(a, it, pi, edge, xtab, lr);
+    else column_sweep_run<real, R, false, LAYERS>(a, it, pi, edge, xtab, lr);
 }
 
-template <typename real>
-__device__ __forceinline__ void column_sweep_body(const SweepArgs &a, const WorkItem &it, unsigned char *smem_raw)
+template <typename real, bool LAYERS = false>
+__device__ __forceinline__ void column_sweep_body(const SweepArgs &a, const WorkItem &it, unsigned char *smem_raw,
+                                                  const LayerRange &lr = LayerRange{})
 {
-    const rt3d::PairInfo pi = uniform_copy(a.pairs[it.pair]);
+    rt3d::PairInfo pi = uniform_copy(a.pairs[it.pair]);
+    if constexpr (LAYERS) {
+        // the pair as if the range's layers were all
+        const long at = long(lr.k_first) * lr.n_pair + it.pair;
+        const rt3d::LayerBlock lb = uniform_copy(lr.blocks[at]);
+        const int2 start = uniform_copy(lr.start[at]);
+        pi.n_seg -= start.x - pi.c_off;
+        pi.c_off = start.x;
+        pi.row0 = start.y;
+        pi.cover0 = lb.span + (pi.split ? 1 : rt3d::kColumnRows);
+        pi.p_off = lb.off;
+        pi.band_stride = long(lb.stride) * a.nx;
+    }
     __shared__ double xtab[kExpTab];
     if (std::is_same<real, double>::value && threadIdx.x < kExpTab) xtab[threadIdx.x] = a.xtab[threadIdx.x];
     __syncthreads();
     real *edge = reinterpret_cast<real *>(smem_raw);
-    if (pi.split) column_sweep_rows<real, 1>(a, it, pi, edge, xtab);
-    else column_sweep_rows<real, rt3d::kColumnRows>(a, it, pi, edge, xtab);
+    if (pi.split) column_sweep_rows<real, 1, LAYERS>(a, it, pi, edge, xtab, lr);
+    else column_sweep_rows<real, rt3d::kColumnRows, LAYERS>(a, it, pi, edge, xtab, lr);
 }
 
 template <typename real>
@@ -285,6 +336,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
 {
     extern __shared__ unsigned char smem_raw[];
     column_sweep_body<real>(a, uniform_copy(a.items[blockIdx.x]), smem_raw);
+}
+
+template <typename real>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void column_sweep_layers_kernel(SweepArgs a, LayerRange lr)
+{
+    extern __shared__ unsigned char smem_raw[];
+    column_sweep_body<real, true>(a, uniform_copy(a.items[blockIdx.x]), smem_raw, lr);
 }
 
 }  // namespace
