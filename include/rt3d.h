@@ -307,8 +307,9 @@ int rt3d_set_sweep_shape(rt3d_ctx *ctx, int shape);
 
 /* Autotuner of the sweep shape.  Times `repeats` formal solutions (from the current J, in the
  * context's precision) for every shape that fits the grid, installs the fastest and, when
- * cache_path is neither NULL nor empty, records it in a JSON cache keyed by device, precision and
- * grid.  When the cache already holds the key, its shape is installed without measuring.
+ * cache_path is neither NULL nor empty, records it in a JSON cache keyed by device, precision,
+ * grid and form of the sweep; shapes that run the same kernels (with rows of up to 512 columns most do) are timed once, and
+ * of equal shapes the first is taken.  When the cache already holds the key, its shape is installed without measuring.
  * *shape_out (may be NULL) receives the shape; ms_out (may be NULL, one entry per shape) the
  * milliseconds per formal solution, -1 where not measured.  Overwrites J_fs and the emergent
  * intensities.  Errors: RT3D_ERR_STATE (no medium), RT3D_ERR_ARG (repeats < 1, unwritable

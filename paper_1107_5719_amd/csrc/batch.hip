@@ -1221,6 +1221,7 @@ int rt3d_batch_autotune(rt3d_batch *b, const char *cache_path, int repeats, int 
         key += (i ? "," : "") + grids[i] + "*" + std::to_string(j - i);
         i = j;
     }
+    if (std::any_of(b->m.begin(), b->m.end(), [](const rt3d_ctx *c) { return c->plan.columns; })) key += rt3d_tune::kColumnKey;
     int cached = -1;
     if (cache_path && *cache_path && rt3d_tune::lookup(cache_path, key, cached) && cached >= 0 && cached < ns) {
         if (cached != b->shape) {
@@ -1235,11 +1236,20 @@ int rt3d_batch_autotune(rt3d_batch *b, const char *cache_path, int repeats, int 
     BHIP_TRY(b, hipEventCreate(&e0), "hipEventCreate");
     if (hipEventCreate(&e1) != hipSuccess) { hipEventDestroy(e0); return bfail(b, RT3D_ERR_HIP, "hipEventCreate"); }
     std::vector<double> ms(ns, INFINITY);
+    std::vector<std::pair<int, std::vector<rt3d::SweepKind>>> timed;
     int rc = RT3D_OK;
     for (int s = 0; s < ns && !rc; ++s) {
         const int r = rt3d_batch_set_sweep_shape(b, s);
         if (r == RT3D_ERR_ARG) continue;      // the shape does not fit some member's grid
         if (r) { rc = r; break; }
+        std::vector<rt3d::SweepKind> kinds;
+        for (const rt3d_ctx *c : b->m) kinds.emplace_back(c->plan);
+        const auto same = std::find_if(timed.begin(), timed.end(), [&](const auto &t) { return t.second == kinds; });
+        if (same != timed.end()) {
+            ms[s] = ms[same->first];
+            continue;
+        }
+        timed.push_back({s, std::move(kinds)});
         rc = rt3d_batch_formal_solution(b);   // warm-up
         if (!rc && hipEventRecord(e0, b->stream) != hipSuccess) rc = bfail(b, RT3D_ERR_HIP, "hipEventRecord");
         for (int k = 0; k < repeats && !rc; ++k) rc = rt3d_batch_formal_solution(b);

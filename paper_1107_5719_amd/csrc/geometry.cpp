@@ -554,6 +554,12 @@ int64_t layer_elems(const SweepPlan &P, int q, int step)
 
 }  // namespace
 
+SweepKind::SweepKind(const SweepPlan &plan) : columns(plan.columns), block_threads(plan.block_threads)
+{
+    for (const PairInfo &pi : plan.pairs) split.push_back(pi.split);
+    for (const WorkItem &it : plan.items) items.insert(items.end(), {it.pair, it.band, it.rows});
+}
+
 std::vector<LayerStart> layer_starts(const SweepPlan &P)
 {
     std::vector<LayerStart> start(P.blocks.size());

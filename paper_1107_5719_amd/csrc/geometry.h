@@ -171,6 +171,18 @@ double column_load(int nx, int ny, int nz, const AngleSet &A);
 // Cycles per segment of a wavefront of the column form that has its SIMD to itself, with rows line rows
 inline double column_segment_cycles(int rows) { return 450.0 + 165.0 * rows; }
 
+// What the launches of a column plan depend on; two shapes whose plans agree in it run the same kernels.
+struct SweepKind {
+    bool columns = false;
+    int block_threads = 0;
+    std::vector<int> split, items;
+    explicit SweepKind(const SweepPlan &plan);
+    bool operator==(const SweepKind &o) const
+    {
+        return columns && o.columns && block_threads == o.block_threads && split == o.split && items == o.items;
+    }
+};
+
 // A part of a sweep whose partial planes do not all fit a buffer: layers [step0, step0 + layers), counted in sweep order, of
 // direction pairs [q0, q1); its work items in a list.
 struct SweepPart {

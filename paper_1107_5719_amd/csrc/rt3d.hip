@@ -1270,7 +1270,8 @@ int rt3d_autotune(rt3d_ctx *c, const char *cache_path, int repeats, int *shape_o
     const int ns = n_sweep_shapes();
     char grid[96];
     std::snprintf(grid, sizeof grid, "%dx%dx%d|%dx%d", c->g.nx, c->g.ny, c->g.nz, c->g.n_theta, c->g.n_phi);
-    const std::string key = device_key() + "|" + (c->precision == RT3D_FP64 ? "fp64" : "fp32_sweep") + "|" + grid;
+    const std::string key = device_key() + "|" + (c->precision == RT3D_FP64 ? "fp64" : "fp32_sweep") + "|" + grid +
+                            (c->plan.columns ? rt3d_tune::kColumnKey : "");
     int cached = -1;
     if (cache_path && *cache_path && rt3d_tune::lookup(cache_path, key, cached) && cached >= 0 && cached < ns) {
         if (cached != c->sweep_shape) {
@@ -1288,11 +1289,19 @@ int rt3d_autotune(rt3d_ctx *c, const char *cache_path, int repeats, int *shape_o
         return fail(c, RT3D_ERR_HIP, "hipEventCreate");
     }
     std::vector<double> ms(ns, INFINITY);
+    std::vector<std::pair<int, rt3d::SweepKind>> timed;
     int rc = RT3D_OK;
     for (int s = 0; s < ns && !rc; ++s) {
         const int r = install_plan(c, s);
         if (r == RT3D_ERR_ARG) continue;      // the shape does not fit this grid
         if (r) { rc = r; break; }
+        const rt3d::SweepKind kind(c->plan);
+        const auto same = std::find_if(timed.begin(), timed.end(), [&](const auto &t) { return t.second == kind; });
+        if (same != timed.end()) {
+            ms[s] = ms[same->first];
+            continue;
+        }
+        timed.push_back({s, kind});
         rc = run_fs_plain(c);                 // warm-up
         if (!rc) rc = sync(c);
         if (!rc && hipEventRecord(e0, c->stream) != hipSuccess) rc = fail(c, RT3D_ERR_HIP, "hipEventRecord");
