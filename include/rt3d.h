@@ -19,7 +19,8 @@
  * every sweep bottom first instead of alternating; same iterates), RT3D_JACOBI_COLUMN (voxels per
  * thread of the column layout, 1, 2 or 4; default by grid size; same iterates), RT3D_JACOBI_WALK
  * (1: odd column layers walk top down, 0: never, -1 (default): for float coefficients in columns of 4;
- * same iterates), RT3D_ANCHOR_RATIO (re-anchoring ratio of the RT3D_FP32_SWEEP form, default 1e-2),
+ * same iterates; any setting of these four but the default one keeps every Jacobi sweep in a launch of its own, where grids
+ * up to 113^3 or so otherwise take two per launch), RT3D_ANCHOR_RATIO (re-anchoring ratio of the RT3D_FP32_SWEEP form, default 1e-2),
  * RT3D_DEVICE_BYTES (the most device memory that a context, or a batch's members when it is created,
  * may hold: beyond it allocations fail as they do when the device has no more; default no limit).
  *
@@ -237,7 +238,9 @@ int rt3d_get_emergent_top(rt3d_ctx *ctx, double *out, int ptr_kind);
  * sweep, reduce, Lambda*, coefficient and Jacobi kernels is bracketed by events; 2 sampled: the same
  * except for the inner sweeps of an OS step, of which the intermediate ones (all but the first, from
  * dJ = 0, and the last, which updates J) are timed as one group by a single pair of events (with two
- * or fewer sweeps the first is timed; Gauss-Seidel: its second sweep).  Mode 2 keeps the events' own
+ * or fewer sweeps the first is timed; Gauss-Seidel: its second sweep).  A launch of two Jacobi sweeps counts as two
+ * launches, so that total_ms / timed is the time of a sweep; mode 2 keeps a step's first and last sweep in launches of their
+ * own, modes 0 and 1 run the same launches.  Mode 2 keeps the events' own
  * cost (about 4% of a step with mode 1) out of the timed work.  Durations are accumulated with the
  * number of launches they cover (rt3d_get_stats: per kernel "launches", "timed", "total_ms");
  * changing the mode clears them.  Errors: RT3D_ERR_ARG. */
@@ -252,8 +255,8 @@ int rt3d_get_history(rt3d_ctx *ctx, double *c_out, double *ms_out, int *flags_ou
 
 /* Statistics as a NUL-terminated JSON object: grid, angles, precision, outer iterations, inner
  * sweeps, device bytes, the sweep plan (workgroups, shape, mean segments per voxel and angle, largest
- * deposit window in rows, LDS bytes of a sweep workgroup), and per-kernel {launches, total_ms} when
- * timing is enabled.
+ * deposit window in rows, LDS bytes of a sweep workgroup), Jacobi launches of two sweeps ("jacobi_pairs") and per-kernel
+ * {launches, total_ms} when timing is enabled.
  * Errors: RT3D_ERR_ARG (buffer too small or NULL). */
 int rt3d_get_stats(rt3d_ctx *ctx, char *json_buf, int buflen);
 

@@ -80,12 +80,13 @@ hipEvent_t get_event(rt3d_ctx *c)
 
 struct TimedLaunch {
     rt3d_ctx *c;
-    int kid;
+    int kid, n;
     hipEvent_t a = nullptr, b = nullptr;
     bool on;
-    // chosen: in sampled timing (mode 2) only the chosen launches are bracketed by events
-    TimedLaunch(rt3d_ctx *ctx, int id, bool chosen = true)
-        : c(ctx), kid(id), on(ctx->timing == 1 || (ctx->timing == 2 && chosen))
+    // chosen: in sampled timing (mode 2) only the chosen launches are bracketed by events.  count: what it counts for (a
+    // Jacobi launch of two sweeps: 2)
+    TimedLaunch(rt3d_ctx *ctx, int id, bool chosen = true, int count = 1)
+        : c(ctx), kid(id), n(count), on(ctx->timing == 1 || (ctx->timing == 2 && chosen))
     {
         if (on) {
             a = get_event(c);
@@ -98,9 +99,9 @@ struct TimedLaunch {
         if (on && a && b) {
             hipEventRecord(b, c->stream);
             c->pending.push_back({kid, a, b});
-            c->kernel_timed[kid] += 1;
+            c->kernel_timed[kid] += n;
         }
-        c->kernel_launches[kid] += 1;
+        c->kernel_launches[kid] += n;
     }
 };
 
@@ -318,9 +319,9 @@ int launch_jacobi_args(rt3d_ctx *c, const JacobiArgs &a, bool reverse = false);
 
 int jacobi_sweeps_at(const rt3d_ctx *c, int m, int M)
 {
-    // every setting of the layout but the default one asks for single sweeps, as does timing every launch
+    // every setting of the layout but the default one asks for single sweeps
     const bool plain = c->jacobi_xcd == 4 && c->jacobi_alternate && c->jacobi_height == 0 && c->jacobi_walk < 0;
-    if (!plain || c->timing == 1 || !jacobi_pair_pays(c->V, c->coef_fp32 != 0)) return 1;
+    if (!plain || !jacobi_pair_pays(c->V, c->coef_fp32 != 0)) return 1;
     // sampled timing keeps the first and the last sweep apart; otherwise an odd number has its first apart
     const int left = (c->timing == 2 ? M - 1 : M) - m;
     if (m == 0) return c->timing != 2 && left % 2 == 0 ? 2 : 1;
@@ -340,9 +341,9 @@ int launch_jacobi(rt3d_ctx *c, const double *w_in, double *w_out, bool update, i
     a.maxrel = c->d_maxrel; a.nonfinite = c->d_flag;
     a.Ja = (f32 && update) ? c->Ja : nullptr;
     a.maxdist = c->d_maxdist;
-    TimedLaunch t(c, K_JACOBI, chosen);
+    TimedLaunch t(c, K_JACOBI, chosen, n);
     if (n == 2) {
-        c->kernel_launches[K_JACOBI] += 1;
+        c->jacobi_pairs += 1;
         launch_jacobi_pair(a, c->jacobi_tile, c->coef_fp32 != 0, c->stream);
         return check_launch(c, "jacobi_kernel_pair");
     }
@@ -1193,6 +1194,7 @@ int rt3d_set_timing(rt3d_ctx *c, int enable)
     for (int k = 0; k < K_COUNT; ++k) {
         c->kernel_ms[k] = 0.0;
         c->kernel_launches[k] = 0;
+        c->jacobi_pairs = 0;
         c->kernel_timed[k] = 0;
     }
     return RT3D_OK;
@@ -1216,14 +1218,14 @@ int rt3d_get_stats(rt3d_ctx *c, char *buf, int buflen)
     int rc = sync(c);
     if (rc) return rc;
     std::string s = "{";
-    char tmp[1024];
+    char tmp[2048];
     const int jcol = c->jacobi_height > 0 ? c->jacobi_height : jacobi_column_height(c->g.nx, c->g.ny, c->g.nz);
     std::snprintf(tmp, sizeof tmp,
                   "\"nx\":%d,\"ny\":%d,\"nz\":%d,\"n_dir\":%d,\"precision\":\"%s\",\"outer_iters\":%ld,"
                   "\"inner_sweeps\":%ld,\"fp64_sweeps\":%ld,\"fp32_sweeps\":%ld,\"device_bytes\":%zu,\"partial_plane_bytes\":%lld,"
                   "\"sweep_workgroups\":%zu,\"sweep_shape\":%d,\"sweep_threads\":%d,\"sweep_lines\":%d,\"mean_segments\":%.6f,"
                   "\"max_window_rows\":%d,\"sweep_lds_bytes\":%zu,\"plan_level\":%d,"
-                  "\"os_method\":\"%s\",\"coef_storage\":\"%s\",\"jacobi_layout\":%d,\"jacobi_column\":%d,\"jacobi_alt_walk\":%d,"
+                  "\"os_method\":\"%s\",\"coef_storage\":\"%s\",\"jacobi_layout\":%d,\"jacobi_column\":%d,\"jacobi_alt_walk\":%d,\"jacobi_pairs\":%ld,"
                   "\"timing\":%d,\"kernels\":{",
                   c->g.nx, c->g.ny, c->g.nz, c->A.n_dir, c->precision == RT3D_FP64 ? "fp64" : "fp32_sweep",
                   c->outer_iters, c->inner_sweeps, c->fp64_sweeps, c->fp32_sweeps, c->device_bytes,
@@ -1232,7 +1234,7 @@ int rt3d_get_stats(rt3d_ctx *c, char *buf, int buflen)
                   c->plan.max_win_rows, sweep_smem_bytes(c->plan, c->precision != RT3D_FP64), c->plan_level,
                   c->os_method == RT3D_OS_GAUSS_SEIDEL ? "gauss_seidel" : "jacobi", c->coef_fp32 ? "fp32" : "fp64",
                   c->jacobi_xcd, jcol,
-                  (c->jacobi_xcd == 4 && jacobi_alt_walk(c->jacobi_walk, c->coef_fp32 != 0, jcol)) ? 1 : 0, c->timing);
+                  (c->jacobi_xcd == 4 && jacobi_alt_walk(c->jacobi_walk, c->coef_fp32 != 0, jcol)) ? 1 : 0, c->jacobi_pairs, c->timing);
     s += tmp;
     for (int k = 0; k < K_COUNT; ++k) {
         std::snprintf(tmp, sizeof tmp, "%s\"%s\":{\"launches\":%ld,\"timed\":%ld,\"total_ms\":%.6f}", k ? "," : "",
