@@ -594,7 +594,7 @@ int build_tables(rt3d_batch *b)
             a.base = v == 1 ? c->Fa : nullptr;
             a.rb = v == 2 ? nullptr : c->r;
             a.chunk = reduce_chunk_pairs(c->V, a.n_pair);
-            a.waves = reduce_waves(c->V, a.n_pair, a.chunk, kPlaneThreads / 64);
+            a.waves = reduce_waves(c->V, a.n_pair, a.chunk, kPlaneThreads / 64, c->plan.columns);
         }
         CopyArgs &k = cp[i];
         k.V = c->V;

@@ -493,10 +493,13 @@ inline int reduce_chunk_pairs(long V, int n_pair)
 // as many as bring the launch (a wavefront takes 128 voxels) up to about 8 wavefronts per SIMD; a
 // chain of pairs that each wait for memory is all that a small grid's reduction spends its time on (65^3 x 64 with
 // limits of 2, 4, 8 and 16: 56, 52, 46 and 50 us).
-inline int reduce_waves(long V, int n_pair, int chunk, int max_waves)
+// The window form's planes are wide: more waves on other pairs only take the caches from each other where the launch has
+// waves enough (600 x 20 x 20 x 256, 1875 wavefronts of voxels: 218, 176, 207 and 254 us with 1, 2, 4 and 8; 513 x 20 x 40 x 256,
+// 3206: 295, 313, 331, 421; 520 x 8 x 8 x 256, 260: 118, 61, 45, 35 and with 16 48), so it stops at 2 per SIMD.
+inline int reduce_waves(long V, int n_pair, int chunk, int max_waves, bool columns)
 {
     int w = 1;
-    while (2 * w <= std::min(max_waves, (n_pair + chunk - 1) / chunk) && V / 128 * w < 8192) w *= 2;
+    while (2 * w <= std::min(max_waves, (n_pair + chunk - 1) / chunk) && V / 128 * w < (columns ? 8192 : 2048)) w *= 2;
     return w;
 }
 
@@ -513,7 +516,7 @@ __device__ inline rt3d::LayerBlock layer_block(const ReduceArgs &a, int q, int k
     return lb;
 }
 
-// Bands of rows[0] rows each (COL: kColumnRows), the last one of fewer
+// Bands of lb's rows each (COL: kColumnRows), the last one of fewer
 template <bool COL>
 struct BandRow {
     int rows, nb, last;
@@ -521,10 +524,18 @@ struct BandRow {
     __device__ BandRow(const rt3d::LayerBlock &lb, int ny, int j)
     {
         rows = COL ? rt3d::kColumnRows : lb.flags >> rt3d::kBlockRows;
-        nb = (ny + rows - 1) / rows;
-        last = ny - (nb - 1) * rows;
         int jj = j - lb.rmin;
         jj += (jj < 0) ? ny : 0;
+        if (!COL && rows == 1) {
+            // what the default shape leaves of a band in the window form: no divisions
+            nb = ny;
+            last = 1;
+            b = jj;
+            off = 0;
+            return;
+        }
+        nb = (ny + rows - 1) / rows;
+        last = ny - (nb - 1) * rows;
         b = jj / rows;
         off = jj - b * rows;
     }
@@ -584,7 +595,7 @@ __device__ inline void reduce_group(const ReduceArgs &a, const rt3d::LayerBlock 
             const real *Pq = Pi + lb[u].off;
             BandRow<COL> r(lb[u], a.ny, j);
             r.back();
-            if (!(lb[u].flags & rt3d::kBlockDown)) {
+            if (!COL || !(lb[u].flags & rt3d::kBlockDown)) {      // (the window form marks none)
                 while (r.before(lb[u].span)) {
                     r.back();
                     const real2 z = *reinterpret_cast<const real2 *>(Pq + r.at(lb[u], a.nx));
@@ -717,7 +728,9 @@ __device__ inline ReduceVoxels reduce_voxels(const ReduceArgs &a, int p2, int k)
 // 4.8 TB/s; 4 pairs' loads in flight per wave, a row's address by one scalar load and a few integer operations per
 // pair), the chain of pairs on small ones.  us per launch with one chain of pairs per voxel and the tables read
 // by vector loads, and now: 17^3 x 64 45 and 7, 65^3 x 64 55 and 33, 65^3 x 256 193 and 159, 129^3 x 256 654 and 642,
-// 129 x 129 x 193 x 256 in float32 746 and 645, the benchmark batch of 12 grids up to 97^3 417 and 290.
+// 129 x 129 x 193 x 256 in float32 746 and 645, the benchmark batch of 12 grids up to 97^3 417 and 290.  Window form (float64 /
+// float32): 600 x 20 x 20 x 256 204 / 161 and 179 / 115, 600 x 200 x 40 x 64 719 / 463 and 716 / 416, 1000 x 30 x 30 x 64 174 / 92
+// and 171 / 77, 1024 x 40 x 10 x 128 147 / 94 and 145 / 95, 513 x 64 x 64 x 256 1247 / 837 and 1292 / 759.
 template <typename real, bool COL>
 __device__ inline void reduce_body(const ReduceArgs &a, int b, int k, double2 *part)
 {
@@ -770,7 +783,7 @@ inline void launch_reduce_kernel(ReduceArgs &a, bool columns, bool f32, hipStrea
 {
     const long V = long(a.nx) * a.ny * a.nz;
     a.chunk = reduce_chunk_pairs(V, a.n_pair);
-    a.waves = reduce_waves(V, a.n_pair, a.chunk, 16);
+    a.waves = reduce_waves(V, a.n_pair, a.chunk, 16, columns);
     const int threads = reduce_threads(a);
     const dim3 grid(reduce_blocks(a, threads), a.nz);
     const size_t smem = reduce_smem_bytes(a, threads);
