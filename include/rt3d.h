@@ -255,7 +255,8 @@ int rt3d_get_history(rt3d_ctx *ctx, double *c_out, double *ms_out, int *flags_ou
 
 /* Statistics as a NUL-terminated JSON object: grid, angles, precision, outer iterations, inner
  * sweeps, device bytes, the sweep plan (workgroups, shape, mean segments per voxel and angle, largest
- * deposit window in rows, LDS bytes of a sweep workgroup), Jacobi launches of two sweeps ("jacobi_pairs") and per-kernel
+ * deposit window in rows, LDS bytes of a sweep workgroup), Jacobi launches of two sweeps ("jacobi_pairs"), how
+ * Lambda* is built ("lstar_form": "tiles", "symmetric" voxel by voxel, or "full") and per-kernel
  * {launches, total_ms} when timing is enabled.
  * Errors: RT3D_ERR_ARG (buffer too small or NULL). */
 int rt3d_get_stats(rt3d_ctx *ctx, char *json_buf, int buflen);

@@ -1219,13 +1219,15 @@ int rt3d_get_stats(rt3d_ctx *c, char *buf, int buflen)
     if (rc) return rc;
     std::string s = "{";
     char tmp[2048];
+    LstarArgs la;
+    lstar_args(c, la);
     const int jcol = c->jacobi_height > 0 ? c->jacobi_height : jacobi_column_height(c->g.nx, c->g.ny, c->g.nz);
     std::snprintf(tmp, sizeof tmp,
                   "\"nx\":%d,\"ny\":%d,\"nz\":%d,\"n_dir\":%d,\"precision\":\"%s\",\"outer_iters\":%ld,"
                   "\"inner_sweeps\":%ld,\"fp64_sweeps\":%ld,\"fp32_sweeps\":%ld,\"device_bytes\":%zu,\"partial_plane_bytes\":%lld,"
                   "\"sweep_workgroups\":%zu,\"sweep_shape\":%d,\"sweep_threads\":%d,\"sweep_lines\":%d,\"mean_segments\":%.6f,"
                   "\"max_window_rows\":%d,\"sweep_lds_bytes\":%zu,\"plan_level\":%d,"
-                  "\"os_method\":\"%s\",\"coef_storage\":\"%s\",\"jacobi_layout\":%d,\"jacobi_column\":%d,\"jacobi_alt_walk\":%d,\"jacobi_pairs\":%ld,"
+                  "\"os_method\":\"%s\",\"coef_storage\":\"%s\",\"jacobi_layout\":%d,\"jacobi_column\":%d,\"jacobi_alt_walk\":%d,\"jacobi_pairs\":%ld,\"lstar_form\":\"%s\","
                   "\"timing\":%d,\"kernels\":{",
                   c->g.nx, c->g.ny, c->g.nz, c->A.n_dir, c->precision == RT3D_FP64 ? "fp64" : "fp32_sweep",
                   c->outer_iters, c->inner_sweeps, c->fp64_sweeps, c->fp32_sweeps, c->device_bytes,
@@ -1234,7 +1236,8 @@ int rt3d_get_stats(rt3d_ctx *c, char *buf, int buflen)
                   c->plan.max_win_rows, sweep_smem_bytes(c->plan, c->precision != RT3D_FP64), c->plan_level,
                   c->os_method == RT3D_OS_GAUSS_SEIDEL ? "gauss_seidel" : "jacobi", c->coef_fp32 ? "fp32" : "fp64",
                   c->jacobi_xcd, jcol,
-                  (c->jacobi_xcd == 4 && jacobi_alt_walk(c->jacobi_walk, c->coef_fp32 != 0, jcol)) ? 1 : 0, c->jacobi_pairs, c->timing);
+                  (c->jacobi_xcd == 4 && jacobi_alt_walk(c->jacobi_walk, c->coef_fp32 != 0, jcol)) ? 1 : 0, c->jacobi_pairs,
+                  la.tx > 0 ? "tiles" : la.T ? "symmetric" : "full", c->timing);
     s += tmp;
     for (int k = 0; k < K_COUNT; ++k) {
         std::snprintf(tmp, sizeof tmp, "%s\"%s\":{\"launches\":%ld,\"timed\":%ld,\"total_ms\":%.6f}", k ? "," : "",
