@@ -1658,7 +1658,12 @@ __global__ __launch_bounds__(rt3d::kPairThreads) void jacobi_kernel_pair(JacobiA
 }
 
 // Grids up to these numbers of voxels take two sweeps per launch: between the sizes above where it pays and where it
-// does not.  (Its buffer offsets need 13 coefficients of all voxels to stay below 4 GB.)
+// does not.  On 30 grids that are no cubes (flat, tall, long, thin) the number of voxels decides as well: with float64 coefficients pairs
+// won on all of them, 200 x 200 x 8 13.5 and 11.0 us per sweep, 8 x 8 x 500 11.9 and 3.9, 193 x 193 x 42 47.0 and 37.8, 512 x 300 x 10 42.1
+// and 40.4, 1000 x 50 x 31 47.5 and 44.5, 60 x 60 x 400 44.4 and 35.3; with float ones they are even around the limit (40 x 200 x 24 9.1 and
+// 9.6, 24 x 40 x 200 9.3 and 8.2, 129 x 129 x 20 10.9 and 10.9) and lose above (129 x 129 x 90 27.1 and 33.9, 1000 x 50 x 31 29.4 and 37.2) but
+// for narrow towers (24 x 24 x 1500 25.8 and 21.6).
+// (Its buffer offsets need 13 coefficients of all voxels to stay below 4 GB.)
 inline bool jacobi_pair_pays(long V, bool f32) { return V <= (f32 ? 3L << 16 : 3L << 19); }
 
 inline void launch_jacobi_pair(const JacobiArgs &a, const rt3d::JacobiTile &t, bool f32, hipStream_t stream)
