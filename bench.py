@@ -35,17 +35,12 @@ SCHEDULES = [(12, 3, 6), (20, 3, 6), (30, 3, 6), (40, 3, 6), (12, 3, 8), (20, 3,
 AA_SCHEDULES = [(12, 5), (20, 5), (30, 5), (12, 8), (20, 8), (30, 8)]
 
 
-SWEEP_G = 2   # directions that share one gather of a voxel's chi, S and one partial-plane deposit
-
-
-def sweep_bytes_per_update(precision: str, G: int = SWEEP_G) -> int:
-    """Algorithmic HBM bytes of the formal-solution sweep per voxel-angle update, (2 s_r + 16) / G: chi
-    and S of the voxel (s_r bytes each: 8 in float64, 4 in float32 sweeps) and a float64 read-modify-
-    write of the voxel's J partial, shared by the G directions that use one gather and one deposit
-    (G = 2 here: the lines of an x-mirrored direction pair are paired so that both cross the same
-    voxel at every segment, and the pair has one partial plane)."""
+def sweep_bytes(precision: str, n_vox: int, n_dir: int, plane_elems: int) -> int:
+    """Bytes that a formal solution's sweep moves at least: every pair of x-mirrored directions reads {chi, S} of
+    every voxel once (s_r bytes each: 8 in float64, 4 in float32 sweeps), and every element of the pairs' partial
+    planes (plane_elems in all: the rows that a band's lines come through, each stored once) is written once."""
     s_r = 8 if precision == "fp64" else 4
-    return (2 * s_r + 16) // G
+    return n_dir // 2 * n_vox * 2 * s_r + plane_elems * s_r
 
 
 def jacobi_bytes_per_voxel(coef: str) -> int:
@@ -542,33 +537,31 @@ def main() -> int:
                                                for k, v in per_launch.items()},
                       "lstar_build_s": round(lstar_s, 4),
                       "sweeps": {"fp64": st["fp64_sweeps"], "fp32": st["fp32_sweeps"]}}
+        plane_elems = st["partial_plane_bytes"] // 8
     main_form = args.precision
     upd = V * n_dir
 
     def sweep_roofline(form):
-        """The sweep against HBM with the algorithmic bytes (2 s_r + 16)/G per voxel-angle update at
-        G = SWEEP_G, from its average launch time in the timed steps (HIP events on the context
-        stream)."""
+        """The sweep from its average launch time in the timed steps (HIP events on the context stream): the vector
+        instructions it issues (rocprofv3 SQ_INSTS_VALU x 64 lanes) against the chip's issue rate for its precision, which
+        bounds it, and beside it the bytes that it has to move (sweep_bytes) and those that it did (rocprofv3 FETCH_SIZE +
+        WRITE_SIZE per launch) against HBM.  Without counters of these sources the bytes stand in front."""
         sweep_ms = step[form]["kernel_ms_per_launch"]["sweep"]
-        upd_per_s = upd / (sweep_ms * 1e-3)
-        b_unit = sweep_bytes_per_update(form)
-        gbs = b_unit * upd_per_s / 1e9
+        t = sweep_ms * 1e-3
+        need = sweep_bytes(form, V, n_dir, plane_elems)
         traffic = measured_traffic(SWEEP_KERNEL[form])
         valu = measured_valu(SWEEP_KERNEL[form])
-        r = {"kernel": SWEEP_KERNEL[form], "bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
-             "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
-             "G": SWEEP_G, "bytes_per_update": b_unit, "updates_per_launch": upd, "ms_per_launch": sweep_ms}
-        # beside it: the measured HBM traffic (rocprofv3 FETCH_SIZE + WRITE_SIZE per launch) over the same
-        # duration, and the vector issue (rocprofv3 SQ_INSTS_VALU x 64 lanes per update) against the
-        # chip's issue rate for the sweep's precision
-        r["counter_view"] = None if traffic is None else {
-            "achieved": round(traffic / (sweep_ms * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(traffic / (sweep_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-            "bytes_per_update": round(traffic / upd, 2)}
-        r["alu_view"] = None if valu is None else {
-            "achieved": round(64 * valu / (sweep_ms * 1e-3) / 1e12, 2), "peak": VALU_ISSUE_PEAK[form] / 1e12,
-            "unit": "T lane-instructions/s", "frac": round(64 * valu / (sweep_ms * 1e-3) / VALU_ISSUE_PEAK[form], 4),
+
+        def hbm(n):
+            return {"bound": "hbm", "achieved": round(n / t / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(n / t / 1e9 / HBM_PEAK_GBS, 4), "bytes_per_update": round(n / upd, 2)}
+
+        alu = None if valu is None else {
+            "bound": "valu", "achieved": round(64 * valu / t / 1e12, 2), "peak": VALU_ISSUE_PEAK[form] / 1e12,
+            "unit": "T lane-instructions/s", "frac": round(64 * valu / t / VALU_ISSUE_PEAK[form], 4),
             "lane_instructions_per_update": round(64 * valu / upd, 1)}
+        r = {"kernel": SWEEP_KERNEL[form], **(alu or hbm(need)), "traffic": traffic, "updates_per_launch": upd,
+             "ms_per_launch": sweep_ms, "hbm_view": hbm(need), "counter_view": None if traffic is None else hbm(traffic)}
         return r
 
     roofline = sweep_roofline(main_form)
