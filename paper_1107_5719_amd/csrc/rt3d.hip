@@ -689,6 +689,7 @@ int create_ctx(rt3d_ctx **out, const rt3d_grid_desc *g, int precision, hipStream
     chk(dev_alloc(c, &c->d_scal, kScalarBytes / sizeof(unsigned long long)));
     if (!rc && hipHostMalloc(reinterpret_cast<void **>(&c->h_scal), kScalarBytes, hipHostMallocDefault) != hipSuccess) {
         c->h_scal = nullptr;
+        hipGetLastError();
         rc = fail(c, RT3D_ERR_OOM, "hipHostMalloc");
     }
     if (!rc) {
