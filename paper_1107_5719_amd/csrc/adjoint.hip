@@ -120,7 +120,7 @@ __device__ inline long seg_voxel(const AdjLineArgs &a, int i0, int j0, int k, in
 }
 
 // Forward pass: the intensity entering every layer of every line (the formal solution's recurrence).
-// One line per thread; 65^3 x 64 254 us with two integer divisions and a library expm1 per segment, 207 us so (bound by
+// One line per thread; 65^3 x 64 254 us with two integer divisions and a library expm1 per segment, 212 us so (bound by
 // the gathers of the shallowest lines, one after the other; loading a layer's segments ahead changed nothing).
 __global__ __launch_bounds__(kLineThreads) void adj_record_kernel(AdjLineArgs a)
 {
@@ -156,7 +156,7 @@ __device__ inline double deposit_weight(const AdjLineArgs &a, long v, double wmu
 
 // Backward pass: q from the end of every line back to its start, stored where it leaves each layer.
 // Without nu downward lines carry nothing (up_only: blockIdx.y counts the upward directions).  65^3 x 64 294 us before
-// (as adj_record_kernel), 306 with and 174 without nu now.
+// (as adj_record_kernel), 300 with and 167 without nu now.
 __global__ __launch_bounds__(kLineThreads) void adj_back_kernel(AdjLineArgs a, int up_only)
 {
     const double *tab = line_exp_table(a);
@@ -210,7 +210,7 @@ __global__ void adj_bc_kernel(AdjLineArgs a, const double *B, double *pull)
 //   mode 0:  out = a_v / chi_v,  a_v = sum q_out (1 - e)                  (nu == null)
 //   mode 1:  out = sum l (c S + (c - q_out)(I_in - S) e)
 // (mode 0: the upward directions only, downward lines carry nothing.)  65^3 x 64 690 and 1330 us in modes 0 and 1 with
-// integer divisions and library exponentials per segment, 206 and 874 us so.
+// integer divisions and library exponentials per segment, 212 and 898 us so.
 __global__ __launch_bounds__(kPlaneThreads) void adj_pull_kernel(AdjLineArgs a, int mode, double *out)
 {
     const double *tab = line_exp_table(a);

@@ -17,8 +17,8 @@
 // shallowest directions, 450 + 165 R cycles each, hence R = 1 for those (make_column_plan).  The form
 // that it replaces moved the lines through an LDS window of voxels instead, a gather, two LDS exchanges
 // and a read-modify-write of the window per segment: the sweep took 2170 us at 129^3 x 256, 621 at 65^3 x 256, 70 at
-// 17^3 x 64 and about 2240 in float32 at 129 x 129 x 193 x 256, against 1740, 268, 30 and 1600
-// here.  Tried and slower: loading the next layer's rows ahead (more moves than latency saved),
+// 17^3 x 64 and about 2240 in float32 at 129 x 129 x 193 x 256, against 1810 to 1880 (shortest launch 1750), 290, 30 and
+// 1710 (1610) here.  Tried and slower: loading the next layer's rows ahead (more moves than latency saved),
 // exchanging by DPP wave shifts instead of LDS, window deposits by LDS atomics.
 #pragma once
 
