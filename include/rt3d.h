@@ -329,7 +329,7 @@ int rt3d_autotune(rt3d_ctx *ctx, const char *cache_path, int repeats, int *shape
  * re-anchoring and Ng schedule are decided on the device with the rules of rt3d_os_step,
  * rt3d_solve_to_convergence and rt3d_set_acceleration, and the arithmetic is that of a single
  * context, so a member's iterates are bitwise those of solving it alone in a context with the same
- * sweep shape.  Member buffers follow the layouts above. */
+ * sweep shape (to rounding where one of the two had to take the plan of level 2, see rt3d_create).  Member buffers follow the layouts above. */
 typedef struct rt3d_batch rt3d_batch;
 
 enum {
